@@ -313,13 +313,14 @@ int dm_mlp_load(const dm_constellation* c, const char* path, dm_mlp** out);
  *   labels_out  HOST array of n_blk DEVICE pointers (N uint16 decided LABELS each) or NULL.
  *   sym_err, bit_err  HOST int64 n_blk outputs, or NULL (no counting).
  *   method      DM_HARD_AUTO, DM_HARD_VALU or DM_HARD_MFMA (see below); all give the same decisions.
- *   n_exact     HOST int64 or NULL: symbols the MFMA method passed to the exact path.
+ *   n_exact     HOST int64 or NULL: symbols whose decision the MFMA ranking alone does not prove
+ *               (runner-up within the error bound, or values outside the operand range).
  * The decision is defined by FP32 distances t_d = y_d - x_d, acc = fma(t_d, t_d, acc) for
  * d = 0..D-1 from acc = 0, ties to the lowest label.  DM_HARD_VALU evaluates exactly that for
- * every point.  DM_HARD_MFMA (M >= 32, D <= 8, point norms^2 < 60000) ranks the points with a
- * split-FP16 MFMA cross term and accepts its winner only when the gap to the runner-up exceeds
- * twice a bound on the error of both computations; other symbols are decided by the FP32
- * formula.  DM_HARD_AUTO picks DM_HARD_MFMA when it applies.  Bit errors are the popcount of
+ * every point.  DM_HARD_MFMA (M >= 32, D <= 8, point norms^2 < 60000) ranks groups of 16 points
+ * with a split-FP16 MFMA cross term and, when the gap to the runner-up group exceeds twice a
+ * bound on the error of both computations, decides among the winning group's points by the FP32
+ * formula; other symbols are decided by the FP32 formula over the whole table.  DM_HARD_AUTO picks DM_HARD_MFMA when it applies.  Bit errors are the popcount of
  * (decided label XOR sent label).  Synchronises `stream` when counting or when n_exact is given.
  * Errors: DM_EINVAL, DM_EUNSUPPORTED, DM_EHIP, DM_ENOMEM.
  */

@@ -90,8 +90,10 @@ struct HardArgs {
     uint16_t* labels_out[kMaxSnrPerLaunch];  // decided labels per block, or null
     int64_t N, tiles_per_blk;
     int M, D, n_blk;
-    unsigned long long* counts;  // [n_blk][2]: symbol errors, bit errors; null = no counting
+    unsigned long long* counts;  // [n_blk][kAccSlots][2]: symbol errors, bit errors; null = no counting
     uint32_t* bad_tx;
+    uint32_t* exact;             // MFMA method, or null: kQueueRegions counters, kQueueStride words apart, of
+                                 // the symbols that the matrix ranking alone does not decide
 };
 
 // Multi-SNR launch over one constellation and one transmitted block.

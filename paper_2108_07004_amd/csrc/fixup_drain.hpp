@@ -4,42 +4,11 @@
 // includes; this file only the fix-up kernels do.
 #pragma once
 #include "device_common.hpp"
+#include "wave_reduce.hpp"
 
 namespace dm {
 
 // ---- wave-cooperative fix-up: one wavefront per queued symbol, lanes split the points ----
-
-// Wave-wide max / sum of one float per lane, every lane receiving the result, in VALU only
-// (the whole wave must be active): v_permlane32_swap and v_permlane16_swap pair lanes 32 and 16
-// apart (the two outputs hold the pair in both lanes), then DPP row rotations by 8, 4, 2, 1
-// combine the 16 lanes of each row.  No LDS round trips on the fix-up's dependent chains.
-template <int CTRL>
-__device__ __forceinline__ float dpp_f(float v) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, false));
-}
-
-template <typename Op>
-__device__ __forceinline__ float wave_reduce_f(float v, Op op) {
-    const uint32_t u = __builtin_bit_cast(uint32_t, v);
-    const auto a = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-    v = op(__builtin_bit_cast(float, (uint32_t)a[0]), __builtin_bit_cast(float, (uint32_t)a[1]));
-    const uint32_t w = __builtin_bit_cast(uint32_t, v);
-    const auto b = __builtin_amdgcn_permlane16_swap(w, w, false, false);
-    v = op(__builtin_bit_cast(float, (uint32_t)b[0]), __builtin_bit_cast(float, (uint32_t)b[1]));
-    v = op(v, dpp_f<0x128>(v));  // row_ror:8
-    v = op(v, dpp_f<0x124>(v));  // row_ror:4
-    v = op(v, dpp_f<0x122>(v));  // row_ror:2
-    v = op(v, dpp_f<0x121>(v));  // row_ror:1
-    return v;
-}
-
-__device__ __forceinline__ float wave_max_f(float v) {
-    return wave_reduce_f(v, [](float x, float y) { return fmaxf(x, y); });
-}
-
-__device__ __forceinline__ float wave_sum_f(float v) {
-    return wave_reduce_f(v, [](float x, float y) { return x + y; });
-}
 
 // Exact subset log-sum-exps of label bit p (p < 0: all points into subset 0) for one symbol,
 // computed by the whole wavefront; returns (log2 S^1 - log2 S^0) and, via lse0, log2 S^0.

@@ -6,6 +6,7 @@
 #include <cstring>
 #include <limits>
 #include <mutex>
+#include <vector>
 
 #include "api_internal.hpp"
 #include "kernels.hpp"
@@ -45,10 +46,10 @@ int dm_hard_decision(const dm_constellation* cc, int n_blk, const float* const* 
         if (labels_out && (r = dmapi::check_device_ptr(labels_out[s], "labels_out[s]", c->device))) return r;
     }
     std::lock_guard<std::mutex> lock(c->mu);
-    if ((r = dmapi::ensure_scratch(c, use_mfma ? (uint64_t)N * std::min(n_blk, dm::kMaxSnrPerLaunch) : 0))) return r;
+    if ((r = dmapi::ensure_scratch(c, 0))) return r;
     if (use_mfma && (r = dmapi::ensure_frag(c, DM_PREC_FP16X3, false))) return r;
     hipStream_t st = (hipStream_t)stream;
-    const int tile = use_mfma ? dm::hard_mfma_block_symbols() : dm::hard_tile_symbols();
+    const int tile = dm::hard_tile_symbols();
     int64_t exact_total = 0;
     for (int s0 = 0; s0 < n_blk; s0 += dm::kMaxSnrPerLaunch) {
         const int nb = std::min(dm::kMaxSnrPerLaunch, n_blk - s0);
@@ -69,36 +70,41 @@ int dm_hard_decision(const dm_constellation* cc, int n_blk, const float* const* 
         a.counts = counting ? c->d_acc : nullptr;
         a.bad_tx = counting ? c->d_fix_pairs + dm::kMaxSnrPerLaunch : nullptr;
         if (counting) {
-            DM_HIP_TRY(hipMemsetAsync(c->d_acc, 0, sizeof(unsigned long long) * 2 * nb, st));
+            DM_HIP_TRY(hipMemsetAsync(c->d_acc, 0, sizeof(unsigned long long) * 2 * dm::kAccSlots * nb, st));
             DM_HIP_TRY(hipMemsetAsync(a.bad_tx, 0, sizeof(uint32_t), st));
         }
-        const int64_t work = a.tiles_per_blk * nb;
         if (use_mfma) {
-            DM_HIP_TRY(hipMemsetAsync(c->d_queue_count, 0, sizeof(uint32_t), st));
-            const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(work, (int64_t)c->cus));
-            DM_HIP_TRY(dm::launch_hard_mfma(a, c->d_frag[DM_PREC_FP16X3], std::sqrt(c->max_norm), c->d_queue,
-                                            c->d_queue_count, c->queue_cap, grid, st));
-            DM_HIP_TRY(dm::launch_hard_fix(a, c->d_queue, c->d_queue_count, c->queue_cap, c->cus * 4, st));
+            a.exact = n_exact ? c->d_queue_count : nullptr;
+            if (n_exact)
+                DM_HIP_TRY(hipMemsetAsync(c->d_queue_count, 0, sizeof(uint32_t) * dm::kQueueCounterWords, st));
+            DM_HIP_TRY(dm::launch_hard_mfma(a, c->d_frag[DM_PREC_FP16X3], std::sqrt(c->max_norm), c->cus, st));
         } else {
-            const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(work, (int64_t)c->cus * 2));
+            const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(a.tiles_per_blk * nb, (int64_t)c->cus * 2));
             DM_HIP_TRY(dm::launch_hard_demap(a, grid, st));
         }
         if (use_mfma && n_exact) {
-            uint32_t q = 0;
-            DM_HIP_TRY(hipMemcpyAsync(&q, c->d_queue_count, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+            std::vector<uint32_t> q(dm::kQueueCounterWords);
+            DM_HIP_TRY(hipMemcpyAsync(q.data(), c->d_queue_count, sizeof(uint32_t) * dm::kQueueCounterWords,
+                                      hipMemcpyDeviceToHost, st));
             DM_HIP_TRY(hipStreamSynchronize(st));
-            exact_total += q;
+            for (int k = 0; k < dm::kQueueRegions; ++k) exact_total += q[(size_t)k * dm::kQueueStride];
         }
         if (counting) {
             auto* h = (unsigned long long*)c->h_stage;
-            auto* bad = (uint32_t*)(h + 2 * dm::kMaxSnrPerLaunch);
-            DM_HIP_TRY(hipMemcpyAsync(h, c->d_acc, sizeof(unsigned long long) * 2 * nb, hipMemcpyDeviceToHost, st));
+            auto* bad = (uint32_t*)(h + 2 * dm::kAccSlots * dm::kMaxSnrPerLaunch);
+            DM_HIP_TRY(hipMemcpyAsync(h, c->d_acc, sizeof(unsigned long long) * 2 * dm::kAccSlots * nb,
+                                      hipMemcpyDeviceToHost, st));
             DM_HIP_TRY(hipMemcpyAsync(bad, a.bad_tx, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
             DM_HIP_TRY(hipStreamSynchronize(st));
             if (*bad) return fail(DM_EINVAL, "a transmitted index is >= M");
             for (int s = 0; s < nb; ++s) {
-                if (sym_err) sym_err[s0 + s] = (int64_t)h[2 * s];
-                if (bit_err) bit_err[s0 + s] = (int64_t)h[2 * s + 1];
+                int64_t se = 0, be = 0;
+                for (int k = 0; k < dm::kAccSlots; ++k) {
+                    se += (int64_t)h[2 * ((size_t)s * dm::kAccSlots + k)];
+                    be += (int64_t)h[2 * ((size_t)s * dm::kAccSlots + k) + 1];
+                }
+                if (sym_err) sym_err[s0 + s] = se;
+                if (bit_err) bit_err[s0 + s] = be;
             }
         }
     }

@@ -10,6 +10,7 @@
 // resolves ties to the lowest label.  Errors are counted in integers (deterministic).
 #include "device_common.hpp"
 #include "kernels.hpp"
+#include "wave_reduce.hpp"
 
 namespace dm {
 
@@ -32,21 +33,13 @@ __global__ __launch_bounds__(kHardThreads) void hard_demap_kernel(const HardArgs
         __syncthreads();
     }
     const int64_t total = a.tiles_per_blk * a.n_blk;
-    // Error counts accumulate per lane and go out once per received block and wave: one counter
-    // address per block, and device-scope atomics on one address serialise (~11 ns each).
+    // Error counts accumulate per lane and go out once per received block and wave, spread over
+    // kAccSlots addresses (device-scope atomics on one address serialise at ~11 ns each).
+    const int wave_slot = (blockIdx.x * (kHardThreads / 64) + (tid >> 6)) % kAccSlots;
     uint32_t se = 0, be = 0;
     int cur = -1;
     auto flush = [&]() {
-        if (cur < 0 || !a.counts) return;
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) {
-            se += __shfl_xor(se, off, 64);
-            be += __shfl_xor(be, off, 64);
-        }
-        if (lane == 0) {
-            if (se) atomicAdd(a.counts + 2 * cur, (unsigned long long)se);
-            if (be) atomicAdd(a.counts + 2 * cur + 1, (unsigned long long)be);
-        }
+        if (cur >= 0 && a.counts) hard_flush(a.counts, cur, wave_slot, lane, se, be);
         se = be = 0;
     };
     for (int64_t tile = blockIdx.x; tile < total; tile += gridDim.x) {

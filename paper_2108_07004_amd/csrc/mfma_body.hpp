@@ -169,6 +169,31 @@ __device__ __forceinline__ Frags<T, Slots<D, SPLIT>::S> build_symbol_frags(const
     return bf;
 }
 
+// Operand fragments of the 64 symbols of a wave that owns one symbol per lane: f0 those of lanes
+// 0..31, f1 those of lanes 32..63, as build_symbol_frags gives them for 32 symbols held by both
+// lane halves.  Every lane splits only its own symbol into the K-slot halves of its column; one
+// v_permlane32_swap of a lower-half word a and an upper-half word b then yields both fragments'
+// words (lower lanes a, upper lanes b, of symbols i and i + 32).
+template <typename T, int D, bool SPLIT>
+__device__ __forceinline__ void build_pair_frags(const float (&y)[D], float c, float K,
+                                                 Frags<T, Slots<D, SPLIT>::S>& f0, Frags<T, Slots<D, SPLIT>::S>& f1,
+                                                 bool& bad) {
+    constexpr int S = Slots<D, SPLIT>::S;
+    const Frags<T, S> lo = build_symbol_frags<T, D, SPLIT>(y, c, K, 0, bad);
+    const Frags<T, S> hi = build_symbol_frags<T, D, SPLIT>(y, c, K, 1, bad);
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+        const uint4 a = __builtin_bit_cast(uint4, lo.v[s]), b = __builtin_bit_cast(uint4, hi.v[s]);
+        uint4 r0, r1;
+        swap_halves(a.x, b.x, r0.x, r1.x);
+        swap_halves(a.y, b.y, r0.y, r1.y);
+        swap_halves(a.z, b.z, r0.z, r1.z);
+        swap_halves(a.w, b.w, r0.w, r1.w);
+        f0.v[s] = __builtin_bit_cast(typename Mma<T>::V, r0);
+        f1.v[s] = __builtin_bit_cast(typename Mma<T>::V, r1);
+    }
+}
+
 struct MfmaAcc {
     float accA[16], accB[4], accC[4], hi0[7], hi1[7];
     __device__ __forceinline__ void init() {
