@@ -5,9 +5,9 @@
 //   FP32 masters, Adam moments and gradients in one internal layout
 //     W1t [256 x 32] (out x in, inputs >= D+1 stay zero) | b1 [256] | W2t [256 x 256] | b2 [256] |
 //     W3t [32 x 256] (outputs >= m stay zero) | b3 [32]
-//   BF16 copies rewritten by every Adam step: W1t, W2t, W3t (forward B operands) and W2, W3
-//   (transposes, backward B operands); the inference fragment table and bias vector are
-//   rebuilt from them lazily.
+//   BF16 copies rewritten by every Adam step, in MFMA operand order: W1t, W2t, W3t (forward B
+//   operands) and W2, W3 (transposes, backward B operands); the inference fragment table and
+//   bias vector are rebuilt from the masters lazily.
 // The external weight order (host arrays) is the textbook one: W1 [(D+1) x 256] with
 // out = x W + b, b1, W2 [256 x 256], b2, W3 [256 x m], b3 [m].
 #include <hip/hip_runtime.h>
@@ -60,14 +60,8 @@ struct dm_mlp {
     bool frag_dirty = true;
     // batch scratch (grow-only)
     int B = 0;
-    __bf16 *X = nullptr, *Xt = nullptr, *A1 = nullptr, *A1T = nullptr, *A2 = nullptr, *A2T = nullptr;
-    __bf16 *dO = nullptr, *dOT = nullptr, *dH2 = nullptr, *dH2T = nullptr, *dH1T = nullptr;
-    // Activations and deltas are BF16 pairs: each allocation above except X / Xt holds the hi
-    // words, then the lo words (these pointers, into the same allocations).
-    __bf16 *A1lo = nullptr, *A1Tlo = nullptr, *A2lo = nullptr, *A2Tlo = nullptr, *dOlo = nullptr, *dOTlo = nullptr;
-    __bf16 *dH2lo = nullptr, *dH2Tlo = nullptr, *dH1Tlo = nullptr;
-    float *H1 = nullptr, *H2 = nullptr, *part = nullptr, *loss_hist = nullptr;
-    size_t part_floats = 0;
+    __bf16 *Xf = nullptr, *A1f = nullptr, *A2f = nullptr, *dOf = nullptr, *dH2f = nullptr, *dH1f = nullptr;
+    float *part = nullptr, *loss_hist = nullptr;  // part: split-K partials of W2t | W1t | W3t, bias sums
     float* targets = nullptr;
     int64_t target_rows = 0;
     unsigned long long* acc = nullptr;  // [n_snr][2][kAccSlots][2]
@@ -154,14 +148,30 @@ void tensors(const dm_mlp* n, Tensor t[6]) {
     t[5] = Tensor{oB3, 1, 32, 1, n->m, nullptr, nullptr};
 }
 
-// Adam step on every tensor (lr == 0 and mask_rows == 0: only rewrite the BF16 copies).
-int adam_all(dm_mlp* n, bool update, float lr, float b1, float b2, float eps, double bc1, double bc2,
+constexpr int kSplits2 = 16, kSplits13 = 64;  // most splits of the batch in dW2, and in dW1 and dW3
+constexpr size_t kPartFloats = (size_t)kSplits2 * 65536 + 2 * (size_t)kSplits13 * 8192;
+
+// Largest power-of-two split of the batch into chunks that are multiples of 16.
+int k_splits(int B, int cap) {
+    int s = cap;
+    while (s > 1 && (B % s != 0 || (B / s) % 16 != 0)) s >>= 1;
+    return s;
+}
+
+enum AdamStep { kCopiesOnly, kGradOnly, kGradAndUpdate };
+
+// Every tensor in one launch: gradients from the K splits of a batch of B and the Adam step, the
+// gradients alone, or only the BF16 copies.
+int adam_all(dm_mlp* n, AdamStep what, int B, float lr, float b1, float b2, float eps, double bc1, double bc2,
              hipStream_t st) {
     Tensor t[6];
     tensors(n, t);
     dm::AdamBatch batch;
     std::memset(&batch, 0, sizeof batch);
     batch.count = 6;
+    batch.reduce = what != kCopiesOnly;
+    batch.update = what != kGradOnly;
+    const int s2 = k_splits(B, kSplits2), s13 = k_splits(B, kSplits13);
     for (int k = 0; k < 6; ++k) {
         const Tensor& x = t[k];
         dm::AdamArgs& a = batch.t[k];
@@ -173,7 +183,7 @@ int adam_all(dm_mlp* n, bool update, float lr, float b1, float b2, float eps, do
         a.copyT = x.copyT;
         a.rows = x.rows;
         a.cols = x.cols;
-        a.mask_rows = update ? x.mask_rows : 0;
+        a.mask_rows = what == kGradAndUpdate ? x.mask_rows : 0;
         a.mask_cols = x.mask_cols;
         a.lr = lr;
         a.beta1 = b1;
@@ -181,10 +191,19 @@ int adam_all(dm_mlp* n, bool update, float lr, float b1, float b2, float eps, do
         a.eps = eps;
         a.bc1 = (float)bc1;
         a.bc2 = (float)bc2;
-        batch.start[k + 1] = batch.start[k] + (size_t)x.rows * x.cols;
+        if (x.off == oW2) {
+            a.part = n->part;
+            a.splits = s2;
+        } else if (x.off == oW1 || x.off == oW3) {
+            a.part = n->part + (size_t)kSplits2 * 65536 + (x.off == oW3 ? (size_t)kSplits13 * 8192 : 0);
+            a.splits = s13;
+        } else {  // biases: partial sums of their row tiles (b1, b2: 8 each, then b3)
+            const int tile = x.off == oB1 ? 0 : x.off == oB2 ? 8 : 16;
+            a.part = n->part + kPartFloats + (size_t)tile * (dm::mlp_sum_floats() / 17);
+        }
     }
     DM_HIP_TRY(dm::launch_adam_batch(batch, st));
-    n->frag_dirty = true;
+    if (what != kGradOnly) n->frag_dirty = true;
     return DM_OK;
 }
 
@@ -193,138 +212,61 @@ int ensure_batch(dm_mlp* n, int B) {
     const size_t b = (size_t)B;
     int r;
     n->B = 0;
-    if ((r = dev_alloc(n->X, b * 16, "X")) || (r = dev_alloc(n->Xt, 32 * b, "Xt")) ||
-        (r = dev_alloc(n->A1, 2 * b * kH, "A1")) || (r = dev_alloc(n->A1T, 2 * b * kH, "A1T")) ||
-        (r = dev_alloc(n->A2, 2 * b * kH, "A2")) || (r = dev_alloc(n->A2T, 2 * b * kH, "A2T")) ||
-        (r = dev_alloc(n->dO, 2 * b * 32, "dO")) || (r = dev_alloc(n->dOT, 2 * b * 32, "dOT")) ||
-        (r = dev_alloc(n->dH2, 2 * b * kH, "dH2")) || (r = dev_alloc(n->dH2T, 2 * b * kH, "dH2T")) ||
-        (r = dev_alloc(n->dH1T, 2 * b * kH, "dH1T")) || (r = dev_alloc(n->H1, b * kH, "H1")) ||
-        (r = dev_alloc(n->H2, b * kH, "H2")) || (r = dev_alloc(n->loss_hist, (size_t)kLossHist * (b / 32), "loss")))
+    if ((r = dev_alloc(n->Xf, 32 * b, "X")) || (r = dev_alloc(n->A1f, 2 * b * kH, "A1")) ||
+        (r = dev_alloc(n->A2f, 2 * b * kH, "A2")) || (r = dev_alloc(n->dOf, 2 * b * 32, "dO")) ||
+        (r = dev_alloc(n->dH2f, 2 * b * kH, "dH2")) || (r = dev_alloc(n->dH1f, 2 * b * kH, "dH1")) ||
+        (r = dev_alloc(n->loss_hist, (size_t)kLossHist * (b / 32), "loss")) ||
+        (r = dev_alloc(n->part, kPartFloats + dm::mlp_sum_floats(), "split-K partials")))
         return r;
-    n->A1lo = n->A1 + b * kH;
-    n->A1Tlo = n->A1T + b * kH;
-    n->A2lo = n->A2 + b * kH;
-    n->A2Tlo = n->A2T + b * kH;
-    n->dOlo = n->dO + b * 32;
-    n->dOTlo = n->dOT + b * 32;
-    n->dH2lo = n->dH2 + b * kH;
-    n->dH2Tlo = n->dH2T + b * kH;
-    n->dH1Tlo = n->dH1T + b * kH;
-    n->part_floats = std::max<size_t>(16 * 65536, 64 * 8192);
-    if ((r = dev_alloc(n->part, n->part_floats, "split-K partials"))) return r;
     n->B = B;
     return DM_OK;
 }
 
-// Largest power-of-two split of K = B into chunks that are multiples of 16.
-int k_splits(int B, int cap) {
-    int s = cap;
-    while (s > 1 && (B % s != 0 || (B / s) % 16 != 0)) s >>= 1;
-    return s;
-}
-
-dm::GemmArgs gemm(const __bf16* A, int lda, const __bf16* Bt, int ldb, int M, int N, int K, int epi) {
-    dm::GemmArgs g;
-    std::memset(&g, 0, sizeof g);
-    g.A = A;
-    g.lda = lda;
-    g.Bt = Bt;
-    g.ldb = ldb;
-    g.M = M;
-    g.N = N;
-    g.K = K;
-    g.splits = 1;
-    g.epi = epi;
-    return g;
-}
-
-// Weight gradient C[M x N] = A[M x B] . Bt[N x B]^T (each operand with its optional low words),
-// split over B, reduced into grad + off.
-int weight_grad(dm_mlp* n, const __bf16* A, const __bf16* A_lo, const __bf16* Bt, const __bf16* Bt_lo, int M, int N,
-                int B, int cap, size_t off, hipStream_t st) {
-    dm::GemmArgs g = gemm(A, B, Bt, B, M, N, B, dm::kEpiPartial);
-    g.A_lo = A_lo;
-    g.Bt_lo = Bt_lo;
-    g.splits = k_splits(B, cap);
-    g.part = n->part;
-    DM_HIP_TRY(dm::launch_gemm_nt(g, st));
-    DM_HIP_TRY(dm::launch_reduce_splits(n->part, g.splits, (size_t)M * N, n->grad + off, st));
-    return DM_OK;
-}
-
-// Forward + backward of one batch: gradients into n->grad, per-tile loss into loss_tiles.
+// Forward + backward of one batch up to the split weight gradients (adam_all reduces them); per-tile
+// loss into loss_tiles.
 int enqueue_grad(dm_mlp* n, int B, const float* y, const float* sigma2, const float* target, float* loss_tiles,
                  hipStream_t st) {
-    DM_HIP_TRY(dm::launch_features(y, sigma2, B, n->D, n->X, n->Xt, st));
-    // layer 1
-    dm::GemmArgs g = gemm(n->X, 16, n->W1t, 32, B, kH, 16, dm::kEpiFwdHidden);
-    g.bias = n->w + oB1;
-    g.Hout = n->H1;
-    g.ldh = kH;
-    g.Aout = n->A1;
-    g.Aout_lo = n->A1lo;
-    g.ldo = kH;
-    g.AoutT = n->A1T;
-    g.AoutT_lo = n->A1Tlo;
-    g.ldt = B;
-    DM_HIP_TRY(dm::launch_gemm_nt(g, st));
-    // layer 2
-    g = gemm(n->A1, kH, n->W2t, kH, B, kH, kH, dm::kEpiFwdHidden);
-    g.A_lo = n->A1lo;
-    g.bias = n->w + oB2;
-    g.Hout = n->H2;
-    g.ldh = kH;
-    g.Aout = n->A2;
-    g.Aout_lo = n->A2lo;
-    g.ldo = kH;
-    g.AoutT = n->A2T;
-    g.AoutT_lo = n->A2Tlo;
-    g.ldt = B;
-    DM_HIP_TRY(dm::launch_gemm_nt(g, st));
-    // layer 3 + loss + output gradient
-    g = gemm(n->A2, kH, n->W3t, kH, B, 32, kH, dm::kEpiFwdOut);
-    g.A_lo = n->A2lo;
-    g.bias = n->w + oB3;
-    g.target = target;
-    g.ld_target = n->m;
-    g.mout = n->m;
-    g.scale = (float)(1.0 / ((double)B * n->m));
-    g.Aout = n->dO;
-    g.Aout_lo = n->dOlo;
-    g.ldo = 32;
-    g.AoutT = n->dOT;
-    g.AoutT_lo = n->dOTlo;
-    g.ldt = B;
-    g.loss_tiles = loss_tiles;
-    DM_HIP_TRY(dm::launch_gemm_nt(g, st));
-    int r;
-    if ((r = weight_grad(n, n->dOT, n->dOTlo, n->A2T, n->A2Tlo, 32, kH, B, 64, oW3, st))) return r;
-    DM_HIP_TRY(dm::launch_rowsum(n->dOT, n->dOTlo, 32, B, B, n->grad + oB3, st));
-    // back through layer 3 and GELU 2
-    g = gemm(n->dO, 32, n->W3, 32, B, kH, 32, dm::kEpiBwdHidden);
-    g.A_lo = n->dOlo;
-    g.Hin = n->H2;
-    g.ldh = kH;
-    g.Aout = n->dH2;
-    g.Aout_lo = n->dH2lo;
-    g.ldo = kH;
-    g.AoutT = n->dH2T;
-    g.AoutT_lo = n->dH2Tlo;
-    g.ldt = B;
-    DM_HIP_TRY(dm::launch_gemm_nt(g, st));
-    if ((r = weight_grad(n, n->dH2T, n->dH2Tlo, n->A1T, n->A1Tlo, kH, kH, B, 16, oW2, st))) return r;
-    DM_HIP_TRY(dm::launch_rowsum(n->dH2T, n->dH2Tlo, kH, B, B, n->grad + oB2, st));
-    // back through layer 2 and GELU 1
-    g = gemm(n->dH2, kH, n->W2, kH, B, kH, kH, dm::kEpiBwdHidden);
-    g.A_lo = n->dH2lo;
-    g.Hin = n->H1;
-    g.ldh = kH;
-    g.AoutT = n->dH1T;
-    g.AoutT_lo = n->dH1Tlo;
-    g.ldt = B;
-    DM_HIP_TRY(dm::launch_gemm_nt(g, st));
-    if ((r = weight_grad(n, n->dH1T, n->dH1Tlo, n->Xt, nullptr, kH, 32, B, 64, oW1, st))) return r;
-    DM_HIP_TRY(dm::launch_rowsum(n->dH1T, n->dH1Tlo, kH, B, B, n->grad + oB1, st));
+    dm::TrainPassArgs p;
+    std::memset(&p, 0, sizeof p);
+    p.y = y;
+    p.sigma2 = sigma2;
+    p.target = target;
+    p.W1t = n->W1t;
+    p.W2t = n->W2t;
+    p.W2 = n->W2;
+    p.W3t = n->W3t;
+    p.W3 = n->W3;
+    p.b1 = n->w + oB1;
+    p.b2 = n->w + oB2;
+    p.b3 = n->w + oB3;
+    p.Xf = n->Xf;
+    p.A1f = n->A1f;
+    p.A2f = n->A2f;
+    p.dOf = n->dOf;
+    p.dH2f = n->dH2f;
+    p.dH1f = n->dH1f;
+    p.loss_tiles = loss_tiles;
+    p.scale = (float)(1.0 / ((double)B * n->m));
+    p.B = B;
+    p.D = n->D;
+    p.m = n->m;
+    DM_HIP_TRY(dm::launch_train_pass(p, st));
+    dm::WeightGradArgs w;
+    std::memset(&w, 0, sizeof w);
+    w.Xf = n->Xf;
+    w.A1f = n->A1f;
+    w.A2f = n->A2f;
+    w.dOf = n->dOf;
+    w.dH2f = n->dH2f;
+    w.dH1f = n->dH1f;
+    w.part2 = n->part;
+    w.part1 = n->part + (size_t)kSplits2 * 65536;
+    w.part3 = w.part1 + (size_t)kSplits13 * 8192;
+    w.sums = n->part + kPartFloats;
+    w.B = B;
+    w.splits2 = k_splits(B, kSplits2);
+    w.splits13 = k_splits(B, kSplits13);
+    DM_HIP_TRY(dm::launch_weight_grad(w, st));
     return DM_OK;
 }
 
@@ -343,7 +285,7 @@ int upload_weights(dm_mlp* n, const float* ext) {
     DM_HIP_TRY(hipMemset(n->vel, 0, kMasterFloats * sizeof(float)));
     DM_HIP_TRY(hipMemset(n->grad, 0, kMasterFloats * sizeof(float)));
     n->step = 0;
-    int r = adam_all(n, false, 0.0f, 0.9f, 0.999f, 1e-8f, 1.0, 1.0, nullptr);
+    int r = adam_all(n, kCopiesOnly, 256, 0.0f, 0.9f, 0.999f, 1e-8f, 1.0, 1.0, nullptr);
     if (r) return r;
     DM_HIP_TRY(hipDeviceSynchronize());
     return DM_OK;
@@ -351,7 +293,7 @@ int upload_weights(dm_mlp* n, const float* ext) {
 
 int ensure_packed(dm_mlp* n, hipStream_t st) {
     if (!n->frag_dirty) return DM_OK;
-    DM_HIP_TRY(dm::launch_mlp_pack(n->W1t, n->W2t, n->W3t, n->w + oB1, n->frag, st));
+    DM_HIP_TRY(dm::launch_mlp_pack(n->w + oW1, n->w + oW2, n->w + oW3, n->w + oB1, n->frag, st));
     DM_HIP_TRY(hipMemcpyAsync(n->bias_inf, n->w + oB1, kH * sizeof(float), hipMemcpyDeviceToDevice, st));
     DM_HIP_TRY(hipMemcpyAsync(n->bias_inf + kH, n->w + oB2, kH * sizeof(float), hipMemcpyDeviceToDevice, st));
     DM_HIP_TRY(hipMemcpyAsync(n->bias_inf + 2 * kH, n->w + oB3, 32 * sizeof(float), hipMemcpyDeviceToDevice, st));
@@ -373,9 +315,8 @@ int64_t dm_mlp_param_count(int32_t D, int32_t m) {
 void dm_mlp_destroy(dm_mlp* n) {
     if (!n) return;
     for (void* p : {(void*)n->w, (void*)n->mom, (void*)n->vel, (void*)n->grad, (void*)n->W1t, (void*)n->W2t,
-                    (void*)n->W2, (void*)n->W3t, (void*)n->W3, (void*)n->frag, (void*)n->bias_inf, (void*)n->X,
-                    (void*)n->Xt, (void*)n->A1, (void*)n->A1T, (void*)n->A2, (void*)n->A2T, (void*)n->dO,
-                    (void*)n->dOT, (void*)n->dH2, (void*)n->dH2T, (void*)n->dH1T, (void*)n->H1, (void*)n->H2,
+                    (void*)n->W2, (void*)n->W3t, (void*)n->W3, (void*)n->frag, (void*)n->bias_inf, (void*)n->Xf,
+                    (void*)n->A1f, (void*)n->A2f, (void*)n->dOf, (void*)n->dH2f, (void*)n->dH1f,
                     (void*)n->part, (void*)n->loss_hist, (void*)n->targets, (void*)n->acc, (void*)n->bad})
         if (p) (void)hipFree(p);
     if (n->h_stage) (void)hipHostFree(n->h_stage);
@@ -458,6 +399,7 @@ int dm_mlp_gradients(dm_mlp* n, const float* y, const float* sigma2, const float
     hipStream_t st = (hipStream_t)stream;
     if ((r = ensure_batch(n, B))) return r;
     if ((r = enqueue_grad(n, B, y, sigma2, target, n->loss_hist, st))) return r;
+    if ((r = adam_all(n, kGradOnly, B, 0.0f, 0.9f, 0.999f, 1e-8f, 1.0, 1.0, st))) return r;
     std::vector<float> in(kMasterFloats), lt(B / 32);
     DM_HIP_TRY(hipMemcpyAsync(in.data(), n->grad, kMasterFloats * sizeof(float), hipMemcpyDeviceToHost, st));
     DM_HIP_TRY(hipMemcpyAsync(lt.data(), n->loss_hist, lt.size() * sizeof(float), hipMemcpyDeviceToHost, st));
@@ -521,7 +463,7 @@ int dm_mlp_train(dm_mlp* n, const dm_constellation* cc, const dm_train_config* c
                 ++n->step;
                 const double bc1 = 1.0 - std::pow((double)b1, (double)n->step);
                 const double bc2 = 1.0 - std::pow((double)b2, (double)n->step);
-                if ((r = adam_all(n, true, (float)lr, b1, b2, eps, bc1, bc2, st))) return r;
+                if ((r = adam_all(n, kGradAndUpdate, B, (float)lr, b1, b2, eps, bc1, bc2, st))) return r;
             }
         }
     }

@@ -94,7 +94,7 @@ __device__ __forceinline__ void gelu4(const float* v, f16x2& g0, f16x2& g1) {
     g1 = f16x2{r[2], r[3]};
 }
 
-// Fragment table from row-major (out x in) BF16 weights: W1t [256 x 32] (inputs 0..13 used),
+// Fragment table from the BF16 values of row-major (out x in) FP32 weights: W1t [256 x 32] (inputs 0..13 used),
 // W2t [256 x 256], W3t [32 x 256]; the FP32 layer-1 bias b1 becomes input columns 14 (hi) and
 // 15 (lo).  W1 and b1 are stored divided by 4 (W1 stays BF16), W3 multiplied by 4; W2 and 4 W3
 // become FP16 operands, exactly for magnitudes in [2^-14, 65504], to within 2^-25 below that,
@@ -103,7 +103,7 @@ __device__ __forceinline__ _Float16 to_f16_sat(float w) {
     return (_Float16)fminf(fmaxf(w, -65504.0f), 65504.0f);
 }
 
-__global__ void pack_kernel(const __bf16* W1t, const __bf16* W2t, const __bf16* W3t, const float* b1, uint4* frag) {
+__global__ void pack_kernel(const float* W1t, const float* W2t, const float* W3t, const float* b1, uint4* frag) {
     const int f = blockIdx.x * blockDim.x + threadIdx.x;
     if (f >= kFrags) return;
     __bf16 v[8];
@@ -116,20 +116,20 @@ __global__ void pack_kernel(const __bf16* W1t, const __bf16* W2t, const __bf16* 
         const __bf16 lo = (__bf16)(bq - (float)hi);
         for (int q = 0; q < 8; ++q) {
             const int k = 8 * (l / 32) + q;
-            v[q] = k == 14 ? hi : (k == 15 ? lo : (__bf16)(0.25f * (float)W1t[u * 32 + k]));
+            v[q] = k == 14 ? hi : (k == 15 ? lo : (__bf16)(0.25f * (float)(__bf16)W1t[u * 32 + k]));
         }
     } else if (f < kW1Frags + kW2Frags) {
         const int g = f - kW1Frags;
         const int b = g / (16 * 64), t = (g / 64) % 16, l = g % 64;
         const int u = perm_unit(b, l % 32);
-        for (int q = 0; q < 8; ++q) w[q] = to_f16_sat((float)W2t[u * kH + 16 * t + 8 * (l / 32) + q]);
+        for (int q = 0; q < 8; ++q) w[q] = to_f16_sat((float)(__bf16)W2t[u * kH + 16 * t + 8 * (l / 32) + q]);
         frag[f] = *reinterpret_cast<const uint4*>(w);
         return;
     } else {
         const int g = f - kW1Frags - kW2Frags;
         const int t = g / 64, l = g % 64;
         const int o = l % 32;
-        for (int q = 0; q < 8; ++q) w[q] = to_f16_sat(4.0f * (float)W3t[o * kH + 16 * t + 8 * (l / 32) + q]);
+        for (int q = 0; q < 8; ++q) w[q] = to_f16_sat(4.0f * (float)(__bf16)W3t[o * kH + 16 * t + 8 * (l / 32) + q]);
         frag[f] = *reinterpret_cast<const uint4*>(w);
         return;
     }
@@ -361,7 +361,7 @@ __global__ void probe_gelu_kernel(const float* x, float* out, int64_t n) {
 
 size_t mlp_frag_count() { return kFrags; }
 
-hipError_t launch_mlp_pack(const __bf16* W1t, const __bf16* W2t, const __bf16* W3t, const float* b1, uint4* frag,
+hipError_t launch_mlp_pack(const float* W1t, const float* W2t, const float* W3t, const float* b1, uint4* frag,
                            hipStream_t st) {
     hipLaunchKernelGGL(pack_kernel, dim3((kFrags + 255) / 256), dim3(256), 0, st, W1t, W2t, W3t, b1, frag);
     return hipGetLastError();

@@ -5,39 +5,38 @@
 
 namespace dm {
 
-enum : int { kEpiPartial = 0, kEpiFwdHidden = 1, kEpiFwdOut = 2, kEpiBwdHidden = 3 };
+// Forward and backward of a batch; matrices over the batch ("f") are written in MFMA operand
+// order, [32-row tile][16-sample step][hi, lo][64 lanes][8] (Xf: no low words); see
+// mlp_kernels.hip.  A tile of 32 rows takes 64 B elements.
+struct TrainPassArgs {
+    const float* y;        // B x D
+    const float* sigma2;   // B
+    const float* target;   // B x m exact LLRs (nats)
+    // weights in operand order: [256 x 32], [256 x 256] and its transpose, [32 x 256] and its transpose
+    const __bf16 *W1t, *W2t, *W2, *W3t, *W3;
+    const float *b1, *b2, *b3;
+    __bf16 *Xf, *A1f, *A2f, *dOf, *dH2f, *dH1f;  // inputs, activations, deltas
+    float* loss_tiles;     // B / 32 loss sums
+    float scale;           // 1 / (B m)
+    int B, D, m;
+};
 
-struct GemmArgs {
-    const __bf16* A;    // M x K, row stride lda (elements)
-    const __bf16* Bt;   // N x K, row stride ldb
-    // Optional low words of A and Bt (same layouts): an operand carried as a BF16 pair
-    // hi + lo (about 16 significant bits) contributes hi.b + lo.b (+ a.lo for the other side);
-    // the lo.lo product is dropped (relative size 2^-16 of each product).
-    const __bf16* A_lo;
-    const __bf16* Bt_lo;
-    int M, N, K, lda, ldb, splits, epi;
-    float* part;        // PARTIAL: [splits][M][N]
-    const float* bias;  // FWD_*: N
-    float* Hout;        // FWD_HIDDEN: M x N pre-activations (ldh); FWD_OUT: outputs (optional)
-    const float* Hin;   // BWD_HIDDEN: pre-activations (ldh)
-    int ldh;
-    __bf16* Aout;       // row-major output (ldo), may be null for BWD_HIDDEN
-    __bf16* AoutT;      // transposed output (ldt)
-    __bf16* Aout_lo;    // low words of the stored outputs, v - hi rounded to BF16 (may be null)
-    __bf16* AoutT_lo;
-    int ldo, ldt;
-    const float* target;  // FWD_OUT: M x ld_target exact LLRs (nats)
-    int ld_target, mout;
-    float scale;          // FWD_OUT: 1 / (B m)
-    float* loss_tiles;    // FWD_OUT: per-tile loss sums (may be null)
+// Weight and bias gradients of a batch: K-split partials and the bias sums.
+struct WeightGradArgs {
+    const __bf16 *Xf, *A1f, *A2f, *dOf, *dH2f, *dH1f;
+    float *part1, *part2, *part3;  // [splits][rows x cols] of W1t, W2t, W3t
+    float* sums;                   // mlp_sum_floats(): bias partial sums, [dH1 | dH2 | dO 32-row tile][t][row]
+    int B, splits2, splits13;      // splits of dW2 (16), and of dW1 and dW3 (16, 32 or 64)
 };
 
 struct AdamArgs {
     float* w;
     float* m;
     float* v;
-    const float* grad;
-    __bf16* copy;   // may be null
+    float* grad;        // written by the reduction
+    const float* part;  // splits > 0: [splits][rows x cols]; splits == 0 (a bias): its partial sums
+    int splits;
+    __bf16* copy;   // BF16 copies in operand order, may be null
     __bf16* copyT;  // may be null
     int rows, cols, mask_rows, mask_cols;
     float lr, beta1, beta2, eps, bc1, bc2;
@@ -58,26 +57,24 @@ struct MlpInferArgs {
     uint32_t* bad_tx;
 };
 
-hipError_t launch_gemm_nt(const GemmArgs& g, hipStream_t st);
-// Row sums of a BF16 matrix, with its low words Xlo (same layout) added when not null.
-hipError_t launch_rowsum(const __bf16* X, const __bf16* Xlo, int rows, int cols, int ld, float* out, hipStream_t st);
-hipError_t launch_reduce_splits(const float* part, int splits, size_t n, float* grad, hipStream_t st);
-hipError_t launch_adam(const AdamArgs& a, hipStream_t st);
-// Several parameter tensors in one launch: tensor k owns the flat elements [start[k], start[k+1]).
+hipError_t launch_train_pass(const TrainPassArgs& a, hipStream_t st);
+size_t mlp_sum_floats();
+hipError_t launch_weight_grad(const WeightGradArgs& a, hipStream_t st);
+// Several parameter tensors in one launch.
 constexpr int kAdamMaxTensors = 8;
 struct AdamBatch {
     AdamArgs t[kAdamMaxTensors];
-    size_t start[kAdamMaxTensors + 1];
+    int first_block[kAdamMaxTensors];  // set by the launcher
     int count;
+    int reduce, update;  // form the gradients from the splits; take the Adam step and rewrite the copies
 };
-hipError_t launch_adam_batch(const AdamBatch& b, hipStream_t st);
-hipError_t launch_features(const float* y, const float* sigma2, int B, int D, __bf16* X, __bf16* Xt, hipStream_t st);
+hipError_t launch_adam_batch(AdamBatch b, hipStream_t st);
 
 // Number of 16-byte fragments of the inference weight table (H = 256 hidden units).
 size_t mlp_frag_count();
-// Build the inference fragment table from the BF16 row-major (out x in) weights
+// Build the inference fragment table from the BF16 values of the row-major (out x in) FP32 masters
 // W1t [256 x 32] (D + 1 <= 14 inputs), W2t [256 x 256], W3t [32 x 256] and the FP32 bias b1.
-hipError_t launch_mlp_pack(const __bf16* W1t, const __bf16* W2t, const __bf16* W3t, const float* b1, uint4* frag,
+hipError_t launch_mlp_pack(const float* W1t, const float* W2t, const float* W3t, const float* b1, uint4* frag,
                            hipStream_t st);
 hipError_t launch_mlp_infer(const MlpInferArgs& a, int grid, hipStream_t st);
 hipError_t prepare_mlp_infer();
