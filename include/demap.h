@@ -119,8 +119,7 @@ int dm_gmi_estimate(const dm_constellation* c, int n_snr, const double* sigma2,
  * from the first launch until the call has synchronised `stream` (each process has its own
  * copy of the array).
  * dm_last_fixup_count reports no counts after this call (it returns DM_EINVAL).
- * Errors: as dm_gmi_estimate; DM_EUNSUPPORTED also when an operand table is missing (after
- * the points were replaced in place).
+ * Errors: as dm_gmi_estimate.
  */
 int dm_gmi_estimate_noalloc(const dm_constellation* c, int n_snr, const double* sigma2,
                             const float* const* y, const uint16_t* tx, int64_t N,

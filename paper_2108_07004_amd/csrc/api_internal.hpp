@@ -28,6 +28,7 @@ struct dm_constellation {
     float* d_table8 = nullptr;
     void* d_frag8[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
     void* d_pv8[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};
+    bool borrowed = false;                // d_table8 and d_row2label belong to someone else
     float max_norm = 0.0f;                // max ||x||^2 (FP16 operand range check)
     uint64_t hash = 0;                    // identity of (M, D, label-order table)
     std::mutex mu;
@@ -77,8 +78,6 @@ int gmi_run(dm_constellation* c, int n_snr, const double* sigma2, const float* c
 int llr_var_run(dm_constellation* c, const float* sigma2_sym, const float* y, int64_t N, float* llr, int prec,
                 hipStream_t st);
 uint64_t table_hash(int M, int D, const std::vector<float>& table);
-// Replace the coordinates (host, label order, M x D) of c in place; see demap_api.hip.
-int set_label_table(dm_constellation* c, const float* table);
 // Allocate the constellation's accumulators / flags / staging (and a fix-up queue of >= want entries).
 int ensure_scratch(dm_constellation* c, uint64_t want_queue);
 

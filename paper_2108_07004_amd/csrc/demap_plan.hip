@@ -469,7 +469,9 @@ int dm_plan_launch(dm_plan* p, void* stream) {
 int dm_plan_results(dm_plan* p, double* gmi, double* mi, int64_t* fixup_pairs, void* stream) {
     if (!p || !gmi) return fail(DM_EINVAL, "null argument");
     hipStream_t st = (hipStream_t)stream;
-    DM_HIP_TRY(hipMemcpyAsync(p->h_stage, p->d_words, p->n_words * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+    // sums, fix-up pairs and the bad-tx flag (not the queue counters after them)
+    const size_t words = (size_t)p->n_inst * dm::kAccSlots * 2 * 2 + p->n_inst + 1;
+    DM_HIP_TRY(hipMemcpyAsync(p->h_stage, p->d_words, words * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
     DM_HIP_TRY(hipStreamSynchronize(st));
     const auto* acc = reinterpret_cast<const unsigned long long*>(p->h_stage);
     const auto* tail = reinterpret_cast<const uint32_t*>(p->h_stage) + (size_t)p->n_inst * dm::kAccSlots * 2 * 2;

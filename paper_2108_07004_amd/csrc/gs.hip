@@ -6,9 +6,12 @@
 // GMI is higher.  The paper evaluates one modification per iteration; evaluating K at once and
 // keeping the best is the data-parallel form of the same greedy acceptance rule.
 //
-// Device side: K private constellations (label order, identity labelling) whose tables are
-// rewritten in place every iteration, K received blocks regenerated by gs_channel_kernel, and
-// one FP32 batched plan (hipGraph) over the K instances.
+// Device side: one allocation holds the K candidates' point tables (label order, identity
+// labelling, row stride 8), rewritten by one copy from pinned memory per iteration; the K received
+// blocks are regenerated by gs_channel_kernel, and one FP32 batched plan (hipGraph) runs over the K
+// instances.  An iteration waits for the GPU once, for the GMIs.  (With a constellation object
+// per candidate, each rewriting its own tables with synchronous copies, 64 copies took 0.9 of the
+// 1.0 ms of an iteration of 32 candidates.)
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -24,28 +27,35 @@ namespace {
 constexpr int kMaxCand = 64;
 
 struct GsChannelArgs {
-    const float* table[kMaxCand];  // label-order tables, row stride 8
-    float* y[kMaxCand];            // N x D received blocks
-    const uint16_t* tx;            // N transmitted labels
-    const float* z;                // N x D unit-variance noise
-    int64_t N;
+    const float* table;  // K label-order tables, row stride 8, table_stride floats apart
+    float* y;            // K received blocks (N x D), y_stride floats apart
+    const uint16_t* tx;  // N transmitted labels
+    const float* z;      // N x D unit-variance noise
+    int64_t N, table_stride, y_stride;
     int D, M, K;
-    double s;                      // noise standard deviation
+    double s;            // noise standard deviation
 };
 
-// y_k[n][d] = fl32(x_k[tx_n][d] + s z[n][d]), product and sum in FP64.  An out-of-range tx
-// reads row 0 here; the GMI launch that follows reports it as an error.
-__global__ void gs_channel_kernel(const GsChannelArgs a) {
-    const int64_t per = a.N * a.D;
-    const int64_t total = per * a.K;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
-        const int k = (int)(i / per);
-        const int64_t r = i % per;
-        const int64_t n = r / a.D;
-        const int d = (int)(r % a.D);
+// y_k[n][d] = fl32(x_k[tx_n][d] + s z[n][d]), one FP64 multiply-add.  One symbol per thread, all
+// its candidates: tx and z are read once, and the writes of a wave are contiguous.  An
+// out-of-range tx reads row 0 here; the GMI launch that follows reports it as an error.
+__global__ __launch_bounds__(256) void gs_channel_kernel(const GsChannelArgs a) {
+    // grid: x over the symbols, y over groups of candidates
+    const int per = (a.K + gridDim.y - 1) / gridDim.y;
+    const int k0 = blockIdx.y * per, k1 = min(a.K, k0 + per);
+    for (int64_t n = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; n < a.N; n += (int64_t)gridDim.x * blockDim.x) {
         uint32_t row = a.tx[n];
         if (row >= (uint32_t)a.M) row = 0;
-        a.y[k][r] = (float)((double)a.table[k][(size_t)row * 8 + d] + a.s * (double)a.z[r]);
+        double zs[8];
+#pragma unroll
+        for (int d = 0; d < 8; ++d) zs[d] = d < a.D ? (double)a.z[n * a.D + d] : 0.0;
+        for (int k = k0; k < k1; ++k) {
+            const float* x = a.table + k * a.table_stride + (size_t)row * 8;
+            float* o = a.y + k * a.y_stride + n * a.D;
+#pragma unroll
+            for (int d = 0; d < 8; ++d)
+                if (d < a.D) o[d] = (float)__builtin_fma(a.s, zs[d], (double)x[d]);
+        }
     }
 }
 
@@ -75,12 +85,17 @@ void normalise(std::vector<double>& t, int M, int D) {
 
 struct GsState {
     std::vector<dm_constellation*> cons;
-    std::vector<float*> ys;
+    float *tables = nullptr, *ys = nullptr;  // K tables, K received blocks
+    uint16_t* ident = nullptr;
+    float* h_tables = nullptr;               // pinned
     dm_plan* plan = nullptr;
     ~GsState() {
         if (plan) dm_plan_destroy(plan);
         for (auto* c : cons) dm_constellation_destroy(c);
-        for (float* y : ys) (void)hipFree(y);
+        (void)hipFree(tables);
+        (void)hipFree(ys);
+        (void)hipFree(ident);
+        if (h_tables) (void)hipHostFree(h_tables);
     }
 };
 
@@ -119,46 +134,77 @@ int dm_gs_optimize(const float* points, const uint16_t* labels, int32_t M, int32
     for (int l = 0; l < M; ++l)
         for (int d = 0; d < D; ++d) base[(size_t)l * D + d] = points[(size_t)row_of[l] * D + d];
     normalise(base, M, D);
-    std::vector<float> f32((size_t)M * D);
-    auto to_f32 = [&](const std::vector<double>& t) {
-        for (size_t i = 0; i < t.size(); ++i) f32[i] = (float)t[i];
-    };
-    to_f32(base);
     std::vector<uint16_t> ident(M);
     for (int l = 0; l < M; ++l) ident[l] = (uint16_t)l;
 
     GsState g;
+    // tables and received blocks start on 256-byte boundaries
+    const int64_t table_stride = ((int64_t)M * 8 + 63) / 64 * 64, y_stride = (N * D + 63) / 64 * 64;
+    const size_t table_bytes = sizeof(float) * (size_t)table_stride * K;
+    if (hipMalloc(&g.tables, table_bytes) != hipSuccess || hipMalloc(&g.ident, sizeof(uint16_t) * M) != hipSuccess ||
+        hipMalloc(&g.ys, sizeof(float) * (size_t)y_stride * K) != hipSuccess ||
+        hipHostMalloc((void**)&g.h_tables, table_bytes, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        return fail(DM_ENOMEM, "allocation of the candidates' tables and received blocks failed");
+    }
+    std::memset(g.h_tables, 0, table_bytes);
+    // Candidate k's table into the staging buffer.
+    auto stage = [&](int k, const std::vector<double>& t) -> int {
+        float* h = g.h_tables + k * table_stride;
+        for (int l = 0; l < M; ++l)
+            for (int d = 0; d < D; ++d) {
+                const float v = (float)t[(size_t)l * D + d];
+                if (!std::isfinite(v) || std::fabs(v) > 1e15f)
+                    return fail(DM_EINVAL, "point coordinate is not finite or exceeds 1e15");
+                h[(size_t)l * 8 + d] = v;
+            }
+        return DM_OK;
+    };
+    for (int k = 0; k < K; ++k)
+        if ((r = stage(k, base))) return r;
+    DM_HIP_TRY(hipMemcpy(g.ident, ident.data(), sizeof(uint16_t) * M, hipMemcpyHostToDevice));
+    int m = 0, cus = 0;
+    while ((1 << m) < M) ++m;
+    DM_HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     g.cons.assign(K, nullptr);
-    g.ys.assign(K, nullptr);
     std::vector<dm_instance> inst(K);
-    for (int k = 0; k < K; ++k) {
-        if ((r = dm_constellation_create(f32.data(), ident.data(), M, D, &g.cons[k]))) return r;
-        if (hipMalloc(&g.ys[k], sizeof(float) * (size_t)N * D) != hipSuccess) {
-            (void)hipGetLastError();
-            return fail(DM_ENOMEM, "received-block allocation failed");
-        }
-        inst[k] = dm_instance{g.cons[k], sigma2, g.ys[k], tx, N, nullptr};
+    for (int k = 0; k < K; ++k) {  // views of the shared tables: all that an FP32 plan reads
+        auto* c = new (std::nothrow) dm_constellation();
+        if (!c) return fail(DM_ENOMEM, "host allocation failed");
+        g.cons[k] = c;
+        c->M = M;
+        c->D = D;
+        c->m = m;
+        c->DP = dm::padded_dim(D);
+        c->device = dev;
+        c->cus = cus;
+        c->borrowed = true;
+        c->d_table8 = g.tables + k * table_stride;
+        c->d_row2label = g.ident;
+        inst[k] = dm_instance{c, sigma2, g.ys + k * y_stride, tx, N, nullptr};
     }
     if ((r = dm_plan_create(inst.data(), K, DM_PREC_FP32, DM_PLAN_FORCE_VALU, &g.plan))) return r;
 
     GsChannelArgs ca;
     std::memset(&ca, 0, sizeof ca);
-    for (int k = 0; k < K; ++k) {
-        ca.table[k] = g.cons[k]->d_table8;
-        ca.y[k] = g.ys[k];
-    }
+    ca.table = g.tables;
+    ca.y = g.ys;
     ca.tx = tx;
     ca.z = z;
     ca.N = N;
+    ca.table_stride = table_stride;
+    ca.y_stride = y_stride;
     ca.D = D;
     ca.M = M;
     ca.K = K;
     ca.s = std::sqrt(sigma2);
-    const int64_t elems = (int64_t)K * N * D;
-    const int grid = (int)std::min<int64_t>((elems + 255) / 256, 4096);
+    // about 8 blocks per CU: the candidates are split where the symbols alone give fewer
+    const int gx = (int)std::min<int64_t>((N + 255) / 256, (int64_t)cus * 8);
+    const int gy = std::max(1, std::min(K, cus * 8 / gx));
     std::vector<double> gmi(K), mi(K);
     auto evaluate = [&]() -> int {
-        hipLaunchKernelGGL(gs_channel_kernel, dim3(grid), dim3(256), 0, st, ca);
+        DM_HIP_TRY(hipMemcpyAsync(g.tables, g.h_tables, table_bytes, hipMemcpyHostToDevice, st));
+        hipLaunchKernelGGL(gs_channel_kernel, dim3(gx, gy), dim3(256), 0, st, ca);
         DM_HIP_TRY(hipGetLastError());
         int rr = dm_plan_launch(g.plan, stream);
         if (rr) return rr;
@@ -184,8 +230,7 @@ int dm_gs_optimize(const float* points, const uint16_t* labels, int32_t M, int32
                 for (int d = 0; d < D; ++d) cand[k][(size_t)a * D + d] += cfg->perturb_sd * rng.normal();
                 normalise(cand[k], M, D);
             }
-            to_f32(cand[k]);
-            if ((r = dmapi::set_label_table(g.cons[k], f32.data()))) return r;
+            if ((r = stage(k, cand[k]))) return r;
         }
         if ((r = evaluate())) return r;
         int best = 0;
