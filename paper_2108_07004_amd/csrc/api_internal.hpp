@@ -16,12 +16,10 @@ struct dm_constellation {
     uint16_t* d_row2label = nullptr;   // M
     std::vector<float> h_table;        // host copy of the label-order table (M x D)
     // scratch (grow-only), shared by calls on this constellation
-    unsigned long long* d_acc = nullptr;  // kMaxSnrPerLaunch x kAccSlots x 2
-    uint32_t* d_fix_pairs = nullptr;      // kMaxSnrPerLaunch + 1 (last word: bad-tx flag)
-    uint32_t* d_queue_count = nullptr;    // kQueueCounterWords: the queue regions' counters
+    uint32_t* d_words = nullptr;          // dmapi::kScratchWords, see there
     dm::FixEntry* d_queue = nullptr;
     uint32_t queue_cap = 0;
-    void* h_stage = nullptr;              // pinned: acc + fix_pairs
+    uint32_t* h_words = nullptr;          // pinned copy of d_words up to the queue counts
     void* d_frag[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};  // MFMA point tables per precision
     void* d_pv[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};    // same operands per label [M][K]
     // Batched-launch copies with the row stride padded to 8 (D <= 8).
@@ -57,12 +55,23 @@ int ensure_table8(dm_constellation* c);
 struct ChunkScratch {
     unsigned long long* acc;
     uint32_t* fix_pairs;
-    uint32_t* queue_count;
+    uint32_t* queue_count;  // dm::kMaxQueueRegions
     dm::FixEntry* queue;
     uint32_t queue_cap;
 };
+
+// 32-bit words of a constellation's scratch: fix-up pair counts [kMaxSnrPerLaunch], bad-tx flag, (from
+// kExactWord) the exact-decision counts of hard decisions, (from kAccWord) GMI / MI or error-count
+// slots [point][kAccSlots][2] int64, (from kCountWord) the queue counts.  What a launch over n
+// points needs cleared, and what the host reads back, is one range: [0, clear_words(n)).
+constexpr size_t kBadWord = dm::kMaxSnrPerLaunch, kExactWord = 64, kAccWord = 128;
+constexpr size_t kAccWordsPerPoint = (size_t)dm::kAccSlots * 2 * 2;
+constexpr size_t kCountWord = kAccWord + kAccWordsPerPoint * dm::kMaxSnrPerLaunch;
+constexpr size_t kScratchWords = kCountWord + dm::kMaxQueueRegions;
+static_assert(kBadWord < kExactWord && kExactWord + dm::kAccSlots <= kAccWord, "scratch header");
+constexpr size_t clear_words(int n) { return kAccWord + kAccWordsPerPoint * (size_t)n; }
 // Exact path over up to 32 SNR points of one block on the given scratch, which the caller has
-// cleared (acc and fix_pairs when want_acc, the kQueueCounterWords of queue_count always); allocates nothing (an MFMA
+// cleared (acc and fix_pairs when want_acc); allocates nothing (an MFMA
 // precision needs its operand table built).  Caller holds c->mu.
 int run_chunk_on(dm_constellation* c, const ChunkScratch& scr, int n_snr, const double* sigma2,
                  const float* const* y, const uint16_t* tx, int64_t N, float* const* llr, bool want_acc, int prec,

@@ -67,9 +67,6 @@ int hip_fail(hipError_t e, const char* what) {
 }
 
 
-constexpr size_t kStageBytes =
-    sizeof(unsigned long long) * dm::kMaxSnrPerLaunch * dm::kAccSlots * 2 + sizeof(uint32_t) * (dm::kMaxSnrPerLaunch + 1);
-
 // Device pointers must be device (or managed) memory of the current device.
 int check_device_ptr(const void* p, const char* name, int device) {
     if (!p) return fail(DM_EINVAL, "%s is null", name);
@@ -93,11 +90,9 @@ int check_current_device(const dm_constellation* c) {
 }
 
 int ensure_scratch(dm_constellation* c, uint64_t want_queue) {
-    if (!c->d_acc) {
-        DM_HIP_TRY(hipMalloc(&c->d_acc, sizeof(unsigned long long) * dm::kMaxSnrPerLaunch * dm::kAccSlots * 2));
-        DM_HIP_TRY(hipMalloc(&c->d_fix_pairs, sizeof(uint32_t) * (dm::kMaxSnrPerLaunch + 1)));
-        DM_HIP_TRY(hipMalloc(&c->d_queue_count, sizeof(uint32_t) * dm::kQueueCounterWords));
-        DM_HIP_TRY(hipHostMalloc(&c->h_stage, kStageBytes, hipHostMallocDefault));
+    if (!c->d_words) {
+        DM_HIP_TRY(hipMalloc(&c->d_words, sizeof(uint32_t) * kScratchWords));
+        DM_HIP_TRY(hipHostMalloc((void**)&c->h_words, sizeof(uint32_t) * kCountWord, hipHostMallocDefault));
     }
     const uint64_t cap = std::min<uint64_t>(std::max<uint64_t>(want_queue, 1024), 1u << 22);
     if (cap > c->queue_cap) {
@@ -114,7 +109,7 @@ int ensure_scratch(dm_constellation* c, uint64_t want_queue) {
 }
 
 int persistent_grid(const dm_constellation* c, int64_t tiles, int blocks_per_cu) {
-    const int64_t g = (int64_t)c->cus * blocks_per_cu;
+    const int64_t g = std::min<int64_t>((int64_t)c->cus * blocks_per_cu, dm::kMaxQueueRegions);
     return (int)std::max<int64_t>(1, std::min<int64_t>(tiles, g));
 }
 
@@ -259,7 +254,8 @@ int run_chunk_on(dm_constellation* c, const ChunkScratch& scr, int n_snr, const 
         if (!c->d_frag[prec] || !c->d_pv[prec])
             return fail(DM_EUNSUPPORTED, "the operand table of precision %d is not built for this constellation", prec);
     }
-    const int tile = prec == DM_PREC_FP32 ? dm::valu_tile_symbols() : dm::mfma_block_symbols();
+    const bool fp32 = prec == DM_PREC_FP32;
+    const int tile = fp32 ? dm::valu_tile_symbols(N * n_snr, c->cus) : dm::mfma_block_symbols();
     const int64_t tiles_per_snr = (N + tile - 1) / tile;
     LaunchArgs a = base_args(c, N);
     a.tx = tx;
@@ -272,20 +268,24 @@ int run_chunk_on(dm_constellation* c, const ChunkScratch& scr, int n_snr, const 
     a.sinks.bad_tx = want_acc ? scr.fix_pairs + dm::kMaxSnrPerLaunch : nullptr;
     a.sinks.queue = scr.queue;
     a.sinks.queue_count = scr.queue_count;
-    a.sinks.queue_cap = scr.queue_cap;
     for (int s = 0; s < n_snr; ++s) {
         a.snr[s].y = y[s];
         a.snr[s].llr = llr ? llr[s] : nullptr;
         a.snr[s].c = exponent_scale(sigma2[s]);
     }
-    const int grid = persistent_grid(c, tiles_per_snr * n_snr, prec == DM_PREC_FP32 ? 2 : 1);
-    const int fix_grid = c->cus * dm::fixup_blocks_per_cu(c->M);
+    // FP32: two 512-thread blocks per CU, four for the small tables (few registers, short symbols)
+    const int grid = persistent_grid(c, tiles_per_snr * n_snr, !fp32 ? 1 : c->M <= 64 ? 4 : 2);
+    a.sinks.queue_regions = grid;
+    a.sinks.queue_seg = scr.queue_cap / (uint32_t)grid;
+    // no more fix-up blocks than the symbols could fill (64 per wave): an empty pass then costs less
+    const int64_t fix_most = ((int64_t)N * n_snr + dm::kFixBlockSymbols - 1) / dm::kFixBlockSymbols;
+    const int fix_grid = (int)std::min<int64_t>((int64_t)c->cus * dm::fixup_blocks_per_cu(c->M), fix_most);
     ProfRec pr{nullptr, nullptr, nullptr};
     if (g_prof_on && allow_prof) {
         pr = ProfRec{prof_event(), prof_event(), prof_event()};
         if (pr.e0) DM_HIP_TRY(hipEventRecord(pr.e0, st));
     }
-    if (prec == DM_PREC_FP32) DM_HIP_TRY(dm::launch_demap_valu(a, grid, st));
+    if (fp32) DM_HIP_TRY(dm::launch_demap_valu(a, grid, tile, st));
     else DM_HIP_TRY(dm::launch_demap_mfma(a, prec, c->d_frag[prec], c->d_pv[prec], grid, st));
     if (pr.e1) DM_HIP_TRY(hipEventRecord(pr.e1, st));
     DM_HIP_TRY(dm::launch_fixup(a, fix_grid, st));
@@ -301,13 +301,12 @@ int run_chunk(dm_constellation* c, int n_snr, const double* sigma2, const float*
               int64_t N, float* const* llr, bool want_acc, int prec, hipStream_t st, const float* sigma2_sym) {
     int r;
     if (prec != DM_PREC_FP32 && c->D <= 8 && c->M >= 32 && (r = ensure_frag(c, prec, false))) return r;
-    if ((r = ensure_scratch(c, (uint64_t)N * n_snr))) return r;
-    if (want_acc) {
-        DM_HIP_TRY(hipMemsetAsync(c->d_acc, 0, sizeof(unsigned long long) * n_snr * dm::kAccSlots * 2, st));
-        DM_HIP_TRY(hipMemsetAsync(c->d_fix_pairs, 0, sizeof(uint32_t) * (dm::kMaxSnrPerLaunch + 1), st));
-    }
-    DM_HIP_TRY(hipMemsetAsync(c->d_queue_count, 0, sizeof(uint32_t) * dm::kQueueCounterWords, st));
-    const ChunkScratch scr{c->d_acc, c->d_fix_pairs, c->d_queue_count, c->d_queue, c->queue_cap};
+    // one entry per symbol, and what rounding the symbols up to whole tiles per workgroup can add
+    const uint64_t symbols = (uint64_t)N * n_snr;
+    if ((r = ensure_scratch(c, symbols + std::min<uint64_t>(symbols, 1u << 19)))) return r;
+    if (want_acc) DM_HIP_TRY(dm::launch_zero_words(c->d_words, clear_words(n_snr), st));
+    const ChunkScratch scr{reinterpret_cast<unsigned long long*>(c->d_words + kAccWord), c->d_words,
+                           c->d_words + kCountWord, c->d_queue, c->queue_cap};
     return run_chunk_on(c, scr, n_snr, sigma2, y, tx, N, llr, want_acc, prec, st, sigma2_sym, true);
 }
 
@@ -421,11 +420,9 @@ void dm_constellation_destroy(dm_constellation* c) {
         (void)hipFree(c->d_row2label);
         (void)hipFree(c->d_table8);
     }
-    (void)hipFree(c->d_acc);
-    (void)hipFree(c->d_fix_pairs);
-    (void)hipFree(c->d_queue_count);
+    (void)hipFree(c->d_words);
     (void)hipFree(c->d_queue);
-    if (c->h_stage) (void)hipHostFree(c->h_stage);
+    if (c->h_words) (void)hipHostFree(c->h_words);
     for (void* f : c->d_frag) (void)hipFree(f);
     for (void* f : c->d_pv) (void)hipFree(f);
     for (void* f : c->d_frag8) (void)hipFree(f);
@@ -494,12 +491,11 @@ int gmi_run(dm_constellation* c, int n_snr, const double* sigma2, const float* c
         const int ns = std::min(dm::kMaxSnrPerLaunch, n_snr - s0);
         r = run_chunk(c, ns, sigma2 + s0, y + s0, tx, N, llr ? llr + s0 : nullptr, true, prec, st, nullptr);
         if (r) return r;
-        auto* acc = (unsigned long long*)c->h_stage;
-        auto* fix = (uint32_t*)(acc + (size_t)dm::kMaxSnrPerLaunch * dm::kAccSlots * 2);
-        DM_HIP_TRY(hipMemcpyAsync(acc, c->d_acc, sizeof(unsigned long long) * ns * dm::kAccSlots * 2, hipMemcpyDeviceToHost, st));
-        DM_HIP_TRY(hipMemcpyAsync(fix, c->d_fix_pairs, sizeof(uint32_t) * (dm::kMaxSnrPerLaunch + 1), hipMemcpyDeviceToHost, st));
+        const uint32_t* fix = c->h_words;
+        const auto* acc = reinterpret_cast<const unsigned long long*>(c->h_words + kAccWord);
+        DM_HIP_TRY(hipMemcpyAsync(c->h_words, c->d_words, sizeof(uint32_t) * clear_words(ns), hipMemcpyDeviceToHost, st));
         DM_HIP_TRY(hipStreamSynchronize(st));
-        if (fix[dm::kMaxSnrPerLaunch]) return fail(DM_EINVAL, "a transmitted index is >= M");
+        if (fix[kBadWord]) return fail(DM_EINVAL, "a transmitted index is >= M");
         for (int s = 0; s < ns; ++s) {
             long long gs = 0, ms = 0;  // two's-complement sums of the fixed-point slots
             for (int k = 0; k < dm::kAccSlots; ++k) {

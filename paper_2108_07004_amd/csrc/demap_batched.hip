@@ -1,23 +1,22 @@
-// Batched exact demapping: one persistent launch over many (constellation, noise level, block)
-// instances of uneven M, D and N (gfx950).
+// Batched exact demapping on MFMA: persistent launches over many (constellation, noise level, block)
+// instances of uneven M, D and N (gfx950); the FP32 instances' launch is in demap_batched_valu.hip.
 //
 // Work items are (instance, sub consecutive symbol tiles) pairs listed instance by instance,
-// the most costly instance first (sub per instance, from the plan's shape choice).  Workgroups claim fixed chunks of `grab` consecutive items from a counter
+// the most costly instance first (sub per instance, from the plan's shape choice), one list per
+// kernel.  Workgroups claim fixed chunks of `grab` consecutive items from a counter
 // (dynamic balance: the cheap items at the end fill the tail) and restage their LDS table only
 // when the next item belongs to another instance.  GMI / MI partial sums are flushed per chunk
 // and instance, so every fixed-point contribution covers a fixed set of symbols whichever
-// workgroup runs it: the totals are bit-reproducible.  Each instance runs either
-// the FP32 direct-difference body (one lane per symbol, 1024-symbol tiles) or the MFMA body
-// (one wave per 32 symbols, 512-symbol tiles; 32..256-point constellations take the
-// compile-time tile loop of mfma_small.hpp), as chosen per (M, D) by the autotuner.  Batched
-// tables use a row stride of 8 (D <= 8 zero-padded): the padded coordinates contribute exact
-// zeros, and the MFMA operand vectors of every instance have the same K layout.
+// workgroup runs it: the totals are bit-reproducible.  One wave takes 32 symbols, a block 512 per
+// tile.  The instances of 32 .. 256 points (the compile-time tile loop of mfma_small.hpp) and those of
+// more points have a kernel each: in one kernel with the FP32 body their registers spilled (46 of 128
+// per lane).  Batched tables use a row stride of 8 (D <= 8 zero-padded): the padded coordinates
+// contribute exact zeros, and the MFMA operand vectors of every instance have the same K layout.
 #include "device_common.hpp"
 #include "fixup_drain.hpp"
 #include "kernels.hpp"
 #include "mfma_body.hpp"
 #include "mfma_small.hpp"
-#include "valu_body.hpp"
 
 namespace dm {
 
@@ -29,16 +28,16 @@ constexpr int kWaves = kThreads / 64;
 // One 32-symbol batch of an instance with 32 * NT points (D padded to 8): compile-time tile loop
 // and epilogue.
 template <typename T, bool SPLIT, int NT>
-__device__ __forceinline__ void small_item(const uint4* lds, const BlockView& b, const Sinks& k, const uint16_t* pv,
+__device__ __forceinline__ void small_item(const uint4* lds, const BlockView& b, const Sinks& k, uint32_t* fill, const uint16_t* pv,
                                            const Frags<T, Slots<8, SPLIT>::S>& bfr, int64_t n, bool active, bool bad,
                                            int txl, int lane, float& g, float& mi) {
     constexpr int MB = SmallBits<NT>::MB;
     float S0[MB], S1[MB], tot;
     mfma_small_sums<T, 8, SPLIT, NT>(lds, lane, bfr, S0, S1, tot);
-    mfma_finish<T, 8, SPLIT, MB>(b, k, pv, bfr, S0, S1, tot, n, active, bad, txl, lane, g, mi);
+    mfma_finish<T, 8, SPLIT, MB>(b, k, fill, pv, bfr, S0, S1, tot, n, active, bad, txl, lane, g, mi);
 }
 
-template <typename T, bool SPLIT>
+template <typename T, bool SPLIT, bool SMALL>
 __global__ __launch_bounds__(kThreads) void demap_batched_kernel(const BatchArgs a) {
     extern __shared__ uint4 lds_raw[];
     constexpr int S = Slots<8, SPLIT>::S;
@@ -48,80 +47,85 @@ __global__ __launch_bounds__(kThreads) void demap_batched_kernel(const BatchArgs
     const int wave = tid >> 6;
     const int wave_slot = (blockIdx.x * kWaves + wave) % kAccSlots;  // integer slots: any spread sums alike
     const Sinks& k = a.sinks;
-    __shared__ int s_claim;
+    __shared__ int s_claim[2];   // this claim and the next, which is requested a claim ahead
+    __shared__ uint32_t s_fill;  // entries in this block's fix-up queue region
+    if (tid == 0) {
+        s_fill = 0u;
+        s_claim[0] = (int)atomicAdd(a.next, (uint32_t)a.grab);
+    }
+    __syncthreads();
     int staged = -1;
-    for (;;) {
-        if (tid == 0) s_claim = (int)atomicAdd(a.next, (uint32_t)a.grab);
-        __syncthreads();
-        const int i0 = s_claim;
-        __syncthreads();  // every thread has read the claim before it is overwritten
+    for (int at = 0;; at ^= 1) {
+        const int i0 = __builtin_amdgcn_readfirstlane(s_claim[at]);
         if (i0 >= a.n_items) break;
         const int i1 = min(i0 + a.grab, a.n_items);
-        int cur = -1;
-        double gsum = 0.0, msum = 0.0;
-        for (int i = i0; i < i1; ++i) {
-            const WorkItem it = a.items[i];
-            const int inst = it.inst;
-            const BatchDesc& d = a.desc[inst];
-            const BlockView b = d.view;
-            const int kind = d.kind;
-            if (inst != staged) {  // restage the point table (whole block, uniform condition)
+        int next = 0;
+        if (tid == 0) next = (int)atomicAdd(a.next, (uint32_t)a.grab);
+        for (int i = i0; i < i1;) {
+            // a run of items of one instance: its symbol tiles one after the other, GMI / MI terms
+            // summed per lane, then over the wave once
+            const WorkItem it = uniform_copy(a.items[i]);
+            const BatchDesc d = uniform_desc(a.desc[it.inst]);
+            const BlockView& b = d.view;
+            i += it.run;
+            if (it.inst != staged) {  // restage the point table (whole block, uniform condition)
                 __syncthreads();
-                if (kind == kKindMfma) {
-                    const int n16 = (b.M >> 5) * S * 64;
-                    for (int j = tid; j < n16; j += kThreads) lds_raw[j] = d.frag[j];
-                } else {
-                    float* lds = reinterpret_cast<float*>(lds_raw);
-                    const int Mpad = b.M < 16 ? 16 : b.M;
-                    for (int j = tid; j < Mpad * 8; j += kThreads)
-                        lds[j] = (j < b.M * 8) ? b.table[j] : 1.0e19f;  // padding rows: e_j = 0
-                }
+                const int n16 = (b.M >> 5) * S * 64;
+                for (int j = tid; j < n16; j += kThreads) lds_raw[j] = d.frag[j];
                 __syncthreads();
-                staged = inst;
+                staged = it.inst;
             }
-            if (inst != cur) {
-                if (cur >= 0 && k.acc && lane == 0) {
-                    acc_add(k.acc, cur, wave_slot, 0, gsum);
-                    acc_add(k.acc, cur, wave_slot, 1, msum);
-                }
-                gsum = msum = 0.0;
-                cur = inst;
-            }
-            // The item's sub symbol tiles; GMI / MI terms summed per lane, then over the wave once.
+            const int tiles = it.run * d.sub;
+            const int sub = wave * 32 + (lane & 31);
+            // (the small tables' kernel has the registers to load a tile's symbols a tile ahead)
+            float y_nx[8];
+            uint32_t row_nx = 0;
+            auto fetch = [&](int t) {
+                const int64_t n = it.n0 + (int64_t)t * (kWaves * 32) + sub;
+                const size_t nc = (size_t)(n < b.N ? n : 0);
+                const float* src = b.y + nc * b.D;
+#pragma unroll
+                for (int q = 0; q < 8; ++q) y_nx[q] = src[min(q, b.D - 1)];
+                if (b.tx) row_nx = b.tx[nc];
+            };
+            if constexpr (SMALL) fetch(0);
             double gl = 0.0, ml = 0.0;
-            for (int sb = 0; sb < d.sub; ++sb) {
+            for (int t = 0; t < tiles; ++t) {
                 float g = 0.0f, mi = 0.0f;
-                bool active;
-                if (kind == kKindMfma) {
-                    const int64_t n = it.n0 + (int64_t)sb * (kWaves * 32) + wave * 32 + (lane & 31);
-                    active = n < b.N;
-                    float y[8];
-                    load_symbol<8>(y, b.y + (size_t)(active ? n : 0) * b.D, b.D, active);
-                    bool bad = false;
-                    const Frags<T, S> bfr = build_symbol_frags<T, 8, SPLIT>(y, b.c, b.K, h, bad);
-                    const int txl = (b.tx && active) ? tx_label(b, k, n) : 0;
-                    switch (b.M) {  // uniform: 32..256 points take the compile-time tile loop
-                        case 32: small_item<T, SPLIT, 1>(lds_raw, b, k, d.pv, bfr, n, active, bad, txl, lane, g, mi); break;
-                        case 64: small_item<T, SPLIT, 2>(lds_raw, b, k, d.pv, bfr, n, active, bad, txl, lane, g, mi); break;
-                        case 128: small_item<T, SPLIT, 4>(lds_raw, b, k, d.pv, bfr, n, active, bad, txl, lane, g, mi); break;
-                        case 256: small_item<T, SPLIT, 8>(lds_raw, b, k, d.pv, bfr, n, active, bad, txl, lane, g, mi); break;
-                        default: {
-                            MfmaAcc A;
-                            A.init();
-                            mfma_tiles<T, 8, SPLIT>(lds_raw, lane, 0, b.M >> 5, b.m, bfr, A);
-                            mfma_epilogue<T, 8, SPLIT>(b, k, d.pv, bfr, A, n, active, bad, txl, lane, g, mi);
+                const int64_t n = it.n0 + (int64_t)t * (kWaves * 32) + sub;
+                const bool active = n < b.N;
+                float y[8];
+                int txl = 0;
+                if constexpr (SMALL) {
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) y[q] = active && q < b.D ? y_nx[q] : 0.0f;
+                    uint32_t row = row_nx;
+                    if (t + 1 < tiles) fetch(t + 1);
+                    if (b.tx && active) {
+                        if (row >= (uint32_t)b.M) {  // out-of-range row: clamped and reported
+                            if (k.bad_tx) atomicOr(k.bad_tx, 1u);
+                            row = 0;
                         }
+                        txl = (int)b.row2label[row];
                     }
                 } else {
-                    const int64_t n = it.n0 + (int64_t)sb * kThreads + tid;
-                    active = n < b.N;
-                    float y[8];
                     load_symbol<8>(y, b.y + (size_t)(active ? n : 0) * b.D, b.D, active);
-                    DM_VALU_ACC_DECL
-                    const int Mpad = b.M < 16 ? 16 : b.M;
-                    valu_accumulate<8>(reinterpret_cast<const float*>(lds_raw), 0, Mpad, y, b.c, b.K, b.m, accA, accB,
-                                       hi0, hi1);
-                    valu_epilogue<8>(b, k, n, active, y, accA, accB, hi0, hi1, g, mi);
+                    txl = (b.tx && active) ? tx_label(b, k, n) : 0;
+                }
+                bool bad = false;
+                const Frags<T, S> bfr = build_symbol_frags<T, 8, SPLIT>(y, b.c, b.K, h, bad);
+                if constexpr (SMALL) {
+                    switch (b.M) {  // uniform
+                        case 32: small_item<T, SPLIT, 1>(lds_raw, b, k, &s_fill, d.pv, bfr, n, active, bad, txl, lane, g, mi); break;
+                        case 64: small_item<T, SPLIT, 2>(lds_raw, b, k, &s_fill, d.pv, bfr, n, active, bad, txl, lane, g, mi); break;
+                        case 128: small_item<T, SPLIT, 4>(lds_raw, b, k, &s_fill, d.pv, bfr, n, active, bad, txl, lane, g, mi); break;
+                        default: small_item<T, SPLIT, 8>(lds_raw, b, k, &s_fill, d.pv, bfr, n, active, bad, txl, lane, g, mi); break;
+                    }
+                } else {
+                    MfmaAcc A;
+                    A.init();
+                    mfma_tiles<T, 8, SPLIT>(lds_raw, lane, 0, b.M >> 5, b.m, bfr, A);
+                    mfma_epilogue<T, 8, SPLIT>(b, k, &s_fill, d.pv, bfr, A, n, active, bad, txl, lane, g, mi);
                 }
                 if (active) {
                     gl += (double)g;
@@ -129,19 +133,22 @@ __global__ __launch_bounds__(kThreads) void demap_batched_kernel(const BatchArgs
                 }
             }
             if (k.acc) {
-                gsum += wave_sum(gl);
-                msum += wave_sum(ml);
+                gl = wave_sum(gl);
+                ml = wave_sum(ml);
+                if (lane == 0) {
+                    acc_add(k.acc, it.inst, wave_slot, 0, gl);
+                    acc_add(k.acc, it.inst, wave_slot, 1, ml);
+                }
             }
         }
-        if (cur >= 0 && k.acc && lane == 0) {
-            acc_add(k.acc, cur, wave_slot, 0, gsum);
-            acc_add(k.acc, cur, wave_slot, 1, msum);
-        }
+        if (tid == 0) s_claim[at ^ 1] = next;
+        __syncthreads();
     }
+    queue_close(k, &s_fill);
 }
 
 // Exact recomputation of the queued symbols of every instance (one lane or one wavefront per symbol).
-__global__ __launch_bounds__(256) void batched_fixup_kernel(const BatchArgs a) {
+__global__ __launch_bounds__(kFixThreads) void batched_fixup_kernel(const BatchArgs a) {
     __shared__ float s_t[4][kFixCached];  // per-wave exponent cache (32 KiB per block)
     drain_fix_queue<8>(a.sinks, [&](const FixEntry& e) { return a.desc[e.tag].view; }, s_t[threadIdx.x >> 6],
                        kFixCached);
@@ -153,36 +160,54 @@ __global__ void zero_words(uint32_t* p, size_t n) {
         p[i] = 0u;
 }
 
-template <typename T, bool SPLIT>
-hipError_t prepare_t() {
-    return hipFuncSetAttribute((const void*)demap_batched_kernel<T, SPLIT>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                               kBatchedLdsAlloc);
+// Dynamic LDS: the largest table of the kernel's instances, plus the one fragment tile that the
+// pipeline of the larger tables reads past a 16-tile block.
+template <bool SPLIT, bool SMALL>
+constexpr int batched_lds() {
+    return SMALL ? 8 * Slots<8, SPLIT>::S * 1024 : kBatchedLdsAlloc;
 }
 
 template <typename T, bool SPLIT>
-hipError_t launch_batched_t(const BatchArgs& a, int grid, hipStream_t st) {
-    hipLaunchKernelGGL((demap_batched_kernel<T, SPLIT>), dim3(grid), dim3(kThreads), kBatchedLdsAlloc, st, a);
+hipError_t prepare_t() {
+    hipError_t e = hipFuncSetAttribute((const void*)demap_batched_kernel<T, SPLIT, false>,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, batched_lds<SPLIT, false>());
+    if (e != hipSuccess) return e;
+    return hipFuncSetAttribute((const void*)demap_batched_kernel<T, SPLIT, true>,
+                               hipFuncAttributeMaxDynamicSharedMemorySize, batched_lds<SPLIT, true>());
+}
+
+template <typename T, bool SPLIT>
+hipError_t launch_batched_t(const BatchArgs& a, bool small, int grid, hipStream_t st) {
+    if (small)
+        hipLaunchKernelGGL((demap_batched_kernel<T, SPLIT, true>), dim3(grid), dim3(kThreads), (batched_lds<SPLIT, true>()),
+                           st, a);
+    else
+        hipLaunchKernelGGL((demap_batched_kernel<T, SPLIT, false>), dim3(grid), dim3(kThreads),
+                           (batched_lds<SPLIT, false>()), st, a);
     return hipGetLastError();
 }
 
 }  // namespace
 
-int batched_tile_symbols(int kind) { return kind == kKindMfma ? kWaves * 32 : kThreads; }
+int batched_tile_symbols(int kind) { return kind == kKindMfma ? kWaves * 32 : 1024; }
 
-hipError_t launch_demap_batched(const BatchArgs& a, int prec, int grid, hipStream_t st) {
+hipError_t launch_demap_batched(const BatchArgs& a, int which, int prec, int grid, hipStream_t st) {
+    if (which == kBatchValu) return launch_demap_batched_valu(a, grid, st);
+    const bool small = which == kBatchSmall;
     switch (prec) {
-        case 0:  // FP32: every instance runs the VALU body; the MFMA operand type is unused
-        case 4: return launch_batched_t<_Float16, true>(a, grid, st);
-        case 1: return launch_batched_t<__bf16, false>(a, grid, st);
-        case 2: return launch_batched_t<_Float16, false>(a, grid, st);
-        case 3: return launch_batched_t<__bf16, true>(a, grid, st);
+        case 4: return launch_batched_t<_Float16, true>(a, small, grid, st);
+        case 1: return launch_batched_t<__bf16, false>(a, small, grid, st);
+        case 2: return launch_batched_t<_Float16, false>(a, small, grid, st);
+        case 3: return launch_batched_t<__bf16, true>(a, small, grid, st);
         default: return hipErrorInvalidValue;
     }
 }
 
 hipError_t prepare_batched(int prec) {
+    const hipError_t e = prepare_batched_valu();
+    if (e != hipSuccess) return e;
     switch (prec) {
-        case 0:
+        case 0: return hipSuccess;  // every instance runs the FP32 body
         case 4: return prepare_t<_Float16, true>();
         case 1: return prepare_t<__bf16, false>();
         case 2: return prepare_t<_Float16, false>();
@@ -192,12 +217,13 @@ hipError_t prepare_batched(int prec) {
 }
 
 hipError_t launch_batched_fixup(const BatchArgs& a, int grid, hipStream_t st) {
-    hipLaunchKernelGGL(batched_fixup_kernel, dim3(grid), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(batched_fixup_kernel, dim3(grid), dim3(kFixThreads), 0, st, a);
     return hipGetLastError();
 }
 
 hipError_t launch_zero_words(uint32_t* p, size_t n, hipStream_t st) {
-    hipLaunchKernelGGL(zero_words, dim3(64), dim3(256), 0, st, p, n);
+    const int blocks = (int)std::max<size_t>(1, std::min<size_t>(64, (n + 255) / 256));
+    hipLaunchKernelGGL(zero_words, dim3(blocks), dim3(256), 0, st, p, n);
     return hipGetLastError();
 }
 

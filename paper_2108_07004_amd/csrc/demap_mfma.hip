@@ -16,6 +16,9 @@ __global__ __launch_bounds__(kMfmaThreads) void demap_mfma_kernel(const LaunchAr
                                                                   const uint16_t* __restrict__ pv) {
     constexpr int S = Slots<D, SPLIT>::S;
     extern __shared__ uint4 lds_frag[];  // [tile][s][64 lanes] x 16 bytes
+    __shared__ uint32_t s_fill;          // entries in this block's fix-up queue region
+    if (threadIdx.x == 0) s_fill = 0u;
+    __syncthreads();
     const int ntiles = a.M >> 5;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -92,7 +95,7 @@ __global__ __launch_bounds__(kMfmaThreads) void demap_mfma_kernel(const LaunchAr
             mfma_tiles<T, D, SPLIT>(lds_frag, lane, t0, cnt, b.m, bfr, A);
         } while (++ch < nchunks);
         float g, mi;
-        mfma_epilogue<T, D, SPLIT>(b, k, pv, bfr, A, n, active, bad, txl, lane, g, mi);
+        mfma_epilogue<T, D, SPLIT>(b, k, &s_fill, pv, bfr, A, n, active, bad, txl, lane, g, mi);
         if (k.acc && active) {
             gsum += (double)g;
             msum += (double)mi;
@@ -104,6 +107,7 @@ __global__ __launch_bounds__(kMfmaThreads) void demap_mfma_kernel(const LaunchAr
         }
     }
     if (cur >= 0 && k.acc) flush();
+    queue_close(k, &s_fill);
 }
 
 template <typename T, int D, bool SPLIT>

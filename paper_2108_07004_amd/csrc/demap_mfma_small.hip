@@ -33,7 +33,9 @@ __global__ __launch_bounds__(kThreads) void demap_mfma_small_kernel(const Launch
     constexpr bool kDirectTx = SPLIT && std::is_same<T, _Float16>::value;
     __shared__ uint4 lds_pv[kDirectTx ? 1 : NT * 32 * 2 * S];  // [label][16 S halves]
     __shared__ uint16_t lds_r2l[NT * 32];       // row -> label
+    __shared__ uint32_t s_fill;                 // entries in this block's fix-up queue region
     const int tid = threadIdx.x;
+    if (tid == 0) s_fill = 0u;
     const int lane = tid & 63;
     const int h = lane >> 5;
     const int wave = tid >> 6;
@@ -116,14 +118,14 @@ __global__ __launch_bounds__(kThreads) void demap_mfma_small_kernel(const Launch
         const float ttx = fmaf(-b.c, sqdist<D>(y, lds_tab + txl * D), b.K);
         float g, mi;
         uint32_t mask, near;
-        mfma_finish<T, D, SPLIT, MB>(b, k, reinterpret_cast<const uint16_t*>(lds_pv), bfr, S0, S1, tot, n, active, bad,
+        mfma_finish<T, D, SPLIT, MB>(b, k, &s_fill, reinterpret_cast<const uint16_t*>(lds_pv), bfr, S0, S1, tot, n, active, bad,
                                      txl, lane, g, mi, &mask, &near, kDirectTx ? &ttx : nullptr);
         // far subsets of flagged bits resolved in the wave (at high SNR nearly every batch has
         // some; each would otherwise be a queue entry and a recomputation from the queue)
         mfma_small_far_pass<T, D, SPLIT, NT>(lds_frag, lane, y, b.c, b.K, bad, b, n, active, txl, near, mask, g);
         if (mask && active && h == 0) {
             double gc = 0.0, mc = 0.0;
-            queue_or_fix<D>(b, k, (uint32_t)n, mask, near, gc, mc);
+            queue_or_fix<D, D>(b, k, &s_fill, (uint32_t)n, mask, near, gc, mc);
             g += (float)gc;
             mi += (float)mc;
         }
@@ -133,6 +135,7 @@ __global__ __launch_bounds__(kThreads) void demap_mfma_small_kernel(const Launch
         }
     }
     if (cur >= 0 && k.acc) flush();
+    queue_close(k, &s_fill);
 }
 
 template <typename T, int D, bool SPLIT>

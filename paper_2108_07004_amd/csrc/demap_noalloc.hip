@@ -31,8 +31,8 @@ constexpr size_t kAccBytes = sizeof(unsigned long long) * dm::kMaxSnrPerLaunch *
 constexpr size_t kSumOff = kAccBytes;                                   // [n_snr][2] int64 totals
 constexpr size_t kFixOff = kSumOff + sizeof(long long) * dm::kMaxSnrPerLaunch * 2;
 constexpr size_t kCountOff = kFixOff + 256;                             // kMaxSnrPerLaunch + 1 words fit
-constexpr size_t kQueueOff = kCountOff + sizeof(uint32_t) * dm::kQueueCounterWords;  // region counters
-constexpr size_t kClearBytes = kQueueOff;                               // zeroed by every call
+constexpr size_t kQueueOff = kCountOff + sizeof(uint32_t) * dm::kMaxQueueRegions;  // region counts
+constexpr size_t kClearBytes = kCountOff;                               // zeroed by every call
 constexpr size_t kScratchBytes = kQueueOff + sizeof(dm::FixEntry) * kQueueEntries;
 static_assert(sizeof(uint32_t) * (dm::kMaxSnrPerLaunch + 1) <= 256, "fix-pair words overflow their slot");
 static_assert(kClearBytes % 4 == 0 && kQueueOff % 256 == 0, "scratch layout");

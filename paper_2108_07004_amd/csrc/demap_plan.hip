@@ -111,12 +111,13 @@ struct dm_plan {
     std::vector<double> ns_per_pair;
     dm::BatchDesc* d_desc = nullptr;
     dm::WorkItem* d_items = nullptr;
-    uint32_t* d_words = nullptr;  // acc (2 words per int64) | fix_pairs[n] | bad_tx | next | queue counters
+    uint32_t* d_words = nullptr;  // acc (2 words per int64) | fix_pairs[n] | bad_tx | next | queue counts
     size_t n_words = 0;
     dm::FixEntry* d_queue = nullptr;
     uint32_t queue_cap = 0;
     void* h_stage = nullptr;
-    dm::BatchArgs args{};
+    dm::BatchArgs args[dm::kBatchKernels] = {};  // per kernel: its work list, claim counter, queue regions
+    int grids[dm::kBatchKernels] = {};           // its workgroups (0: no work)
     hipStream_t cap_stream = nullptr;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -160,9 +161,10 @@ int build_descs(dm_plan* p, std::vector<dm::BatchDesc>& desc) {
     return DM_OK;
 }
 
-// Work list: instances in decreasing order of estimated cost (ns per pair x M x N), each as
-// consecutive symbol tiles.  Workgroups claim it in chunks at run time.
-void build_work(const dm_plan* p, std::vector<dm::WorkItem>& items) {
+// Work lists, one per kernel, one after the other in `items` (kernel q's from first[q] to first[q + 1]):
+// instances in decreasing order of estimated cost (ns per pair x M x N), each as consecutive
+// symbol tiles.  Workgroups claim a list in chunks at run time.
+void build_work(const dm_plan* p, std::vector<dm::WorkItem>& items, int (&first)[dm::kBatchKernels + 1]) {
     std::vector<int> order(p->n_inst);
     std::vector<double> cost(p->n_inst);
     for (int i = 0; i < p->n_inst; ++i) {
@@ -170,48 +172,74 @@ void build_work(const dm_plan* p, std::vector<dm::WorkItem>& items) {
         cost[i] = p->ns_per_pair[i] * p->inst[i].c->M * (double)p->inst[i].N;
     }
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return cost[a] > cost[b]; });
-    for (int i : order) {
-        const int64_t tile = (int64_t)dm::batched_tile_symbols(p->kind[i]) * p->sub[i];
-        for (int64_t n0 = 0; n0 < p->inst[i].N; n0 += tile) items.push_back(dm::WorkItem{i, 0, n0});
+    for (int q = 0; q < dm::kBatchKernels; ++q) {
+        first[q] = (int)items.size();
+        for (int i : order) {
+            if (dm::batch_kernel(p->kind[i], p->inst[i].c->M) != q) continue;
+            const int64_t tile = (int64_t)dm::batched_tile_symbols(p->kind[i]) * p->sub[i];
+            for (int64_t n0 = 0; n0 < p->inst[i].N; n0 += tile) items.push_back(dm::WorkItem{i, 1, n0});
+        }
+        for (int t = (int)items.size() - 2; t >= first[q]; --t)
+            if (items[t].inst == items[t + 1].inst && (t + 1 - first[q]) % p->grab) items[t].run = items[t + 1].run + 1;
     }
+    first[dm::kBatchKernels] = (int)items.size();
 }
 
-int alloc_plan_buffers(dm_plan* p, const std::vector<dm::BatchDesc>& desc, const std::vector<dm::WorkItem>& items) {
+int alloc_plan_buffers(dm_plan* p, const std::vector<dm::BatchDesc>& desc, const std::vector<dm::WorkItem>& items,
+                       const int (&first)[dm::kBatchKernels + 1], int cus) {
     DM_HIP_TRY(hipMalloc(&p->d_desc, desc.size() * sizeof(dm::BatchDesc)));
     DM_HIP_TRY(hipMalloc(&p->d_items, std::max<size_t>(1, items.size()) * sizeof(dm::WorkItem)));
     DM_HIP_TRY(hipMemcpy(p->d_desc, desc.data(), desc.size() * sizeof(dm::BatchDesc), hipMemcpyHostToDevice));
     if (!items.empty())
         DM_HIP_TRY(hipMemcpy(p->d_items, items.data(), items.size() * sizeof(dm::WorkItem), hipMemcpyHostToDevice));
-    // the queue's region counters start on a kQueueStride-word boundary after the other words
-    const size_t q_off = (((size_t)p->n_inst * dm::kAccSlots * 2 * 2 + p->n_inst + 2 + dm::kQueueStride - 1) /
-                          dm::kQueueStride) * dm::kQueueStride;
-    p->n_words = q_off + dm::kQueueCounterWords;
-    DM_HIP_TRY(hipMalloc(&p->d_words, p->n_words * sizeof(uint32_t)));
+    p->n_words = (size_t)p->n_inst * dm::kAccSlots * 2 * 2 + p->n_inst + 1 + dm::kBatchKernels;  // cleared by every launch
+    DM_HIP_TRY(hipMalloc(&p->d_words, (p->n_words + dm::kMaxQueueRegions) * sizeof(uint32_t)));
     int64_t total_n = 0;
     for (const auto& in : p->inst) total_n += in.N;
-    p->queue_cap = (uint32_t)std::min<int64_t>(std::max<int64_t>(total_n, 1024), 1 << 22);
+    p->queue_cap = (uint32_t)std::min<int64_t>(std::max<int64_t>(2 * total_n, 1 << 16), 1 << 22);
     DM_HIP_TRY(hipMalloc(&p->d_queue, (size_t)p->queue_cap * sizeof(dm::FixEntry)));
     DM_HIP_TRY(hipHostMalloc(&p->h_stage, p->n_words * sizeof(uint32_t), hipHostMallocDefault));
     auto* acc = reinterpret_cast<unsigned long long*>(p->d_words);
     uint32_t* tail = p->d_words + (size_t)p->n_inst * dm::kAccSlots * 2 * 2;
-    p->args.desc = p->d_desc;
-    p->args.items = p->d_items;
-    p->args.n_items = (int32_t)items.size();
-    p->args.grab = p->grab;
-    p->args.next = tail + p->n_inst + 1;
-    p->args.sinks.acc = acc;
-    p->args.sinks.fix_pairs = tail;
-    p->args.sinks.bad_tx = tail + p->n_inst;
-    p->args.sinks.queue_count = p->d_words + q_off;
-    p->args.sinks.queue = p->d_queue;
-    p->args.sinks.queue_cap = p->queue_cap;
+    // one block of 1024 threads per CU, no more than a kernel's list has claims
+    size_t valu_lds = 0;
+    for (int i = 0; i < p->n_inst; ++i)
+        if (p->kind[i] == dm::kKindValu && p->inst[i].N > 0)
+            valu_lds = std::max(valu_lds, (size_t)std::max(16, p->inst[i].c->M) * 8 * sizeof(float));
+    int regions = 0;
+    for (int q = 0; q < dm::kBatchKernels; ++q) {
+        const int n = first[q + 1] - first[q];
+        p->grids[q] = std::min((n + p->grab - 1) / p->grab, std::min(cus, dm::kMaxQueueRegions / dm::kBatchKernels));
+        p->grid = std::max(p->grid, p->grids[q]);
+        regions += p->grids[q];
+    }
+    int at = 0;
+    for (int q = 0; q < dm::kBatchKernels; ++q) {
+        dm::BatchArgs& a = p->args[q];
+        a.desc = p->d_desc;
+        a.items = p->d_items + first[q];
+        a.n_items = (int32_t)(first[q + 1] - first[q]);
+        a.grab = p->grab;
+        a.next = tail + p->n_inst + 1 + q;
+        a.lds_bytes = (int32_t)valu_lds;
+        a.sinks.acc = acc;
+        a.sinks.fix_pairs = tail;
+        a.sinks.bad_tx = tail + p->n_inst;
+        a.sinks.queue_count = p->d_words + p->n_words;
+        a.sinks.queue = p->d_queue;
+        a.sinks.queue_regions = regions;
+        a.sinks.queue_first = at;
+        a.sinks.queue_seg = p->queue_cap / (uint32_t)std::max(1, regions);
+        at += p->grids[q];
+    }
     return DM_OK;
 }
 
 int enqueue(dm_plan* p, hipStream_t st) {
     DM_HIP_TRY(dm::launch_zero_words(p->d_words, p->n_words, st));
-    DM_HIP_TRY(dm::launch_demap_batched(p->args, p->prec, p->grid, st));
-    DM_HIP_TRY(dm::launch_batched_fixup(p->args, p->fix_grid, st));
+    for (int q = dm::kBatchKernels - 1; q >= 0; --q)
+        if (p->grids[q] > 0) DM_HIP_TRY(dm::launch_demap_batched(p->args[q], q, p->prec, p->grids[q], st));
+    DM_HIP_TRY(dm::launch_batched_fixup(p->args[0], p->fix_grid, st));
     return DM_OK;
 }
 
@@ -231,8 +259,7 @@ void free_plan(dm_plan* p) {
 // Plan skeleton without graph: validated instances, kinds, item sizes, per-pair costs and
 // claim size set by the caller.
 int make_plan(const dm_instance* inst, int n_inst, int prec, const std::vector<int>& kinds,
-              const std::vector<int>& subs, const std::vector<double>& cost, int grab, int grid_cap,
-              dm_plan** out) {
+              const std::vector<int>& subs, const std::vector<double>& cost, int grab, dm_plan** out) {
     auto* p = new (std::nothrow) dm_plan();
     if (!p) return fail(DM_ENOMEM, "host allocation failed");
     p->n_inst = n_inst;
@@ -256,15 +283,15 @@ int make_plan(const dm_instance* inst, int n_inst, int prec, const std::vector<i
         free_plan(p);
         return r;
     }
-    p->grid = std::max(1, grid_cap > 0 ? std::min(grid_cap, cus) : cus);
     e = dm::prepare_batched(prec);  // LDS attribute set outside any graph capture
     if (e != hipSuccess) {
         free_plan(p);
         return hip_fail(e, "hipFuncSetAttribute(batched kernel)");
     }
     p->fix_grid = cus * 4;
-    build_work(p, items);
-    r = alloc_plan_buffers(p, desc, items);
+    int first[dm::kBatchKernels + 1];
+    build_work(p, items, first);
+    r = alloc_plan_buffers(p, desc, items, first, cus);
     if (r) {
         free_plan(p);
         return r;
@@ -338,7 +365,7 @@ int time_candidate(const dm_instance& in, int prec, int kind, int sub, int cus, 
     std::vector<dm_instance> insts(copies, probe);
     dm_plan* p = nullptr;
     int r = make_plan(insts.data(), copies, prec, std::vector<int>(copies, kind), std::vector<int>(copies, sub),
-                      std::vector<double>(copies, 1.0), kGrabDefault, 0, &p);
+                      std::vector<double>(copies, 1.0), kGrabDefault, &p);
     if (r) return r;
     float ms = 0.0f;
     r = time_plan(p, &ms);
@@ -427,7 +454,7 @@ int dm_plan_create(const dm_instance* inst, int n_inst, int prec, int flags, dm_
         float best_ms = 0.0f;
         for (int g : kGrabs) {
             dm_plan* tp = nullptr;
-            if ((r = make_plan(quiet.data(), n_inst, prec, kinds, subs, cost, g, 0, &tp))) return r;
+            if ((r = make_plan(quiet.data(), n_inst, prec, kinds, subs, cost, g, &tp))) return r;
             float ms = 0.0f;
             r = time_plan(tp, &ms);
             free_plan(tp);
@@ -439,7 +466,7 @@ int dm_plan_create(const dm_instance* inst, int n_inst, int prec, int flags, dm_
         }
     }
     dm_plan* p = nullptr;
-    r = make_plan(inst, n_inst, prec, kinds, subs, cost, grab, 0, &p);
+    r = make_plan(inst, n_inst, prec, kinds, subs, cost, grab, &p);
     if (r) return r;
     // Capture zero-fill + batched kernel + fix-up into a graph on a private stream.
     hipError_t e = hipStreamCreateWithFlags(&p->cap_stream, hipStreamNonBlocking);
@@ -469,7 +496,7 @@ int dm_plan_launch(dm_plan* p, void* stream) {
 int dm_plan_results(dm_plan* p, double* gmi, double* mi, int64_t* fixup_pairs, void* stream) {
     if (!p || !gmi) return fail(DM_EINVAL, "null argument");
     hipStream_t st = (hipStream_t)stream;
-    // sums, fix-up pairs and the bad-tx flag (not the queue counters after them)
+    // sums, fix-up pairs and the bad-tx flag
     const size_t words = (size_t)p->n_inst * dm::kAccSlots * 2 * 2 + p->n_inst + 1;
     DM_HIP_TRY(hipMemcpyAsync(p->h_stage, p->d_words, words * sizeof(uint32_t), hipMemcpyDeviceToHost, st));
     DM_HIP_TRY(hipStreamSynchronize(st));
@@ -503,8 +530,11 @@ int dm_plan_info(const dm_plan* p, int* kinds, double* ns_per_pair, int32_t* ite
 
 int dm_plan_stats(const dm_plan* p, int64_t* n_items, int32_t* claim_items, int32_t* grid) {
     if (!p) return fail(DM_EINVAL, "null plan");
-    if (n_items) *n_items = p->args.n_items;
-    if (claim_items) *claim_items = p->args.grab;
+    if (n_items) {
+        *n_items = 0;
+        for (const dm::BatchArgs& a : p->args) *n_items += a.n_items;
+    }
+    if (claim_items) *claim_items = p->grab;
     if (grid) *grid = p->grid;
     return DM_OK;
 }

@@ -17,14 +17,12 @@ __device__ __forceinline__ uint32_t flag_bits(int p, float s0, float s1) {
     return (1u << p) | ((p < kFarBits && s1 < s0) ? 1u << (kFarShift + p) : 0u);
 }
 
-// The fix-up queue is split into kQueueRegions equal regions, each with its own counter
-// (kQueueStride words apart): a wave appends to the region its global wave index hashes to.
-// Device-scope atomics on one address serialise at ~11 ns each on MI355X (measured), and at high
-// SNR nearly every 32-symbol batch queues symbols, so a single counter made the queue, not the
-// arithmetic, the bound of those launches; 64 counters spread the same atomics ~35x thinner.
-constexpr int kQueueRegions = 64;
-constexpr int kQueueStride = 64;                                   // words between two counters
-constexpr int kQueueCounterWords = kQueueRegions * kQueueStride;  // counter array, zeroed per launch
+// The fix-up queue is split into one region per workgroup of the demapping launch (at most
+// kMaxQueueRegions).  A workgroup counts its entries in LDS and stores the count when it ends, so
+// the queue needs no device-scope atomics (they serialise at ~11 ns per address on MI355X, and at
+// high SNR nearly every 32-symbol batch queues symbols) and no clearing before a launch.   A call
+// then clears its sums with one small kernel, where four memsets took 10 us of a small call's 62.
+constexpr int kMaxQueueRegions = 1024;
 constexpr int kFixCached = 2048;  // the wave fix-up caches a symbol's exponents in LDS up to this M
 
 // One symbol whose far-subset sums underflowed the shared exponent window.
@@ -69,9 +67,11 @@ struct Sinks {
     unsigned long long* acc;     // [tags][kAccSlots][2] int64 fixed-point GMI / MI sums, or null
     uint32_t* fix_pairs;         // [tags] count of (symbol, bit) pairs sent to the fix-up, or null
     uint32_t* bad_tx;            // set to 1 when a transmitted index is >= M (clamped, reported)
-    FixEntry* queue;             // queue_cap entries: kQueueRegions regions of queue_cap / kQueueRegions
-    uint32_t* queue_count;       // kQueueCounterWords: region r's counter at word r * kQueueStride
-    uint32_t queue_cap;
+    FixEntry* queue;             // queue_regions regions of queue_seg entries, one per workgroup
+    uint32_t* queue_count;       // [queue_regions] entries of each region, stored by its workgroup
+    uint32_t queue_seg;
+    int32_t queue_regions;       // workgroups of the demapping launches that share the queue
+    int32_t queue_first;         // region of this launch's workgroup 0
 };
 
 struct SnrArg {
@@ -92,8 +92,8 @@ struct HardArgs {
     int M, D, n_blk;
     unsigned long long* counts;  // [n_blk][kAccSlots][2]: symbol errors, bit errors; null = no counting
     uint32_t* bad_tx;
-    uint32_t* exact;             // MFMA method, or null: kQueueRegions counters, kQueueStride words apart, of
-                                 // the symbols that the matrix ranking alone does not decide
+    uint32_t* exact;             // MFMA method, or null: [kAccSlots] counts of the symbols that the matrix
+                                 // ranking alone does not decide
 };
 
 // Multi-SNR launch over one constellation and one transmitted block.
@@ -114,6 +114,10 @@ struct LaunchArgs {
 // ---- batched launch over many instances ----
 constexpr int kKindValu = 0;  // FP32 direct-difference body
 constexpr int kKindMfma = 1;  // MFMA cross-term body
+// Kernels of a batched launch, each with its own work list: FP32 items, MFMA items of 32 .. 256 points
+// and MFMA items of more points.
+enum : int { kBatchValu = 0, kBatchSmall = 1, kBatchLarge = 2, kBatchKernels = 3 };
+inline int batch_kernel(int kind, int M) { return kind == kKindValu ? kBatchValu : M <= 256 ? kBatchSmall : kBatchLarge; }
 constexpr int kBatchedLdsBytes = 131072;  // largest staged table (FP32 rows or MFMA fragments)
 // Dynamic LDS of the batched kernel: the table plus the one 2 KiB fragment tile (split
 // operands) that the MFMA pipeline reads past a 16-tile block.
@@ -129,7 +133,7 @@ struct BatchDesc {             // one instance (device memory); view.tag = insta
 
 struct WorkItem {              // symbols [n0, n0 + tile) of one instance
     int32_t inst;
-    int32_t pad;
+    int32_t run;               // items from this one on that are the same instance's and the same claim's
     int64_t n0;
 };
 
@@ -139,8 +143,44 @@ struct BatchArgs {
     int32_t n_items;
     int32_t grab;              // items per claim; claims start at multiples of grab
     uint32_t* next;            // claim counter (zeroed before every launch)
+    int32_t lds_bytes;         // FP32 kernel: its largest table
     Sinks sinks;
 };
+
+// Wave-uniform copy of a struct in memory: its words in scalar registers.  Loads that the compiler
+// cannot prove unclobbered go through vector registers, and a BlockView held there took 25 of the
+// batched kernels' 128.
+template <typename V>
+__device__ __forceinline__ V uniform_copy(const V& src) {
+    static_assert(sizeof(V) % 4 == 0, "whole words");
+    uint32_t w[sizeof(V) / 4];
+    __builtin_memcpy(w, &src, sizeof(V));
+#pragma unroll
+    for (size_t i = 0; i < sizeof(V) / 4; ++i) w[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)w[i]);
+    V v;
+    __builtin_memcpy(&v, w, sizeof(V));
+    return v;
+}
+
+// A pointer read from memory is generic to the compiler; this says that it is global (plain global
+// loads and stores instead of flat ones, which also wait for the LDS).
+template <typename T>
+__device__ __forceinline__ T* as_global(T* p) {
+    return (T*)(__attribute__((address_space(1))) T*)p;
+}
+
+// Wave-uniform copy of an instance's descriptor.
+__device__ __forceinline__ BatchDesc uniform_desc(const BatchDesc& src) {
+    BatchDesc d = uniform_copy(src);
+    d.view.table = as_global(d.view.table);
+    d.view.row2label = as_global(d.view.row2label);
+    d.view.tx = as_global(d.view.tx);
+    d.view.y = as_global(d.view.y);
+    d.view.llr = as_global(d.view.llr);
+    d.frag = as_global(d.frag);
+    d.pv = as_global(d.pv);
+    return d;
+}
 
 __device__ __forceinline__ BlockView view_snr(const LaunchArgs& a, int s) {
     BlockView v;
@@ -252,18 +292,18 @@ __device__ __forceinline__ void load_symbol(float (&y)[DP], const float* src, in
 }
 
 // Exact log-sum-exp (log2 units, t_j = K - c d_j^2) of the subsets of label bit p,
-// with each subset shifted by its own maximum.  Returns L = log2 S^1 - log2 S^0.
-template <int DP>
+// with each subset shifted by its own maximum (table rows LS apart).  Returns L = log2 S^1 - log2 S^0.
+template <int DP, int LS>
 __device__ float exact_bit_llr2(const float (&y)[DP], const float* table, int M, int p, float c, float K) {
     float mx0 = -INFINITY, mx1 = -INFINITY;
     for (int j = 0; j < M; ++j) {
-        const float t = fmaf(-c, sqdist<DP>(y, table + (size_t)j * DP), K);
+        const float t = fmaf(-c, sqdist<DP>(y, table + (size_t)j * LS), K);
         if ((j >> p) & 1) mx1 = fmaxf(mx1, t);
         else mx0 = fmaxf(mx0, t);
     }
     float s0 = 0.0f, s1 = 0.0f;
     for (int j = 0; j < M; ++j) {
-        const float t = fmaf(-c, sqdist<DP>(y, table + (size_t)j * DP), K);
+        const float t = fmaf(-c, sqdist<DP>(y, table + (size_t)j * LS), K);
         if ((j >> p) & 1) s1 += hw_exp2(t - mx1);
         else s0 += hw_exp2(t - mx0);
     }
@@ -271,18 +311,18 @@ __device__ float exact_bit_llr2(const float (&y)[DP], const float* table, int M,
 }
 
 // MI term m - log2 sum_j 2^(t_j - t_tx), exact max shift.
-template <int DP>
+template <int DP, int LS>
 __device__ float exact_mi_term(const float (&y)[DP], const float* table, int M, int m, int txl, float c, float K) {
     float mx = -INFINITY;
-    for (int j = 0; j < M; ++j) mx = fmaxf(mx, fmaf(-c, sqdist<DP>(y, table + (size_t)j * DP), K));
+    for (int j = 0; j < M; ++j) mx = fmaxf(mx, fmaf(-c, sqdist<DP>(y, table + (size_t)j * LS), K));
     float s = 0.0f;
-    for (int j = 0; j < M; ++j) s += hw_exp2(fmaf(-c, sqdist<DP>(y, table + (size_t)j * DP), K) - mx);
-    const float ttx = fmaf(-c, sqdist<DP>(y, table + (size_t)txl * DP), K);
+    for (int j = 0; j < M; ++j) s += hw_exp2(fmaf(-c, sqdist<DP>(y, table + (size_t)j * LS), K) - mx);
+    const float ttx = fmaf(-c, sqdist<DP>(y, table + (size_t)txl * LS), K);
     return (float)m - ((mx - ttx) + hw_log2(s));
 }
 
 // Recompute the flagged bits of one symbol in one lane; returns the GMI / MI corrections.
-template <int DP>
+template <int DP, int LS>
 __device__ void fixup_one(const BlockView& b, const Sinks& k, uint32_t n, uint32_t mask, double& gcorr,
                           double& mcorr) {
     float y[DP];
@@ -290,36 +330,34 @@ __device__ void fixup_one(const BlockView& b, const Sinks& k, uint32_t n, uint32
     const int txl = b.tx ? tx_label(b, k, n) : 0;
     for (int p = 0; p < b.m; ++p) {
         if (!((mask >> p) & 1u)) continue;
-        const float L = exact_bit_llr2<DP>(y, b.table, b.M, p, b.c, b.K);
+        const float L = exact_bit_llr2<DP, LS>(y, b.table, b.M, p, b.c, b.K);
         if (b.llr) b.llr[(size_t)n * b.m + (b.m - 1 - p)] = L * 0.69314718055994531f;
         if (b.tx) gcorr += (double)gmi_bit_term(L, (txl >> p) & 1);
     }
-    if ((mask & kMiFlag) && b.tx) mcorr += (double)exact_mi_term<DP>(y, b.table, b.M, b.m, txl, b.c, b.K);
+    if ((mask & kMiFlag) && b.tx) mcorr += (double)exact_mi_term<DP, LS>(y, b.table, b.M, b.m, txl, b.c, b.K);
 }
 
-// Queue region of the calling wave (wave-uniform, so the compiler folds the lanes' counter
-// increments into one atomic per wave).
-__device__ __forceinline__ uint32_t queue_region() {
-    const uint32_t w = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    return (uint32_t)__builtin_amdgcn_readfirstlane((int)(w % kQueueRegions));
-}
-
-// Queue a symbol for the fix-up (near: FixEntry.near of the symbol) in the wave's region; when
-// that region is full the calling lane recomputes the symbol in place (slow but exact), counts
-// its pairs, and the corrections come back through gc / mc.  Queued pairs are counted by the
-// fix-up when it drains them.
-template <int DP>
-__device__ __forceinline__ void queue_or_fix(const BlockView& b, const Sinks& k, uint32_t n, uint32_t mask,
-                                             uint32_t near, double& gc, double& mc) {
-    const uint32_t seg = k.queue_cap / kQueueRegions;
-    const uint32_t r = queue_region();
-    const uint32_t slot = atomicAdd(k.queue_count + r * kQueueStride, 1u);
-    if (slot < seg) {
-        k.queue[(size_t)r * seg + slot] = FixEntry{n, (uint32_t)b.tag, mask, near};
+// Queue a symbol for the fix-up (near: FixEntry.near of the symbol) in the workgroup's region, whose
+// fill is counted in LDS at *fill; when the region is full the calling lane recomputes the
+// symbol in place (slow but exact), counts its pairs, and the corrections come back through
+// gc / mc.  Queued pairs are counted by the fix-up when it drains them.  LS: row stride of the block's
+// table.
+template <int DP, int LS>
+__device__ __forceinline__ void queue_or_fix(const BlockView& b, const Sinks& k, uint32_t* fill, uint32_t n,
+                                             uint32_t mask, uint32_t near, double& gc, double& mc) {
+    const uint32_t slot = atomicAdd(fill, 1u);
+    if (slot < k.queue_seg) {
+        k.queue[(size_t)(k.queue_first + blockIdx.x) * k.queue_seg + slot] = FixEntry{n, (uint32_t)b.tag, mask, near};
     } else {
         if (k.fix_pairs) atomicAdd(k.fix_pairs + b.tag, (uint32_t)__popc(mask & 0xFFFFu));
-        fixup_one<DP>(b, k, n, mask, gc, mc);
+        fixup_one<DP, LS>(b, k, n, mask, gc, mc);
     }
+}
+
+// Store the workgroup's region count; every thread calls it once, after its last queue_or_fix.
+__device__ __forceinline__ void queue_close(const Sinks& k, const uint32_t* fill) {
+    __syncthreads();
+    if (threadIdx.x == 0) k.queue_count[k.queue_first + blockIdx.x] = min(*fill, k.queue_seg);
 }
 
 }  // namespace dm

@@ -322,31 +322,48 @@ __device__ void fix_rows(const Sinks& k, ViewFn view, AddFn add, FetchFn fetch, 
     }
 }
 
-// Exclusive prefix of the queue regions' fill into s_qpre[0 .. kQueueRegions]: wave 0 of the
-// block computes it; the caller synchronises the block before reading it.
+// Exclusive prefix of the queue regions' fill into s_qpre[0 .. kMaxQueueRegions] (regions past the
+// last are empty); the block's kFixThreads threads compute it, the caller synchronises before
+// reading it.
+constexpr int kFixThreads = 256;
+
 __device__ __forceinline__ void queue_prefix(const Sinks& k, uint32_t* s_qpre) {
-    static_assert(kQueueRegions == 64, "one wave scans the region counts");
-    if (threadIdx.x < 64) {  // wave 0, fully active
-        const int r = threadIdx.x;
-        uint32_t x = min(k.queue_count[r * kQueueStride], k.queue_cap / kQueueRegions);
+    constexpr int kPer = kMaxQueueRegions / kFixThreads;
+    __shared__ uint32_t s_wave[kFixThreads / 64];
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    uint32_t own[kPer], x = 0u;
 #pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const uint32_t y = __shfl_up(x, off, 64);
-            if (r >= off) x += y;
-        }
-        s_qpre[r + 1] = x;
-        if (r == 0) s_qpre[0] = 0u;
+    for (int q = 0; q < kPer; ++q) {
+        const int r = tid * kPer + q;
+        own[q] = r < k.queue_regions ? k.queue_count[r] : 0u;
+        x += own[q];
     }
+    const uint32_t mine = x;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t y = __shfl_up(x, off, 64);
+        if (lane >= off) x += y;
+    }
+    if (lane == 63) s_wave[wv] = x;
+    __syncthreads();
+    uint32_t at = x - mine;
+    for (int w = 0; w < wv; ++w) at += s_wave[w];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        s_qpre[tid * kPer + q] = at;
+        at += own[q];
+    }
+    if (tid == kFixThreads - 1) s_qpre[kMaxQueueRegions] = at;
 }
 
-// Position in k.queue of entry i < s_qpre[kQueueRegions] of the filled regions read as one list:
+// Position in k.queue of entry i < s_qpre[kMaxQueueRegions] of the filled regions read as one list:
 // the largest region r with s_qpre[r] <= i holds it at offset i - s_qpre[r].
 __device__ __forceinline__ size_t queue_index(const Sinks& k, const uint32_t* s_qpre, uint32_t i) {
     uint32_t r = 0;
 #pragma unroll
-    for (uint32_t step = kQueueRegions / 2; step >= 1; step >>= 1)
+    for (uint32_t step = kMaxQueueRegions / 2; step >= 1; step >>= 1)
         if (s_qpre[r + step] <= i) r += step;
-    return (size_t)r * (k.queue_cap / kQueueRegions) + (i - s_qpre[r]);
+    return (size_t)r * k.queue_seg + (i - s_qpre[r]);
 }
 
 // Drain the fix-up queue: symbols of constellations with at most kFixLaneMaxM points are
@@ -367,7 +384,7 @@ __device__ void drain_fix_queue(const Sinks& k, ViewFn view, float* tl, int cach
     constexpr int kFixLdsTags = 64;
     __shared__ unsigned long long s_acc[kFixLdsTags * 2];
     __shared__ uint32_t s_pairs[kFixLdsTags];
-    __shared__ uint32_t s_qpre[kQueueRegions + 1];  // exclusive prefix of the regions' fill
+    __shared__ uint32_t s_qpre[kMaxQueueRegions + 1];  // exclusive prefix of the regions' fill
     for (int i = threadIdx.x; i < kFixLdsTags * 2; i += blockDim.x) s_acc[i] = 0ull;
     for (int i = threadIdx.x; i < kFixLdsTags; i += blockDim.x) s_pairs[i] = 0u;
     queue_prefix(k, s_qpre);
@@ -389,7 +406,7 @@ __device__ void drain_fix_queue(const Sinks& k, ViewFn view, float* tl, int cach
             acc_add(k.acc, tag, slot, which, v);
         }
     };
-    uint32_t count = s_qpre[kQueueRegions];
+    uint32_t count = s_qpre[kMaxQueueRegions];
     const int lane = threadIdx.x & 63;
     const uint32_t wave = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
     const uint32_t nwaves = gridDim.x * (blockDim.x >> 6);
@@ -406,7 +423,7 @@ __device__ void drain_fix_queue(const Sinks& k, ViewFn view, float* tl, int cach
             const BlockView b = view(e);
             if (b.M <= kFixLaneMaxM) {
                 double gc = 0.0, mc = 0.0;
-                fixup_one<DP>(b, k, e.n, e.mask, gc, mc);
+                fixup_one<DP, DP>(b, k, e.n, e.mask, gc, mc);
                 add((int)e.tag, lane, 0, gc);
                 add((int)e.tag, lane, 1, mc);
             }

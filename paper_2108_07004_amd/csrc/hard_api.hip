@@ -6,7 +6,6 @@
 #include <cstring>
 #include <limits>
 #include <mutex>
-#include <vector>
 
 #include "api_internal.hpp"
 #include "kernels.hpp"
@@ -67,36 +66,26 @@ int dm_hard_decision(const dm_constellation* cc, int n_blk, const float* const* 
         a.M = c->M;
         a.D = c->D;
         a.n_blk = nb;
-        a.counts = counting ? c->d_acc : nullptr;
-        a.bad_tx = counting ? c->d_fix_pairs + dm::kMaxSnrPerLaunch : nullptr;
-        if (counting) {
-            DM_HIP_TRY(hipMemsetAsync(c->d_acc, 0, sizeof(unsigned long long) * 2 * dm::kAccSlots * nb, st));
-            DM_HIP_TRY(hipMemsetAsync(a.bad_tx, 0, sizeof(uint32_t), st));
-        }
+        a.counts = counting ? reinterpret_cast<unsigned long long*>(c->d_words + dmapi::kAccWord) : nullptr;
+        a.bad_tx = counting ? c->d_words + dmapi::kBadWord : nullptr;
+        a.exact = use_mfma && n_exact ? c->d_words + dmapi::kExactWord : nullptr;
+        const bool read = counting || a.exact;
+        if (read) DM_HIP_TRY(dm::launch_zero_words(c->d_words, dmapi::clear_words(nb), st));
         if (use_mfma) {
-            a.exact = n_exact ? c->d_queue_count : nullptr;
-            if (n_exact)
-                DM_HIP_TRY(hipMemsetAsync(c->d_queue_count, 0, sizeof(uint32_t) * dm::kQueueCounterWords, st));
             DM_HIP_TRY(dm::launch_hard_mfma(a, c->d_frag[DM_PREC_FP16X3], std::sqrt(c->max_norm), c->cus, st));
         } else {
             const int grid = (int)std::max<int64_t>(1, std::min<int64_t>(a.tiles_per_blk * nb, (int64_t)c->cus * 2));
             DM_HIP_TRY(dm::launch_hard_demap(a, grid, st));
         }
-        if (use_mfma && n_exact) {
-            std::vector<uint32_t> q(dm::kQueueCounterWords);
-            DM_HIP_TRY(hipMemcpyAsync(q.data(), c->d_queue_count, sizeof(uint32_t) * dm::kQueueCounterWords,
-                                      hipMemcpyDeviceToHost, st));
-            DM_HIP_TRY(hipStreamSynchronize(st));
-            for (int k = 0; k < dm::kQueueRegions; ++k) exact_total += q[(size_t)k * dm::kQueueStride];
-        }
+        if (!read) continue;
+        DM_HIP_TRY(hipMemcpyAsync(c->h_words, c->d_words, sizeof(uint32_t) * dmapi::clear_words(nb),
+                                  hipMemcpyDeviceToHost, st));
+        DM_HIP_TRY(hipStreamSynchronize(st));
+        if (a.exact)
+            for (int k = 0; k < dm::kAccSlots; ++k) exact_total += c->h_words[dmapi::kExactWord + k];
         if (counting) {
-            auto* h = (unsigned long long*)c->h_stage;
-            auto* bad = (uint32_t*)(h + 2 * dm::kAccSlots * dm::kMaxSnrPerLaunch);
-            DM_HIP_TRY(hipMemcpyAsync(h, c->d_acc, sizeof(unsigned long long) * 2 * dm::kAccSlots * nb,
-                                      hipMemcpyDeviceToHost, st));
-            DM_HIP_TRY(hipMemcpyAsync(bad, a.bad_tx, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
-            DM_HIP_TRY(hipStreamSynchronize(st));
-            if (*bad) return fail(DM_EINVAL, "a transmitted index is >= M");
+            const auto* h = reinterpret_cast<const unsigned long long*>(c->h_words + dmapi::kAccWord);
+            if (c->h_words[dmapi::kBadWord]) return fail(DM_EINVAL, "a transmitted index is >= M");
             for (int s = 0; s < nb; ++s) {
                 int64_t se = 0, be = 0;
                 for (int k = 0; k < dm::kAccSlots; ++k) {

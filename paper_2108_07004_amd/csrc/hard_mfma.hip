@@ -275,7 +275,7 @@ __global__ __launch_bounds__(kHardMfmaThreads) void hard_mfma_kernel(const HardA
     flush();
     if (a.exact) {
         exact = wave_sum_u32(exact);
-        if (lane == 0 && exact) atomicAdd(a.exact + (wave_slot % kQueueRegions) * kQueueStride, exact);
+        if (lane == 0 && exact) atomicAdd(a.exact + wave_slot, exact);
     }
 }
 

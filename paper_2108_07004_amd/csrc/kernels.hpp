@@ -11,15 +11,19 @@ namespace dm {
 // Table row stride used by the kernels for a dimensionality D (1..8 exact, else 16 or 32).
 int padded_dim(int D);
 
-// Symbols per tile of the FP32 kernel (one lane per symbol).
-int valu_tile_symbols();
+// Symbols per tile (threads per block) of the FP32 kernel, one lane per symbol: 512, or down to 64
+// when that many would leave CUs without a tile.
+int valu_tile_symbols(int64_t symbols, int cus);
 int hard_tile_symbols();
 hipError_t launch_hard_demap(const HardArgs& a, int grid, hipStream_t st);
 // MFMA decisions (split-FP16 operand table `frag` of the label-order points, r_max = max ||x||).
 hipError_t launch_hard_mfma(const HardArgs& a, const void* frag, float r_max, int cus, hipStream_t st);
 
 // FP32 direct-difference demapper (one lane per symbol, persistent grid).
-hipError_t launch_demap_valu(const LaunchArgs& a, int grid, hipStream_t st);
+hipError_t launch_demap_valu(const LaunchArgs& a, int grid, int threads, hipStream_t st);
+
+// Symbols that the waves of one fix-up block take at a time (one lane each).
+constexpr int kFixBlockSymbols = 256;
 
 // Exact recomputation of the queued (symbol, bit) pairs whose far-subset sum underflowed.
 hipError_t launch_fixup(const LaunchArgs& a, int grid, hipStream_t st);
@@ -53,8 +57,11 @@ int batched_tile_symbols(int kind);
 // capturing it).
 hipError_t prepare_batched(int prec);
 
-// Persistent batched kernel (prec selects the MFMA operand variant used by MFMA instances).
-hipError_t launch_demap_batched(const BatchArgs& a, int prec, int grid, hipStream_t st);
+// One persistent batched kernel (kBatchValu / kBatchSmall / kBatchLarge); prec selects the MFMA
+// operand variant.
+hipError_t launch_demap_batched(const BatchArgs& a, int which, int prec, int grid, hipStream_t st);
+hipError_t launch_demap_batched_valu(const BatchArgs& a, int grid, hipStream_t st);
+hipError_t prepare_batched_valu();
 
 // Fix-up of queued symbols of any instance (tables with row stride 8).
 hipError_t launch_batched_fixup(const BatchArgs& a, int grid, hipStream_t st);

@@ -332,7 +332,7 @@ __device__ __forceinline__ void mfma_subset_sums(const MfmaAcc& A, int h, float 
 // flagged bits are not queued: *defer receives the symbol's fix-up mask (both halves) and
 // defer_near its FixEntry.near word, for the caller to resolve or queue.
 template <typename T, int D, bool SPLIT, int MB>
-__device__ __forceinline__ void mfma_finish(const BlockView& b, const Sinks& k, const uint16_t* pv,
+__device__ __forceinline__ void mfma_finish(const BlockView& b, const Sinks& k, uint32_t* fill, const uint16_t* pv,
                                             const Frags<T, Slots<D, SPLIT>::S>& bfr, const float (&S0)[MB],
                                             const float (&S1)[MB], float tot, int64_t n, bool active, bool bad,
                                             int txl, int lane, float& g, float& mi, uint32_t* defer = nullptr,
@@ -492,7 +492,7 @@ __device__ __forceinline__ void mfma_finish(const BlockView& b, const Sinks& k, 
     }
     if (mask && active && h == 0) {
         double gc = 0.0, mc = 0.0;
-        queue_or_fix<D>(b, k, (uint32_t)n, mask, near_word(stot, m, bad_sym), gc, mc);
+        queue_or_fix<D, D>(b, k, fill, (uint32_t)n, mask, near_word(stot, m, bad_sym), gc, mc);
         g += (float)gc;
         mi += (float)mc;
     }
@@ -502,7 +502,7 @@ __device__ __forceinline__ void mfma_finish(const BlockView& b, const Sinks& k, 
 // Subset sums of the first MB label bits and mfma_finish with MB bits known at compile time
 // (MB == 16: b.m bits at run time).
 template <typename T, int D, bool SPLIT, int MB>
-__device__ __forceinline__ void mfma_epilogue_m(const BlockView& b, const Sinks& k, const uint16_t* pv,
+__device__ __forceinline__ void mfma_epilogue_m(const BlockView& b, const Sinks& k, uint32_t* fill, const uint16_t* pv,
                                                 const Frags<T, Slots<D, SPLIT>::S>& bfr, const MfmaAcc& A,
                                                 int64_t n, bool active, bool bad, int txl, int lane, float& g,
                                                 float& mi) {
@@ -514,23 +514,23 @@ __device__ __forceinline__ void mfma_epilogue_m(const BlockView& b, const Sinks&
         S0[p] = S0a[p];
         S1[p] = S1a[p];
     }
-    mfma_finish<T, D, SPLIT, MB>(b, k, pv, bfr, S0, S1, tot, n, active, bad, txl, lane, g, mi);
+    mfma_finish<T, D, SPLIT, MB>(b, k, fill, pv, bfr, S0, S1, tot, n, active, bad, txl, lane, g, mi);
 }
 
 // The generic epilogue: subset sums from the accumulators, then mfma_finish over b.m bits; the
 // constellations of 512 to 4096 points (m = 9..12) take epilogues with m fixed at compile time
 // (no per-bit guards), the branch on m being uniform over the launch.
 template <typename T, int D, bool SPLIT>
-__device__ __forceinline__ void mfma_epilogue(const BlockView& b, const Sinks& k, const uint16_t* pv,
+__device__ __forceinline__ void mfma_epilogue(const BlockView& b, const Sinks& k, uint32_t* fill, const uint16_t* pv,
                                               const Frags<T, Slots<D, SPLIT>::S>& bfr, const MfmaAcc& A,
                                               int64_t n, bool active, bool bad, int txl, int lane, float& g,
                                               float& mi) {
     switch (b.m) {
-        case 9: mfma_epilogue_m<T, D, SPLIT, 9>(b, k, pv, bfr, A, n, active, bad, txl, lane, g, mi); break;
-        case 10: mfma_epilogue_m<T, D, SPLIT, 10>(b, k, pv, bfr, A, n, active, bad, txl, lane, g, mi); break;
-        case 11: mfma_epilogue_m<T, D, SPLIT, 11>(b, k, pv, bfr, A, n, active, bad, txl, lane, g, mi); break;
-        case 12: mfma_epilogue_m<T, D, SPLIT, 12>(b, k, pv, bfr, A, n, active, bad, txl, lane, g, mi); break;
-        default: mfma_epilogue_m<T, D, SPLIT, 16>(b, k, pv, bfr, A, n, active, bad, txl, lane, g, mi);
+        case 9: mfma_epilogue_m<T, D, SPLIT, 9>(b, k, fill, pv, bfr, A, n, active, bad, txl, lane, g, mi); break;
+        case 10: mfma_epilogue_m<T, D, SPLIT, 10>(b, k, fill, pv, bfr, A, n, active, bad, txl, lane, g, mi); break;
+        case 11: mfma_epilogue_m<T, D, SPLIT, 11>(b, k, fill, pv, bfr, A, n, active, bad, txl, lane, g, mi); break;
+        case 12: mfma_epilogue_m<T, D, SPLIT, 12>(b, k, fill, pv, bfr, A, n, active, bad, txl, lane, g, mi); break;
+        default: mfma_epilogue_m<T, D, SPLIT, 16>(b, k, fill, pv, bfr, A, n, active, bad, txl, lane, g, mi);
     }
 }
 
