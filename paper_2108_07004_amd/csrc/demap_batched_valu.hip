@@ -4,7 +4,7 @@
 // D; the tables' row stride is 8) and M = 2 .. 64 at compile time.  Padding every instance to 16
 // points of 8 coordinates, as one body for all shapes had to, made an 8-QAM symbol five times as long
 // (the shaping search's launches of 2^21 symbols: 72 us, now 33).  Sixty-four mixed instances of
-// 2^16 .. 2^20 symbols: 7.8 ms in one kernel for all bodies, 5.0 + 1.3 + 0.2 ms in three.
+// 2^14 .. 2^22 symbols: 7.8 ms in one kernel for all bodies, 5.0 + 1.3 + 0.2 ms in three.
 #include "device_common.hpp"
 #include "kernels.hpp"
 #include "valu_body.hpp"
