@@ -255,7 +255,7 @@ int run_chunk_on(dm_constellation* c, const ChunkScratch& scr, int n_snr, const 
             return fail(DM_EUNSUPPORTED, "the operand table of precision %d is not built for this constellation", prec);
     }
     const bool fp32 = prec == DM_PREC_FP32;
-    const int tile = fp32 ? dm::valu_tile_symbols(N * n_snr, c->cus) : dm::mfma_block_symbols();
+    const int tile = fp32 ? dm::valu_tile_symbols(N * n_snr, c->cus) : dm::mfma_block_symbols(c->M, c->D, N * n_snr, c->cus);
     const int64_t tiles_per_snr = (N + tile - 1) / tile;
     LaunchArgs a = base_args(c, N);
     a.tx = tx;
@@ -274,7 +274,8 @@ int run_chunk_on(dm_constellation* c, const ChunkScratch& scr, int n_snr, const 
         a.snr[s].c = exponent_scale(sigma2[s]);
     }
     // FP32: two 512-thread blocks per CU, four for the small tables (few registers, short symbols)
-    const int grid = persistent_grid(c, tiles_per_snr * n_snr, !fp32 ? 1 : c->M <= 64 ? 4 : 2);
+    const int grid = persistent_grid(c, tiles_per_snr * n_snr,
+                                     fp32 ? (c->M <= 64 ? 4 : 2) : dm::mfma_small_supported(c->M, c->D) ? (c->M == 256 ? 3 : 4) : 1);
     a.sinks.queue_regions = grid;
     a.sinks.queue_seg = scr.queue_cap / (uint32_t)grid;
     // no more fix-up blocks than the symbols could fill (64 per wave): an empty pass then costs less
@@ -286,7 +287,7 @@ int run_chunk_on(dm_constellation* c, const ChunkScratch& scr, int n_snr, const 
         if (pr.e0) DM_HIP_TRY(hipEventRecord(pr.e0, st));
     }
     if (fp32) DM_HIP_TRY(dm::launch_demap_valu(a, grid, tile, st));
-    else DM_HIP_TRY(dm::launch_demap_mfma(a, prec, c->d_frag[prec], c->d_pv[prec], grid, st));
+    else DM_HIP_TRY(dm::launch_demap_mfma(a, prec, c->d_frag[prec], c->d_pv[prec], grid, tile, st));
     if (pr.e1) DM_HIP_TRY(hipEventRecord(pr.e1, st));
     DM_HIP_TRY(dm::launch_fixup(a, fix_grid, st));
     if (pr.e2) {

@@ -145,10 +145,13 @@ int mfma_slots(int D, bool split) {
     return 16 * ((used + 15) / 16);
 }
 
-int mfma_block_symbols() { return (kMfmaThreads / 64) * 32; }
+int mfma_block_symbols(int M, int D, int64_t symbols, int cus) {
+    return mfma_small_supported(M, D) ? mfma_small_threads(symbols, cus) : (kMfmaThreads / 64) * 32;
+}
 
-hipError_t launch_demap_mfma(const LaunchArgs& a, int prec, const void* frag, const void* pv, int grid, hipStream_t st) {
-    if (mfma_small_supported(a.M, a.D)) return launch_demap_mfma_small(a, prec, frag, pv, grid, st);
+hipError_t launch_demap_mfma(const LaunchArgs& a, int prec, const void* frag, const void* pv, int grid, int tile,
+                             hipStream_t st) {
+    if (mfma_small_supported(a.M, a.D)) return launch_demap_mfma_small(a, prec, frag, pv, grid, tile, st);
     switch (prec) {
         case 1: return launch_d<__bf16, false>(a, frag, pv, grid, st);
         case 2: return launch_d<_Float16, false>(a, frag, pv, grid, st);

@@ -3,7 +3,7 @@
 // tile count fixed at compile time (tile loop and subset sums in mfma_small.hpp, epilogue in
 // mfma_body.hpp).  The whole operand table (at most 8 tiles x 2 MFMAs x 1 KiB), the FP32 points
 // (at most 8 KiB) and the row-to-label map are staged in LDS once per block, so that the
-// transmitted label and its point, read once per batch, cost LDS rather than global-memory
+// transmitted label and its point, read once per symbol, cost LDS rather than global-memory
 // latency.  With split FP16 operands the MI term takes the transmitted point's exponent from the
 // direct FP32 differences (a few VALU instructions) instead of a diagonal MFMA product and a
 // register select; the other precisions keep the diagonal product (their per-label operand
@@ -19,11 +19,17 @@ namespace dm {
 
 namespace {
 
-constexpr int kThreads = 1024;  // 16 waves; one block per CU (128 VGPRs per lane)
-constexpr int kWaves = kThreads / 64;
+// Most threads per block.  A wave takes 64 symbols, one per lane, through the tile loop 32 at a time: what
+// is done once per symbol (operand splitting, flags, MI term, FP64 sums, loads) then fills the lanes
+// instead of running in both halves, and half the vector instructions of an 8-tile batch were outside
+// its tile loop.  The first half's sums wait in registers, so 256 points take 160 of them per lane:
+// three waves per SIMD (at four, 18 registers spilled and a third of the gain was lost); fewer points
+// fit four.  Measured, DP-16QAM, 8 x 2^20 symbols: split FP16 497 -> 458 us (four waves: 478), split
+// BF16 513 -> 480 us; 64-QAM split FP16 226 -> 183 us.
+constexpr int kThreads = 256;
 
 template <typename T, int D, bool SPLIT, int NT>
-__global__ __launch_bounds__(kThreads) void demap_mfma_small_kernel(const LaunchArgs a, const uint4* __restrict__ frag,
+__global__ __launch_bounds__(kThreads, NT == 8 ? 3 : 4) void demap_mfma_small_kernel(const LaunchArgs a, const uint4* __restrict__ frag,
                                                                     const uint16_t* __restrict__ pv) {
     constexpr int S = Slots<D, SPLIT>::S;
     constexpr int MB = SmallBits<NT>::MB;  // label bits of the constellation
@@ -34,21 +40,19 @@ __global__ __launch_bounds__(kThreads) void demap_mfma_small_kernel(const Launch
     __shared__ uint4 lds_pv[kDirectTx ? 1 : NT * 32 * 2 * S];  // [label][16 S halves]
     __shared__ uint16_t lds_r2l[NT * 32];       // row -> label
     __shared__ uint32_t s_fill;                 // entries in this block's fix-up queue region
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, threads = blockDim.x;
     if (tid == 0) s_fill = 0u;
     const int lane = tid & 63;
-    const int h = lane >> 5;
-    const int wave = tid >> 6;
-    const int wave_slot = (blockIdx.x * kWaves + wave) % kAccSlots;
+    const int wave_slot = (blockIdx.x * (threads >> 6) + (tid >> 6)) % kAccSlots;
     const Sinks& k = a.sinks;
-    for (int i = tid; i < NT * S * 64; i += kThreads) lds_frag[i] = frag[i];
-    for (int i = tid; i < NT * 32 * D; i += kThreads) lds_tab[i] = a.table[i];
+    for (int i = tid; i < NT * S * 64; i += threads) lds_frag[i] = frag[i];
+    for (int i = tid; i < NT * 32 * D; i += threads) lds_tab[i] = a.table[i];
     if constexpr (!kDirectTx)
-        for (int i = tid; i < NT * 32 * 2 * S; i += kThreads) lds_pv[i] = reinterpret_cast<const uint4*>(pv)[i];
-    for (int i = tid; i < NT * 32; i += kThreads) lds_r2l[i] = a.row2label[i];
+        for (int i = tid; i < NT * 32 * 2 * S; i += threads) lds_pv[i] = reinterpret_cast<const uint4*>(pv)[i];
+    for (int i = tid; i < NT * 32; i += threads) lds_r2l[i] = a.row2label[i];
     __syncthreads();
 
-    const int64_t sym_per_blk = (int64_t)kWaves * 32;
+    const int64_t sym_per_blk = threads;
     const int64_t blks_per_snr = (a.N + sym_per_blk - 1) / sym_per_blk;
     const int64_t total = blks_per_snr * a.n_snr;
     double gsum = 0.0, msum = 0.0;
@@ -63,10 +67,9 @@ __global__ __launch_bounds__(kThreads) void demap_mfma_small_kernel(const Launch
     int s_idx = (int)(blockIdx.x / blks_per_snr);
     int64_t r = blockIdx.x - (int64_t)s_idx * blks_per_snr;
     // The received symbols and transmitted rows of the next batch are loaded one batch ahead:
-    // their latency overlaps the current batch's tile loop and epilogue.
-    const int sub = wave * 32 + (lane & 31);
+    // their latency overlaps the current batch's tile loops and epilogue.
     auto fetch = [&](int s, int64_t rr, float (&yy)[D], uint32_t& row) {
-        const int64_t n = rr * sym_per_blk + sub;
+        const int64_t n = rr * sym_per_blk + tid;
         const bool act = n < a.N;
         const float* yrow = a.snr[s].y + (size_t)(act ? n : 0) * D;
 #pragma unroll
@@ -77,7 +80,7 @@ __global__ __launch_bounds__(kThreads) void demap_mfma_small_kernel(const Launch
     uint32_t row_nx = 0;
     if ((int64_t)blockIdx.x < total) fetch(s_idx, r, y_nx, row_nx);
     for (int64_t bt = blockIdx.x; bt < total; bt += gridDim.x) {
-        const int64_t n = r * sym_per_blk + sub;
+        const int64_t n = r * sym_per_blk + tid;
         if (s_idx != cur) {
             if (cur >= 0 && k.acc) flush();
             gsum = msum = 0.0;
@@ -104,33 +107,37 @@ __global__ __launch_bounds__(kThreads) void demap_mfma_small_kernel(const Launch
             }
             txl = (int)lds_r2l[row];
         }
+        PairSums<MB> P;
         bool bad = false;
-        const Frags<T, S> bfr = build_symbol_frags<T, D, SPLIT>(y, b.c, b.K, h, bad);
-
-        float S0[MB], S1[MB], tot;
-        mfma_small_sums<T, D, SPLIT, NT>(lds_frag, lane, bfr, S0, S1, tot);
+        float ttx = 0.0f;
+        {
+            Frags<T, S> f0, f1;
+            build_pair_frags<T, D, SPLIT>(y, b.c, b.K, f0, f1, bad);
+            mfma_pair_sums<T, D, SPLIT, NT>(lds_frag, lane, f0, f1, P);
+            if constexpr (!kDirectTx)
+                if (b.tx) ttx = pair_diagonal<T, D, SPLIT>(reinterpret_cast<const uint16_t*>(lds_pv), f0, f1, txl, lane);
+        }
         // The MI term's exponent of the transmitted point: with split FP16 operands from the
         // direct FP32 differences (the MFMA exponents carry ~1e-6 of rounding, which then stays
         // in the MI term instead of cancelling); with the coarser BF16 split and the plain
         // operands from the same MFMA arithmetic as the sum, so that the transmitted point's own
         // rounding cancels (with BF16 splits the direct form was 1.2e-4 bit off in MI on
         // DP-16QAM at high SNR).
-        const float ttx = fmaf(-b.c, sqdist<D>(y, lds_tab + txl * D), b.K);
-        float g, mi;
+        if constexpr (kDirectTx) ttx = fmaf(-b.c, sqdist<D>(y, lds_tab + txl * D), b.K);
+        float ge, go, mi;
         uint32_t mask, near;
-        mfma_finish<T, D, SPLIT, MB>(b, k, &s_fill, reinterpret_cast<const uint16_t*>(lds_pv), bfr, S0, S1, tot, n, active, bad,
-                                     txl, lane, g, mi, &mask, &near, kDirectTx ? &ttx : nullptr);
+        mfma_pair_finish<MB>(b, P, n, active, bad, txl, ttx, ge, go, mi, mask, near);
         // far subsets of flagged bits resolved in the wave (at high SNR nearly every batch has
         // some; each would otherwise be a queue entry and a recomputation from the queue)
-        mfma_small_far_pass<T, D, SPLIT, NT>(lds_frag, lane, y, b.c, b.K, bad, b, n, active, txl, near, mask, g);
-        if (mask && active && h == 0) {
+        mfma_pair_far_pass<T, D, SPLIT, NT>(lds_frag, lane, y, b.c, b.K, bad, b, n, active, txl, near, mask, ge, go);
+        if (mask && active) {
             double gc = 0.0, mc = 0.0;
             queue_or_fix<D, D>(b, k, &s_fill, (uint32_t)n, mask, near, gc, mc);
-            g += (float)gc;
+            ge += (float)gc;
             mi += (float)mc;
         }
         if (k.acc && active) {
-            gsum += (double)g;
+            gsum += (double)ge + (double)go;
             msum += (double)mi;
         }
     }
@@ -139,25 +146,25 @@ __global__ __launch_bounds__(kThreads) void demap_mfma_small_kernel(const Launch
 }
 
 template <typename T, int D, bool SPLIT>
-hipError_t launch_nt(const LaunchArgs& a, const void* frag, const void* pv, int grid, hipStream_t st) {
+hipError_t launch_nt(const LaunchArgs& a, const void* frag, const void* pv, int grid, int threads, hipStream_t st) {
     const uint4* f = (const uint4*)frag;
     const uint16_t* p = (const uint16_t*)pv;
     switch (a.M) {
-        case 32: hipLaunchKernelGGL((demap_mfma_small_kernel<T, D, SPLIT, 1>), dim3(grid), dim3(kThreads), 0, st, a, f, p); break;
-        case 64: hipLaunchKernelGGL((demap_mfma_small_kernel<T, D, SPLIT, 2>), dim3(grid), dim3(kThreads), 0, st, a, f, p); break;
-        case 128: hipLaunchKernelGGL((demap_mfma_small_kernel<T, D, SPLIT, 4>), dim3(grid), dim3(kThreads), 0, st, a, f, p); break;
-        case 256: hipLaunchKernelGGL((demap_mfma_small_kernel<T, D, SPLIT, 8>), dim3(grid), dim3(kThreads), 0, st, a, f, p); break;
+        case 32: hipLaunchKernelGGL((demap_mfma_small_kernel<T, D, SPLIT, 1>), dim3(grid), dim3(threads), 0, st, a, f, p); break;
+        case 64: hipLaunchKernelGGL((demap_mfma_small_kernel<T, D, SPLIT, 2>), dim3(grid), dim3(threads), 0, st, a, f, p); break;
+        case 128: hipLaunchKernelGGL((demap_mfma_small_kernel<T, D, SPLIT, 4>), dim3(grid), dim3(threads), 0, st, a, f, p); break;
+        case 256: hipLaunchKernelGGL((demap_mfma_small_kernel<T, D, SPLIT, 8>), dim3(grid), dim3(threads), 0, st, a, f, p); break;
         default: return hipErrorNotSupported;
     }
     return hipGetLastError();
 }
 
 template <typename T, bool SPLIT>
-hipError_t launch_d(const LaunchArgs& a, const void* frag, const void* pv, int grid, hipStream_t st) {
+hipError_t launch_d(const LaunchArgs& a, const void* frag, const void* pv, int grid, int threads, hipStream_t st) {
     switch (a.D) {
-        case 2: return launch_nt<T, 2, SPLIT>(a, frag, pv, grid, st);
-        case 4: return launch_nt<T, 4, SPLIT>(a, frag, pv, grid, st);
-        case 8: return launch_nt<T, 8, SPLIT>(a, frag, pv, grid, st);
+        case 2: return launch_nt<T, 2, SPLIT>(a, frag, pv, grid, threads, st);
+        case 4: return launch_nt<T, 4, SPLIT>(a, frag, pv, grid, threads, st);
+        case 8: return launch_nt<T, 8, SPLIT>(a, frag, pv, grid, threads, st);
         default: return hipErrorNotSupported;
     }
 }
@@ -166,14 +173,22 @@ hipError_t launch_d(const LaunchArgs& a, const void* frag, const void* pv, int g
 
 bool mfma_small_supported(int M, int D) { return M >= 32 && M <= 256 && (D == 2 || D == 4 || D == 8); }
 
+// The fewer the symbols, the smaller the blocks, so that each CU has some; 256 symbols a block (four or
+// three blocks per CU) leave the ends of a large launch even.
+int mfma_small_threads(int64_t symbols, int cus) {
+    int t = 64;
+    while (t < kThreads && symbols > (int64_t)cus * t) t *= 2;
+    return t;
+}
+
 hipError_t launch_demap_mfma_small(const LaunchArgs& a, int prec, const void* frag, const void* pv, int grid,
-                                   hipStream_t st) {
+                                   int threads, hipStream_t st) {
     if (!mfma_small_supported(a.M, a.D)) return hipErrorNotSupported;
     switch (prec) {
-        case 1: return launch_d<__bf16, false>(a, frag, pv, grid, st);
-        case 2: return launch_d<_Float16, false>(a, frag, pv, grid, st);
-        case 3: return launch_d<__bf16, true>(a, frag, pv, grid, st);
-        case 4: return launch_d<_Float16, true>(a, frag, pv, grid, st);
+        case 1: return launch_d<__bf16, false>(a, frag, pv, grid, threads, st);
+        case 2: return launch_d<_Float16, false>(a, frag, pv, grid, threads, st);
+        case 3: return launch_d<__bf16, true>(a, frag, pv, grid, threads, st);
+        case 4: return launch_d<_Float16, true>(a, frag, pv, grid, threads, st);
         default: return hipErrorInvalidValue;
     }
 }

@@ -37,18 +37,21 @@ inline int fixup_blocks_per_cu(int M) { return (int)std::min<size_t>(8, (160 * 1
 int mfma_slots(int D, bool split);
 
 // Symbols per block iteration of the MFMA kernel.
-int mfma_block_symbols();
+int mfma_block_symbols(int M, int D, int64_t symbols, int cus);
 
 // MFMA demapper specialised for M = 32..256 points and D in {2, 4, 8} (tile count and label
 // bits known at compile time); hipErrorNotSupported for other shapes.
 bool mfma_small_supported(int M, int D);
 hipError_t launch_demap_mfma_small(const LaunchArgs& a, int prec, const void* frag, const void* pv, int grid,
-                                   hipStream_t st);
+                                   int threads, hipStream_t st);
+// Threads (and symbols) per block of that kernel for a launch of so many symbols.
+int mfma_small_threads(int64_t symbols, int cus);
 
 // MFMA demapper: prec 1 = BF16, 2 = FP16, 3 = BF16 split, 4 = FP16 split.  `frag` is the
 // point-side operand table in fragment order ([tile][mfma][lane] x 16 bytes); `pv` the same
 // operands per label ([label][K slots], 16-bit), read for the transmitted points.
-hipError_t launch_demap_mfma(const LaunchArgs& a, int prec, const void* frag, const void* pv, int grid, hipStream_t st);
+hipError_t launch_demap_mfma(const LaunchArgs& a, int prec, const void* frag, const void* pv, int grid, int tile,
+                             hipStream_t st);
 
 // Symbols per work item of the batched kernel for an instance kind (kKindValu / kKindMfma).
 int batched_tile_symbols(int kind);

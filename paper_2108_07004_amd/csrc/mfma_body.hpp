@@ -324,19 +324,67 @@ __device__ __forceinline__ void mfma_subset_sums(const MfmaAcc& A, int h, float 
     }
 }
 
+// Exponent of the transmitted point (label txl) of symbol lane % 32, in both lane halves, from the same
+// MFMA arithmetic as the sum (so the rounding of beta and of the cross term cancels): lane l feeds row
+// l%32 with the point-side vector of its own symbol's transmitted label; the diagonal element (l%32,
+// l%32) sits in register 4*(j>>3) + (j&3) of the lane half (j>>2)&1.
+template <typename T, int D, bool SPLIT, bool TREE>
+__device__ __forceinline__ float mfma_diagonal(const uint16_t* pv, const Frags<T, Slots<D, SPLIT>::S>& bfr, int txl,
+                                               int lane) {
+    using V = typename Mma<T>::V;
+    constexpr int S = Slots<D, SPLIT>::S;
+    const int h = lane >> 5;
+    const uint16_t* pr = pv + (size_t)txl * (16 * S) + 8 * h;
+    f32x16 dg = Mma<T>::run(__builtin_bit_cast(V, *(const uint4*)pr), bfr.v[0]);
+#pragma unroll
+    for (int s2 = 1; s2 < S; ++s2)
+        dg = Mma<T>::run(__builtin_bit_cast(V, *(const uint4*)(pr + 16 * s2)), bfr.v[s2], dg);
+    const int j = lane & 31;
+    int rd = 4 * (j >> 3) + (j & 3);
+    asm volatile("" : "+v"(rd));  // keeps the lane masks below from being hoisted out of the loop
+    float v;
+    if constexpr (TREE) {
+        // dg[rd] by a four-level tree of bit selects (all-ones masks from the bits of rd): no
+        // serial compare chain, and no run-time register index for the compiler to form.
+        // The constellations of up to 256 points have the registers for it; the larger ones,
+        // at the 128-register cap, keep the compare chain below.
+        // (each element is copied to a scalar before the bit cast: this compiler casts
+        // element 0 for a bit cast applied to an element of a vector-typed value)
+        uint32_t w[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const float f = dg[r];
+            w[r] = __builtin_bit_cast(uint32_t, f);
+        }
+#pragma unroll
+        for (int lvl = 0; lvl < 4; ++lvl) {
+            const uint32_t pick = 0u - (((uint32_t)rd >> lvl) & 1u);  // 0 or all ones
+#pragma unroll
+            for (int i = 0; i < (8 >> lvl); ++i) w[i] = (w[2 * i + 1] & pick) | (w[2 * i] & ~pick);
+        }
+        v = __builtin_bit_cast(float, w[0]);
+    } else {
+        v = dg[0];
+#pragma unroll
+        for (int r = 1; r < 16; ++r) v = (rd == r) ? dg[r] : v;
+    }
+    // The lane half (j >> 2) & 1 holds the diagonal element; after the swap it is r1 if
+    // that half is the upper one, else r0, in both halves.
+    uint32_t v0, v1;
+    swap_halves(__builtin_bit_cast(uint32_t, v), __builtin_bit_cast(uint32_t, v), v0, v1);
+    return __builtin_bit_cast(float, ((j >> 2) & 1) ? v1 : v0);
+}
+
 // Combine the two lanes of each symbol, write LLRs, flag and queue underflowed bits and form
 // the per-symbol GMI (both halves) and MI (half 0) terms, from this half's subset sums S0 / S1
 // and total tot.  MB < 16: the constellation has exactly MB label bits (known at compile
 // time); MB == 16: b.m bits.  txl is the symbol's transmitted label (0 without tx), loaded by
-// the caller before the tile loop so that its latency is hidden.  With a non-null defer the
-// flagged bits are not queued: *defer receives the symbol's fix-up mask (both halves) and
-// defer_near its FixEntry.near word, for the caller to resolve or queue.
+// the caller before the tile loop so that its latency is hidden.
 template <typename T, int D, bool SPLIT, int MB>
 __device__ __forceinline__ void mfma_finish(const BlockView& b, const Sinks& k, uint32_t* fill, const uint16_t* pv,
                                             const Frags<T, Slots<D, SPLIT>::S>& bfr, const float (&S0)[MB],
                                             const float (&S1)[MB], float tot, int64_t n, bool active, bool bad,
-                                            int txl, int lane, float& g, float& mi, uint32_t* defer = nullptr,
-                                            uint32_t* defer_near = nullptr, const float* ttx_direct = nullptr) {
+                                            int txl, int lane, float& g, float& mi) {
     using V = typename Mma<T>::V;
     constexpr int S = Slots<D, SPLIT>::S;
     constexpr int NJ = (MB + 1) / 2;
@@ -416,64 +464,9 @@ __device__ __forceinline__ void mfma_finish(const BlockView& b, const Sinks& k, 
             }
         }
     }
-    // MI term: the exponent of the transmitted point comes from the same MFMA arithmetic
-    // as the sum (so the rounding of beta and of the cross term cancels): lane l feeds row
-    // l%32 with the point-side vector of its own symbol's transmitted label; the diagonal
-    // element (l%32, l%32) sits in register 4*(j>>3) + (j&3) of the lane half (j>>2)&1.
     mi = 0.0f;
-    if (b.tx && ttx_direct) {
-        // the caller's FP32 exponent of the transmitted point, K - c ||y - x_tx||^2 from the
-        // direct differences: it differs from that point's MFMA exponent inside stot by the
-        // operands' rounding (~1e-5 in log2 units for the split precisions), not by a bias
-        if (h == 0) {
-            if (!bad_sym && stot >= b.flag_thresh && stot < 3.0e38f) {
-                const int e = __builtin_amdgcn_frexp_expf(stot);
-                const float mant = __builtin_amdgcn_frexp_mantf(stot);
-                mi = ((float)(m - e) + *ttx_direct) - hw_log2(mant);
-            } else {
-                mask |= kMiFlag;
-            }
-        }
-    } else if (b.tx) {
-        const uint16_t* pr = pv + (size_t)txl * (16 * S) + 8 * h;
-        f32x16 dg = Mma<T>::run(__builtin_bit_cast(V, *(const uint4*)pr), bfr.v[0]);
-#pragma unroll
-        for (int s2 = 1; s2 < S; ++s2)
-            dg = Mma<T>::run(__builtin_bit_cast(V, *(const uint4*)(pr + 16 * s2)), bfr.v[s2], dg);
-        const int j = lane & 31;
-        int rd = 4 * (j >> 3) + (j & 3);
-        asm volatile("" : "+v"(rd));  // keeps the lane masks below from being hoisted out of the loop
-        float v;
-        if constexpr (MB <= 8) {
-            // dg[rd] by a four-level tree of bit selects (all-ones masks from the bits of rd): no
-            // serial compare chain, and no run-time register index for the compiler to form.
-            // The constellations of up to 256 points have the registers for it; the larger ones,
-            // at the 128-register cap, keep the compare chain below.
-            // (each element is copied to a scalar before the bit cast: this compiler casts
-            // element 0 for a bit cast applied to an element of a vector-typed value)
-            uint32_t w[16];
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const float f = dg[r];
-                w[r] = __builtin_bit_cast(uint32_t, f);
-            }
-#pragma unroll
-            for (int lvl = 0; lvl < 4; ++lvl) {
-                const uint32_t pick = 0u - (((uint32_t)rd >> lvl) & 1u);  // 0 or all ones
-#pragma unroll
-                for (int i = 0; i < (8 >> lvl); ++i) w[i] = (w[2 * i + 1] & pick) | (w[2 * i] & ~pick);
-            }
-            v = __builtin_bit_cast(float, w[0]);
-        } else {
-            v = dg[0];
-#pragma unroll
-            for (int r = 1; r < 16; ++r) v = (rd == r) ? dg[r] : v;
-        }
-        // The lane half (j >> 2) & 1 holds the diagonal element; after the swap it is r1 if
-        // that half is the upper one, else r0, in both halves.
-        uint32_t v0, v1;
-        swap_halves(__builtin_bit_cast(uint32_t, v), __builtin_bit_cast(uint32_t, v), v0, v1);
-        const float ttx = __builtin_bit_cast(float, ((j >> 2) & 1) ? v1 : v0);
+    if (b.tx) {
+        const float ttx = mfma_diagonal<T, D, SPLIT, (MB <= 8)>(pv, bfr, txl, lane);
         if (h == 0) {
             if (!bad_sym && stot >= b.flag_thresh && stot < 3.0e38f) {
                 const int e = __builtin_amdgcn_frexp_expf(stot);
@@ -485,11 +478,6 @@ __device__ __forceinline__ void mfma_finish(const BlockView& b, const Sinks& k, 
         }
     }
     mask = half_or(mask);
-    if (defer) {
-        *defer = mask;
-        *defer_near = near_word(stot, m, bad_sym);
-        return;
-    }
     if (mask && active && h == 0) {
         double gc = 0.0, mc = 0.0;
         queue_or_fix<D, D>(b, k, fill, (uint32_t)n, mask, near_word(stot, m, bad_sym), gc, mc);

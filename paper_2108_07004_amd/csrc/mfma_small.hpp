@@ -98,11 +98,109 @@ __device__ __forceinline__ void mfma_small_sums(const uint4* lds_frag, int lane,
     }
 }
 
-// Far-subset pass of an NT-tile constellation's 32-symbol batch (both lane halves of every
-// symbol call it; uniform per wave).  mask / near: the symbol's fix-up mask and near word from
-// mfma_finish (deferred); y, c, K: the symbol and its block's exponent scale and offset.  A
+// Subset sums of a wave's 64 symbols, one per lane: s0 / s1 over the points whose label bit p is 0 / 1,
+// stot over all points.
+template <int MB>
+struct PairSums {
+    float s0[MB], s1[MB], stot;
+};
+
+// The sums of 64 symbols from two passes over the tiles, 32 columns each (f0: symbols of lanes 0..31,
+// f1: of lanes 32..63).  One v_permlane32_swap of both passes' values of a sum gives every lane the
+// two label halves of its own symbol.
+template <typename T, int D, bool SPLIT, int NT>
+__device__ __forceinline__ void mfma_pair_sums(const uint4* lds_frag, int lane,
+                                               const Frags<T, Slots<D, SPLIT>::S>& f0,
+                                               const Frags<T, Slots<D, SPLIT>::S>& f1,
+                                               PairSums<SmallBits<NT>::MB>& P) {
+    constexpr int MB = SmallBits<NT>::MB;
+    float S0a[MB], S1a[MB], ta, S0b[MB], S1b[MB], tb;
+    mfma_small_sums<T, D, SPLIT, NT>(lds_frag, lane, f0, S0a, S1a, ta);
+    mfma_small_sums<T, D, SPLIT, NT>(lds_frag, lane, f1, S0b, S1b, tb);
+#pragma unroll
+    for (int p = 0; p < MB; ++p) {
+        if (p == 4) continue;
+        P.s0[p] = half_pair_sum(S0a[p], S0b[p]);
+        P.s1[p] = half_pair_sum(S1a[p], S1b[p]);
+    }
+    uint32_t r0, r1;  // the lane half is label bit 4
+    swap_halves(__float_as_uint(ta), __float_as_uint(tb), r0, r1);
+    P.s0[4] = __uint_as_float(r0);
+    P.s1[4] = __uint_as_float(r1);
+    P.stot = P.s0[4] + P.s1[4];
+}
+
+// The transmitted points' exponents from the MFMA arithmetic (see mfma_finish), one symbol per lane.
+template <typename T, int D, bool SPLIT>
+__device__ __forceinline__ float pair_diagonal(const uint16_t* pv, const Frags<T, Slots<D, SPLIT>::S>& f0,
+                                               const Frags<T, Slots<D, SPLIT>::S>& f1, int txl, int lane) {
+    uint32_t t0, t1;
+    swap_halves((uint32_t)txl, (uint32_t)txl, t0, t1);
+    const float a = mfma_diagonal<T, D, SPLIT, true>(pv, f0, (int)t0, lane);
+    const float c = mfma_diagonal<T, D, SPLIT, true>(pv, f1, (int)t1, lane);
+    return lane < 32 ? a : c;
+}
+
+// LLRs, flags and GMI / MI terms of one symbol per lane, the arithmetic of mfma_finish: ge / go are the
+// GMI terms of the even and odd label bits (two partial sums, as the two lane halves form them there);
+// mask, near: the fix-up mask of the flagged bits and the near word, for the caller to resolve.
+template <int MB>
+__device__ __forceinline__ void mfma_pair_finish(const BlockView& b, const PairSums<MB>& P, int64_t n, bool active,
+                                                 bool bad, int txl, float ttx, float& ge, float& go, float& mi,
+                                                 uint32_t& mask, uint32_t& near) {
+    const uint32_t lo_u = __builtin_bit_cast(uint32_t, b.flag_thresh);
+    const uint32_t hi_u = __builtin_bit_cast(uint32_t, 3.0e38f);
+    const float stot = P.stot;
+    const int es = __builtin_amdgcn_frexp_expf(stot);
+    const float ls = hw_log2(__builtin_amdgcn_frexp_mantf(stot));
+    ge = go = 0.0f;
+    uint32_t flagged = 0;
+    float Lv[MB];
+#pragma unroll
+    for (int p = 0; p < MB; ++p) {
+        const float s0 = P.s0[p], s1 = P.s1[p];
+        const uint32_t u0 = __builtin_bit_cast(uint32_t, s0), u1 = __builtin_bit_cast(uint32_t, s1);
+        const bool ok = !bad && min(u0, u1) >= lo_u && max(u0, u1) < hi_u;
+        float gb;
+        Lv[p] = llr_gmi(s0, s1, (txl >> p) & 1, es, ls, gb) * 0.69314718055994531f;
+        float& g = p & 1 ? go : ge;
+        g += ok ? gb : 0.0f;
+        flagged |= ok ? 0u : 1u << p;
+    }
+    if (b.llr && active) {
+        float* const out = b.llr + (size_t)n * MB;
+#pragma unroll
+        for (int j = 0; j < MB; ++j) out[j] = Lv[MB - 1 - j];
+    }
+    mask = 0u;
+    if (flagged) {  // rare: the GMI-only shortcut, else the exact fix-up
+#pragma unroll
+        for (int p = 0; p < MB; ++p) {
+            const float s0 = P.s0[p], s1 = P.s1[p];
+            if ((flagged >> p) & 1) {
+                const int bit = (txl >> p) & 1;
+                if (!bad && !b.want_llr && fmaxf(s0, s1) >= b.near_thresh && fmaxf(s0, s1) < 3.0e38f &&
+                    (bit ? s1 > s0 : s0 > s1)) {
+                    float& g = p & 1 ? go : ge;
+                    g += 1.0f;
+                } else {
+                    mask |= flag_bits(p, s0, s1);
+                }
+            }
+        }
+    }
+    mi = 0.0f;
+    if (b.tx) {
+        if (!bad && stot >= b.flag_thresh && stot < 3.0e38f) mi = ((float)(MB - es) + ttx) - ls;
+        else mask |= kMiFlag;
+    }
+    near = near_word(stot, MB, bad);
+}
+
+// Far-subset pass of a wave's 64 symbols (uniform per wave; a set of 32 without a flagged symbol is
+// skipped).  mask / near: the symbol's fix-up mask and near word from mfma_pair_finish; y, c, K: the symbol and its block's exponent scale and offset.  A
 // flagged bit whose symbol passed its near log-sum has a far subset whose terms all lie below
-// the flag bound sh = m - 102, so the batch runs the tile loop again with the exponent offset
+// the flag bound sh = m - 102, so the set runs the tile loop again with the exponent offset
 // lowered by sh: every far term is then kept to FP32 precision down to 2^-126, while near terms
 // overflow to +inf -- harmlessly, since every register-indexed sum and tile total that makes up
 // a far subset holds far terms only.  L = (sh + log2 S_far) - (near log-sum) with the sign of the
@@ -113,42 +211,48 @@ __device__ __forceinline__ void mfma_small_sums(const uint4* lds_frag, int lane,
 // symbol, near is set to kNearNone: the bits left would fail the fix-up's far-only sum the same
 // way (same shift, same bound), so the fix-up takes their two-pass sums at once.
 template <typename T, int D, bool SPLIT, int NT>
-__device__ __forceinline__ void mfma_small_far_pass(const uint4* lds_frag, int lane, const float (&y)[D], float c,
-                                                    float K, bool bad, const BlockView& b, int64_t n, bool active,
-                                                    int txl, uint32_t& near, uint32_t& mask, float& g) {
+__device__ __forceinline__ void mfma_pair_far_pass(const uint4* lds_frag, int lane, const float (&y)[D], float c,
+                                                   float K, bool bad, const BlockView& b, int64_t n, bool active,
+                                                   int txl, uint32_t& near, uint32_t& mask, float& ge, float& go) {
     constexpr int MB = SmallBits<NT>::MB;
     constexpr int S = Slots<D, SPLIT>::S;
     constexpr float sh = (float)(MB - 102);
     constexpr uint32_t kFarMask = (1u << (MB < kFarBits ? MB : kFarBits)) - 1u;
     const uint32_t far = (active && near != kNearNone) ? (mask & kFarMask) : 0u;
-    if (__ballot(far != 0u) == 0ull) return;  // uniform per wave
-    const int h = lane >> 5;
+    const uint64_t need = __ballot(far != 0u);
+    if (need == 0ull) return;  // uniform per wave
     bool bad2 = false;
-    const Frags<T, S> bfr2 = build_symbol_frags<T, D, SPLIT>(y, c, K - sh, h, bad2);
-    float S0[MB], S1[MB], tot;
-    mfma_small_sums<T, D, SPLIT, NT>(lds_frag, lane, bfr2, S0, S1, tot);
-    const bool bad_sym = half_or((uint32_t)(bad || bad2)) != 0;
+    Frags<T, S> f0, f1;
+    build_pair_frags<T, D, SPLIT>(y, c, K - sh, f0, f1, bad2);
+    const bool bad_sym = bad || bad2;
     const float near_lse = __builtin_bit_cast(float, near);
-    uint32_t done = 0u;
+#pragma unroll 1
+    for (int set = 0; set < 2; ++set) {
+        if ((uint32_t)(need >> (32 * set)) == 0u) continue;  // no symbol of these 32 lanes needs it
+        Frags<T, S> f;
 #pragma unroll
-    for (int j = 0; j < (MB + 1) / 2; ++j) {
-        // lane half h finishes bit 2j + h (the halves' partial sums meet in one swap)
-        const float c0 = half_pair_sum(S0[2 * j], 2 * j + 1 < MB ? S0[2 * j + 1] : 0.0f);
-        const float c1 = half_pair_sum(S1[2 * j], 2 * j + 1 < MB ? S1[2 * j + 1] : 0.0f);
-        const int p = 2 * j + h;
-        if (p < MB && ((far >> p) & 1u) && !bad_sym) {
-            const int fb = (int)((mask >> (kFarShift + p)) & 1u);
-            const float sf = fb ? c1 : c0;
-            if (sf >= 0x1p-95f && sf < 3.0e38f) {
-                const float lf = sh + hw_log2(sf);
-                const float L = fb ? lf - near_lse : near_lse - lf;
-                if (b.llr) b.llr[(size_t)n * MB + (MB - 1 - p)] = L * 0.69314718055994531f;
-                if (b.tx) g += gmi_bit_term(L, (txl >> p) & 1);
-                done |= 1u << p;
+        for (int s = 0; s < S; ++s) f.v[s] = set ? f1.v[s] : f0.v[s];
+        float S0[MB], S1[MB], tot;
+        mfma_small_sums<T, D, SPLIT, NT>(lds_frag, lane, f, S0, S1, tot);
+        const bool mine = (lane >> 5) == set && !bad_sym;
+#pragma unroll
+        for (int p = 0; p < MB; ++p) {
+            const float c0 = half_pair_sum(S0[p], S0[p]);
+            const float c1 = half_pair_sum(S1[p], S1[p]);
+            if (mine && ((far >> p) & 1u)) {
+                const int fb = (int)((mask >> (kFarShift + p)) & 1u);
+                const float sf = fb ? c1 : c0;
+                if (sf >= 0x1p-95f && sf < 3.0e38f) {
+                    const float lf = sh + hw_log2(sf);
+                    const float L = fb ? lf - near_lse : near_lse - lf;
+                    if (b.llr) b.llr[(size_t)n * MB + (MB - 1 - p)] = L * 0.69314718055994531f;
+                    float& g = p & 1 ? go : ge;
+                    if (b.tx) g += gmi_bit_term(L, (txl >> p) & 1);
+                    mask &= ~(1u << p);
+                }
             }
         }
     }
-    mask &= ~half_or(done);
     if (far != 0u && !bad_sym) near = kNearNone;
 }
 
