@@ -289,7 +289,8 @@ int run_chunk_on(dm_constellation* c, const ChunkScratch& scr, int n_snr, const 
     if (fp32) DM_HIP_TRY(dm::launch_demap_valu(a, grid, tile, st));
     else DM_HIP_TRY(dm::launch_demap_mfma(a, prec, c->d_frag[prec], c->d_pv[prec], grid, tile, st));
     if (pr.e1) DM_HIP_TRY(hipEventRecord(pr.e1, st));
-    DM_HIP_TRY(dm::launch_fixup(a, fix_grid, st));
+    if (dm::fixup_large_supported(c->M, c->D)) DM_HIP_TRY(dm::launch_fixup_large(a, c->cus, st));
+    else DM_HIP_TRY(dm::launch_fixup(a, fix_grid, st));
     if (pr.e2) {
         DM_HIP_TRY(hipEventRecord(pr.e2, st));
         g_prof.push_back(pr);

@@ -17,6 +17,7 @@ __device__ float wave_exact_llr2(const float (&y)[DP], const float* table, int M
                                  float& lse0) {
     const int lane = threadIdx.x & 63;
     float mx0 = -INFINITY, mx1 = -INFINITY;
+#pragma unroll 4
     for (int j = lane; j < M; j += 64) {
         const float t = fmaf(-c, sqdist<DP>(y, table + (size_t)j * DP), K);
         if (p >= 0 && ((j >> p) & 1)) mx1 = fmaxf(mx1, t);
@@ -25,6 +26,7 @@ __device__ float wave_exact_llr2(const float (&y)[DP], const float* table, int M
     mx0 = wave_max_f(mx0);
     mx1 = wave_max_f(mx1);
     float s0 = 0.0f, s1 = 0.0f;
+#pragma unroll 4
     for (int j = lane; j < M; j += 64) {
         const float t = fmaf(-c, sqdist<DP>(y, table + (size_t)j * DP), K);
         if (p >= 0 && ((j >> p) & 1)) s1 += hw_exp2(t - mx1);
@@ -45,6 +47,7 @@ __device__ float wave_exact_llr2(const float (&y)[DP], const float* table, int M
 __device__ __forceinline__ float cached_exact_llr2(const float* tl, int M, int p, float& lse0) {
     const int lane = threadIdx.x & 63;
     float mx0 = -INFINITY, mx1 = -INFINITY;
+#pragma unroll 8
     for (int j = lane; j < M; j += 64) {
         const float t = tl[j];
         if (p >= 0 && ((j >> p) & 1)) mx1 = fmaxf(mx1, t);
@@ -53,6 +56,7 @@ __device__ __forceinline__ float cached_exact_llr2(const float* tl, int M, int p
     mx0 = wave_max_f(mx0);
     mx1 = wave_max_f(mx1);
     float s0 = 0.0f, s1 = 0.0f;
+#pragma unroll 8
     for (int j = lane; j < M; j += 64) {
         const float t = tl[j];
         if (p >= 0 && ((j >> p) & 1)) s1 += hw_exp2(t - mx1);
@@ -75,8 +79,10 @@ __device__ void fixup_wave(const BlockView& b, const Sinks& k, uint32_t n, uint3
     load_symbol<DP>(y, b.y + (size_t)n * b.D, b.D, true);
     const int txl = b.tx ? tx_label(b, k, n) : 0;
     const bool cached = b.M <= cache_pts;  // uniform
-    if (cached)
+    if (cached) {
+#pragma unroll 4
         for (int j = lane; j < b.M; j += 64) tl[j] = fmaf(-b.c, sqdist<DP>(y, b.table + (size_t)j * DP), b.K);
+    }
     for (int p = 0; p < b.m; ++p) {
         if (!((mask >> p) & 1u)) continue;
         float lse0;
@@ -323,13 +329,14 @@ __device__ void fix_rows(const Sinks& k, ViewFn view, AddFn add, FetchFn fetch, 
 }
 
 // Exclusive prefix of the queue regions' fill into s_qpre[0 .. kMaxQueueRegions] (regions past the
-// last are empty); the block's kFixThreads threads compute it, the caller synchronises before
+// last are empty); the block's THREADS threads compute it, the caller synchronises before
 // reading it.
 constexpr int kFixThreads = 256;
 
+template <int THREADS>
 __device__ __forceinline__ void queue_prefix(const Sinks& k, uint32_t* s_qpre) {
-    constexpr int kPer = kMaxQueueRegions / kFixThreads;
-    __shared__ uint32_t s_wave[kFixThreads / 64];
+    constexpr int kPer = kMaxQueueRegions / THREADS;
+    __shared__ uint32_t s_wave[THREADS / 64];
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     uint32_t own[kPer], x = 0u;
 #pragma unroll
@@ -353,7 +360,7 @@ __device__ __forceinline__ void queue_prefix(const Sinks& k, uint32_t* s_qpre) {
         s_qpre[tid * kPer + q] = at;
         at += own[q];
     }
-    if (tid == kFixThreads - 1) s_qpre[kMaxQueueRegions] = at;
+    if (tid == THREADS - 1) s_qpre[kMaxQueueRegions] = at;
 }
 
 // Position in k.queue of entry i < s_qpre[kMaxQueueRegions] of the filled regions read as one list:
@@ -387,7 +394,7 @@ __device__ void drain_fix_queue(const Sinks& k, ViewFn view, float* tl, int cach
     __shared__ uint32_t s_qpre[kMaxQueueRegions + 1];  // exclusive prefix of the regions' fill
     for (int i = threadIdx.x; i < kFixLdsTags * 2; i += blockDim.x) s_acc[i] = 0ull;
     for (int i = threadIdx.x; i < kFixLdsTags; i += blockDim.x) s_pairs[i] = 0u;
-    queue_prefix(k, s_qpre);
+    queue_prefix<kFixThreads>(k, s_qpre);
     __syncthreads();
     auto fetch = [&](uint32_t i) -> FixEntry { return k.queue[queue_index(k, s_qpre, i)]; };
     auto count_pairs = [&](const FixEntry& e) {

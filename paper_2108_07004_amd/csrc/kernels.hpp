@@ -27,6 +27,9 @@ constexpr int kFixBlockSymbols = 256;
 
 // Exact recomputation of the queued (symbol, bit) pairs whose far-subset sum underflowed.
 hipError_t launch_fixup(const LaunchArgs& a, int grid, hipStream_t st);
+// The same for large tables (512 points and more that fit its LDS): one launch of at most cus blocks.
+bool fixup_large_supported(int M, int D);
+hipError_t launch_fixup_large(const LaunchArgs& a, int cus, hipStream_t st);
 // Exponent cache of the fix-up kernel (per wave, 4 waves per block) for an M-point constellation,
 // and the blocks per CU that fit it within 160 KiB of LDS and the kernel's 8 waves per SIMD.
 inline int fixup_cache_points(int M) { return M <= kFixCached ? ((M + 63) / 64) * 64 : 64; }
