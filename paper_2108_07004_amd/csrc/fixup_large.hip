@@ -5,9 +5,7 @@
 // the recomputation takes longer than the demapping.  With one wavefront per symbol every symbol reads
 // the whole table (64 KiB at 2048 points of 8D) from L2, and every flagged bit passes over all exponents
 // twice.  Here 64 symbols share each point read (from LDS, broadcast), and one pass serves all bits:
-//   t_j = K - c ||y - x_j||^2 in FP32 as everywhere, split into n + f with n whole, |f| <= 1/2;
-//   e_j = 2^n * 2^f as a double (2^f from v_exp_f32, n added to the exponent field),
-// so that the subset sums hold every term down to 2^-1000 and no maxima are needed.  The sums are taken
+// (wide_sums.hpp: FP32 exponents, sums with the exponent range of a double).  The sums are taken
 // over indexed accumulators as in valu_body.hpp: two FP64 additions per point.  A sum below 2^-980 (or
 // not finite) sends that bit to the wavefront form (fixup_wave).
 //
@@ -27,6 +25,7 @@
 #include "device_common.hpp"
 #include "fixup_drain.hpp"
 #include "kernels.hpp"
+#include "wide_sums.hpp"
 
 namespace dm {
 
@@ -41,29 +40,6 @@ constexpr int kXchg = kGroups * 4 * 2 * kRound * 64;  // doubles
 constexpr int kTot = kGroups * 4 * 64;
 constexpr size_t kLdsBytes = (size_t)kTabFloats * 4 + (size_t)(kXchg + kTot) * 8;
 static_assert(kLdsBytes >= (size_t)(kThreads / 64) * kFixCached * 4, "the wavefront form's exponent caches");
-constexpr double kSumMin = 0x1p-980, kSumMax = 0x1p+200;
-
-// 2^t as a double, t clamped to at least -1000.
-__device__ __forceinline__ double wide_exp2(float t) {
-    constexpr float kMagic = 12582912.0f;  // 1.5 * 2^23: the sum's low mantissa bits are the nearest whole number
-    t = fmaxf(t, -1000.0f);
-    const float z = t + kMagic;
-    const double e = (double)hw_exp2(t - (z - kMagic));
-    const uint64_t u = __builtin_bit_cast(uint64_t, e);
-    const uint32_t hi = (uint32_t)(u >> 32) + (__float_as_uint(z) << 20);
-    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | (uint32_t)u);
-}
-
-// log2(a) - log2(b) of two sums in range, with exact binary exponents.
-__device__ __forceinline__ float wide_log2_ratio(double a, double b) {
-    const int ea = __builtin_amdgcn_frexp_exp(a), eb = __builtin_amdgcn_frexp_exp(b);
-    const float ma = (float)__builtin_amdgcn_frexp_mant(a), mb = (float)__builtin_amdgcn_frexp_mant(b);
-    return (float)(ea - eb) + (hw_log2(ma) - hw_log2(mb));
-}
-
-__device__ __forceinline__ bool wide_ok(double a, double b) {
-    return fmin(a, b) >= kSumMin && fmax(a, b) < kSumMax;
-}
 
 template <int DP>
 __global__ __launch_bounds__(kThreads) void fixup_large_kernel(const LaunchArgs a, uint32_t lanes_from) {
@@ -215,8 +191,7 @@ __global__ __launch_bounds__(kThreads) void fixup_large_kernel(const LaunchArgs 
                 const double all = (t0 + t1) + (t2 + t3);
                 if (wide_ok(all, all)) {
                     const float ttx = fmaf(-b.c, sqdist<DP>(y, tab + (size_t)txl * DP), b.K);
-                    const int e2 = __builtin_amdgcn_frexp_exp(all);
-                    mc += (double)(((float)(m - e2) + ttx) - hw_log2((float)__builtin_amdgcn_frexp_mant(all)));
+                    mc += (double)wide_mi(m, all, ttx);
                 } else {
                     left |= kMiFlag;
                 }

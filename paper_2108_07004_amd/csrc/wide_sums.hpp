@@ -1,0 +1,39 @@
+// Sums of likelihoods with the exponent range of a double (gfx950), for the fix-up: exponents t in FP32
+// as everywhere, split into n + f with n whole and |f| <= 1/2, and 2^n * 2^f summed as doubles (2^f from
+// v_exp_f32, n added to the exponent field).  The sums hold every term down to 2^-1000, so no maxima
+// are needed and one pass over the points serves all label bits.
+#pragma once
+#include "device_common.hpp"
+
+namespace dm {
+
+// 2^t as a double, t clamped to at least -1000.
+__device__ __forceinline__ double wide_exp2(float t) {
+    constexpr float kMagic = 12582912.0f;  // 1.5 * 2^23: the sum's low mantissa bits are the nearest whole number
+    t = fmaxf(t, -1000.0f);
+    const float z = t + kMagic;
+    const double e = (double)hw_exp2(t - (z - kMagic));
+    const uint64_t u = __builtin_bit_cast(uint64_t, e);
+    const uint32_t hi = (uint32_t)(u >> 32) + (__float_as_uint(z) << 20);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | (uint32_t)u);
+}
+
+// log2(a) - log2(b) of two sums in range, with exact binary exponents.
+__device__ __forceinline__ float wide_log2_ratio(double a, double b) {
+    const int ea = __builtin_amdgcn_frexp_exp(a), eb = __builtin_amdgcn_frexp_exp(b);
+    const float ma = (float)__builtin_amdgcn_frexp_mant(a), mb = (float)__builtin_amdgcn_frexp_mant(b);
+    return (float)(ea - eb) + (hw_log2(ma) - hw_log2(mb));
+}
+
+// Both sums large enough that no term that matters was clamped, and finite.
+__device__ __forceinline__ bool wide_ok(double a, double b) {
+    return fmin(a, b) >= 0x1p-980 && fmax(a, b) < 0x1p+200;
+}
+
+// MI term of a symbol with m label bits: the sum over all points and the transmitted point's exponent.
+__device__ __forceinline__ float wide_mi(int m, double all, float ttx) {
+    const int e = __builtin_amdgcn_frexp_exp(all);
+    return ((float)(m - e) + ttx) - hw_log2((float)__builtin_amdgcn_frexp_mant(all));
+}
+
+}  // namespace dm

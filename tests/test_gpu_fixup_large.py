@@ -63,3 +63,20 @@ def test_non_finite_symbols_as_by_wavefronts():
         fin = np.isfinite(one)
         assert np.array_equal(one[~fin & ~np.isnan(one)], whole[i][~fin & ~np.isnan(one)]), i
         assert rel_err(whole[i][fin], one[fin].astype(np.float64)) <= 2 * LLR_TOL_FP32, i
+
+
+@pytest.mark.parametrize("M,D", [(16, 3), (16, 8), (32, 1), (32, 2), (64, 4), (64, 5), (64, 8)])
+def test_small_tables_by_lane(M, D):
+    """16 to 64 points, up to SNRs whose sums leave the one-pass form's range."""
+    const = W.gaussian_constellation(M, D, 67, M, D)
+    g = W.rng(67, "misc", M, D)
+    c = dm.Constellation(const.points, const.labels)
+    N = 700
+    tx = g.integers(0, M, N).astype(np.uint16)
+    blk = DeviceBlock(const, tx, g.standard_normal((N, D)), W.sigma2_from_snr_db(np.array([14.0, 22.0, 30.0, 45.0])))
+    llrs = blk.new_llrs()
+    gmi, mi = dm.gmi_estimate(c, blk.sigma2, blk.ys, blk.tx_t, llrs)
+    for s, s2 in enumerate(blk.sigma2):
+        ref = oracle.demap(const.points, const.labels, s2, blk.y_host(s), tx)
+        assert rel_err(llrs[s].cpu().numpy(), ref["llr"]) <= LLR_TOL_FP32, s
+        assert abs(gmi[s] - ref["gmi"]) <= GMI_TOL and abs(mi[s] - ref["mi_mean"]) <= GMI_TOL, s
