@@ -80,3 +80,24 @@ def test_small_tables_by_lane(M, D):
         ref = oracle.demap(const.points, const.labels, s2, blk.y_host(s), tx)
         assert rel_err(llrs[s].cpu().numpy(), ref["llr"]) <= LLR_TOL_FP32, s
         assert abs(gmi[s] - ref["gmi"]) <= GMI_TOL and abs(mi[s] - ref["mi_mean"]) <= GMI_TOL, s
+
+
+@pytest.mark.parametrize("M,D", [(128, 2), (256, 4)])
+@pytest.mark.parametrize("N", [1, 33, 600, 17000, 300000])
+def test_row_chunks(M, D, N):
+    """128 and 256 points: entry counts around the row form's chunk sizes, against the same symbols in
+    other launches (their LLRs are bit-identical) and, for the first of them, the oracle."""
+    import torch
+    const = W.gaussian_constellation(M, D, 68, M, D)
+    g = W.rng(68, "misc", M, D)
+    c = dm.Constellation(const.points, const.labels)
+    tx = g.integers(0, M, N).astype(np.uint16)
+    s2 = float(W.sigma2_from_snr_db(24.0))
+    y = W.awgn(const.points, tx, g.standard_normal((N, D)), s2)
+    y_t = torch.from_numpy(y).to("cuda:0")
+    whole = dm.demap_llr(c, s2, y_t)
+    n = min(N, 500)
+    ref = oracle.demap(const.points, const.labels, s2, y[:n], tx[:n])
+    assert rel_err(whole[:n].cpu().numpy(), ref["llr"]) <= LLR_TOL_FP32
+    for lo, hi in ((0, n), (N // 2, min(N, N // 2 + 3000))):
+        assert torch.equal(dm.demap_llr(c, s2, y_t[lo:hi].contiguous()), whole[lo:hi])
