@@ -535,7 +535,8 @@ int dm_demap_learned(dm_mlp* n, const dm_constellation* cc, int n_snr, const dou
     if ((r = ensure_packed(n, st))) return r;
     DM_HIP_TRY(hipMemsetAsync(n->acc, 0, acc_words * sizeof(unsigned long long), st));
     DM_HIP_TRY(hipMemsetAsync(n->bad, 0, sizeof(uint32_t), st));
-    auto infer = [&](int s, int64_t lo, int64_t hi, int set) -> int {
+    // symbols [lo, hi) of every point the network covers, a launch for up to kMaxSnrPerLaunch of them
+    auto infer = [&](int64_t lo, int64_t hi, int set) -> int {
         const int64_t cnt = hi - lo;
         if (cnt <= 0) return DM_OK;
         dm::MlpInferArgs a;
@@ -546,16 +547,24 @@ int dm_demap_learned(dm_mlp* n, const dm_constellation* cc, int n_snr, const dou
         a.D = n->D;
         a.m = n->m;
         a.M = c->M;
-        a.snr_feature = (float)((snr_db_of(sigma2[s]) - 7.5) / 7.5);
         a.bad_tx = tx ? n->bad : nullptr;
-        a.y = y[s] + lo * n->D;
         a.tx = tx ? tx + lo : nullptr;
-        a.llr = llr ? llr[s] + lo * n->m : nullptr;
         a.N = cnt;
-        a.acc = tx ? n->acc + ((size_t)s * 2 + set) * dm::kAccSlots * 2 : nullptr;
-        const int64_t tiles = (cnt + 31) / 32;
-        const int grid = (int)std::max<int64_t>(1, std::min<int64_t>((tiles + 7) / 8, n->cus));
-        DM_HIP_TRY(dm::launch_mlp_infer(a, grid, st));
+        for (int s = 0; s < n_snr; ++s) {
+            if (code[s] == DM_LEARNED_OK) {
+                dm::MlpInferPoint& p = a.pt[a.n_pts++];
+                p.y = y[s] + lo * n->D;
+                p.llr = llr ? llr[s] + lo * n->m : nullptr;
+                p.acc = tx ? n->acc + ((size_t)s * 2 + set) * dm::kAccSlots * 2 : nullptr;
+                p.snr_feature = (float)((snr_db_of(sigma2[s]) - 7.5) / 7.5);
+            }
+            if (a.n_pts == dm::kMaxSnrPerLaunch || (s == n_snr - 1 && a.n_pts > 0)) {
+                const int64_t tiles = (cnt + 31) / 32 * a.n_pts;
+                const int grid = (int)std::max<int64_t>(1, std::min<int64_t>((tiles + 7) / 8, n->cus));
+                DM_HIP_TRY(dm::launch_mlp_infer(a, grid, st));
+                a.n_pts = 0;
+            }
+        }
         return DM_OK;
     };
     auto* acc_h = (unsigned long long*)n->h_stage;
@@ -565,10 +574,8 @@ int dm_demap_learned(dm_mlp* n, const dm_constellation* cc, int n_snr, const dou
         for (int k = 0; k < dm::kAccSlots; ++k) v += (long long)acc_h[(((size_t)s * 2 + set) * dm::kAccSlots + k) * 2];
         return (double)v / dm::kFixScale;
     };
-    for (int s = 0; s < n_snr; ++s) {
-        if (gmi_loss) gmi_loss[s] = NAN;
-        if (code[s] == DM_LEARNED_OK && audit && (r = infer(s, 0, na, 0))) return r;
-    }
+    if (gmi_loss) std::fill(gmi_loss, gmi_loss + n_snr, NAN);
+    if (audit && (r = infer(0, na, 0))) return r;
     // 3. exact audit of the prefixes (one launch over all audited points; synchronises)
     std::vector<int> aud;
     for (int s = 0; s < n_snr; ++s)
@@ -594,8 +601,7 @@ int dm_demap_learned(dm_mlp* n, const dm_constellation* cc, int n_snr, const dou
         }
     }
     // 4. the network on the rest of every point it keeps; exact over whole blocks elsewhere
-    for (int s = 0; s < n_snr; ++s)
-        if (code[s] == DM_LEARNED_OK && (r = infer(s, audit ? na : 0, N, 1))) return r;
+    if ((r = infer(audit ? na : 0, N, 1))) return r;
     DM_HIP_TRY(hipMemcpyAsync(acc_h, n->acc, acc_words * sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
     DM_HIP_TRY(hipMemcpyAsync(bad_h, n->bad, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
     DM_HIP_TRY(hipStreamSynchronize(st));

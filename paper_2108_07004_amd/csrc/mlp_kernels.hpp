@@ -1,6 +1,8 @@
 // Host-visible argument blocks and launchers of the learned-demapper kernels.
 #pragma once
 #include <hip/hip_runtime.h>
+
+#include "device_common.hpp"
 #include <stdint.h>
 
 namespace dm {
@@ -43,17 +45,22 @@ struct AdamArgs {
 };
 
 // Inference: all BF16 weights staged in LDS; see mlp_infer.hip for the fragment layout.
+// One received block at its SNR.
+struct MlpInferPoint {
+    const float* y;           // N x D received symbols
+    float* llr;               // N x m or null
+    unsigned long long* acc;  // [kAccSlots][2] fixed-point GMI sum, or null
+    float snr_feature;        // (s - 7.5) / 7.5, s = -10 log10(2 sigma2)
+};
 struct MlpInferArgs {
+    MlpInferPoint pt[kMaxSnrPerLaunch];
+    int n_pts;
     const uint4* frag;      // [W1 | W2 | W3] operand fragments
     const float* bias;      // b1 (256, unused: packed into the fragments) | b2 (256) | b3 (32, zero past m)
-    const float* y;         // N x D received symbols
     const uint16_t* tx;     // N transmitted rows or null
     const uint16_t* row2label;
-    float* llr;             // N x m or null
-    int64_t N;
+    int64_t N;              // symbols per block
     int D, m, M;
-    float snr_feature;      // (s - 7.5) / 7.5, s = -10 log10(2 sigma2)
-    unsigned long long* acc;  // [kAccSlots][1] fixed-point GMI sum, or null
     uint32_t* bad_tx;
 };
 
