@@ -322,6 +322,10 @@ __device__ float exact_mi_term(const float (&y)[DP], const float* table, int M, 
     return (float)m - ((mx - ttx) + hw_log2(s));
 }
 
+// GMI / MI terms of one recomputed symbol, as they enter sums shared with other symbols: a symbol with
+// a NaN, an infinity or overflowing distances contributes nothing, and the others' terms stay.
+__device__ __forceinline__ double finite_term(double v) { return __builtin_isfinite(v) ? v : 0.0; }
+
 // Recompute the flagged bits of one symbol in one lane; returns the GMI / MI corrections.
 template <int DP, int LS>
 __device__ void fixup_one(const BlockView& b, const Sinks& k, uint32_t n, uint32_t mask, double& gcorr,
@@ -351,7 +355,10 @@ __device__ __forceinline__ void queue_or_fix(const BlockView& b, const Sinks& k,
         k.queue[(size_t)(k.queue_first + blockIdx.x) * k.queue_seg + slot] = FixEntry{n, (uint32_t)b.tag, mask, near};
     } else {
         if (k.fix_pairs) atomicAdd(k.fix_pairs + b.tag, (uint32_t)__popc(mask & 0xFFFFu));
-        fixup_one<DP, LS>(b, k, n, mask, gc, mc);
+        double g1 = 0.0, m1 = 0.0;
+        fixup_one<DP, LS>(b, k, n, mask, g1, m1);
+        gc += finite_term(g1);
+        mc += finite_term(m1);
     }
 }
 

@@ -480,6 +480,7 @@ __device__ void drain_fix_queue(const Sinks& k, ViewFn view, float* tl, int cach
     };
     auto add = [&](int tag, int slot, int which, double v) {
         if (!k.acc) return;
+        v = finite_term(v);
         if (tag < kFixLdsTags) {
             const long long q = __double2ll_rn(v * kFixScale);
             if (q != 0) atomicAdd(&s_acc[tag * 2 + which], (unsigned long long)q);

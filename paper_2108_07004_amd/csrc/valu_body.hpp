@@ -302,7 +302,10 @@ __device__ __forceinline__ void valu_epilogue(const BlockView& b, const Sinks& k
     if constexpr (MC != 0 && MC <= 16) {
         const bool fix = mask != 0u && active;
         if (__builtin_popcountll(__ballot(fix)) >= kInPlaceLanes && fix) {
-            valu_fix_in_place<DP, LS, MC>(b, tab, y, mask, txl, xtx, Lv, gc, mc);
+            double g1 = 0.0, m1 = 0.0;
+            valu_fix_in_place<DP, LS, MC>(b, tab, y, mask, txl, xtx, Lv, g1, m1);
+            gc += finite_term(g1);
+            mc += finite_term(m1);
             pairs += (uint32_t)__popc(mask & 0xFFFFu);
             mask = 0u;
         }
