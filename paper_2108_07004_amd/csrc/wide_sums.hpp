@@ -1,16 +1,16 @@
 // Sums of likelihoods with the exponent range of a double (gfx950), for the fix-up: exponents t in FP32
 // as everywhere, split into n + f with n whole and |f| <= 1/2, and 2^n * 2^f summed as doubles (2^f from
-// v_exp_f32, n added to the exponent field).  The sums hold every term down to 2^-1000, so no maxima
+// v_exp_f32, n added to the exponent field).  The sums hold every term down to 2^-1020, so no maxima
 // are needed and one pass over the points serves all label bits.
 #pragma once
 #include "device_common.hpp"
 
 namespace dm {
 
-// 2^t as a double, t clamped to at least -1000.
+// 2^t as a double, t clamped to at least -1020 (the result is then a normal double).
 __device__ __forceinline__ double wide_exp2(float t) {
     constexpr float kMagic = 12582912.0f;  // 1.5 * 2^23: the sum's low mantissa bits are the nearest whole number
-    t = fmaxf(t, -1000.0f);
+    t = fmaxf(t, -1020.0f);
     const float z = t + kMagic;
     const double e = (double)hw_exp2(t - (z - kMagic));
     const uint64_t u = __builtin_bit_cast(uint64_t, e);
@@ -25,7 +25,9 @@ __device__ __forceinline__ float wide_log2_ratio(double a, double b) {
     return (float)(ea - eb) + (hw_log2(ma) - hw_log2(mb));
 }
 
-// Both sums large enough that no term that matters was clamped, and finite.
+// Both sums finite and large enough that what clamping added does not count: at most 2^13 terms (half of
+// 16384 points) of 2^-1020 each, 2^-27 of a sum of 2^-980.  (With a clamp at -1000 that was 2^-7, and LLRs
+// of some 680 nats were off by up to 4e-3.)
 __device__ __forceinline__ bool wide_ok(double a, double b) {
     return fmin(a, b) >= 0x1p-980 && fmax(a, b) < 0x1p+200;
 }
