@@ -132,7 +132,7 @@ __global__ __launch_bounds__(kThreads, NT == 8 ? 3 : 4) void demap_mfma_small_ke
         mfma_pair_far_pass<T, D, SPLIT, NT>(lds_frag, lane, y, b.c, b.K, bad, b, n, active, txl, near, mask, ge, go);
         if (mask && active) {
             double gc = 0.0, mc = 0.0;
-            queue_or_fix<D, D>(b, k, &s_fill, (uint32_t)n, mask, near, gc, mc);
+            queue_or_fix<D, D, (MB <= 6)>(b, k, &s_fill, (uint32_t)n, mask, near, gc, mc);
             ge += (float)gc;
             mi += (float)mc;
         }

@@ -342,30 +342,4 @@ __device__ void fixup_one(const BlockView& b, const Sinks& k, uint32_t n, uint32
     if ((mask & kMiFlag) && b.tx) mcorr += (double)exact_mi_term<DP, LS>(y, b.table, b.M, b.m, txl, b.c, b.K);
 }
 
-// Queue a symbol for the fix-up (near: FixEntry.near of the symbol) in the workgroup's region, whose
-// fill is counted in LDS at *fill; when the region is full the calling lane recomputes the
-// symbol in place (slow but exact), counts its pairs, and the corrections come back through
-// gc / mc.  Queued pairs are counted by the fix-up when it drains them.  LS: row stride of the block's
-// table.
-template <int DP, int LS>
-__device__ __forceinline__ void queue_or_fix(const BlockView& b, const Sinks& k, uint32_t* fill, uint32_t n,
-                                             uint32_t mask, uint32_t near, double& gc, double& mc) {
-    const uint32_t slot = atomicAdd(fill, 1u);
-    if (slot < k.queue_seg) {
-        k.queue[(size_t)(k.queue_first + blockIdx.x) * k.queue_seg + slot] = FixEntry{n, (uint32_t)b.tag, mask, near};
-    } else {
-        if (k.fix_pairs) atomicAdd(k.fix_pairs + b.tag, (uint32_t)__popc(mask & 0xFFFFu));
-        double g1 = 0.0, m1 = 0.0;
-        fixup_one<DP, LS>(b, k, n, mask, g1, m1);
-        gc += finite_term(g1);
-        mc += finite_term(m1);
-    }
-}
-
-// Store the workgroup's region count; every thread calls it once, after its last queue_or_fix.
-__device__ __forceinline__ void queue_close(const Sinks& k, const uint32_t* fill) {
-    __syncthreads();
-    if (threadIdx.x == 0) k.queue_count[k.queue_first + blockIdx.x] = min(*fill, k.queue_seg);
-}
-
 }  // namespace dm

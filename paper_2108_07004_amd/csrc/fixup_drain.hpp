@@ -1,9 +1,10 @@
 // Draining the fix-up queue (gfx950): the exact recomputation of queued symbols by the fix-up
-// kernels, one lane, one 16-lane row or one wavefront per symbol.  The queue itself, its entries
-// and the in-place path of a full region are in device_common.hpp, which every demapping kernel
-// includes; this file only the fix-up kernels do.
+// kernels, one lane, one 16-lane row or one wavefront per symbol.  The queue's entries are in
+// device_common.hpp, appending to it and the path of a full region in fixup_queue.hpp, which every
+// demapping kernel includes; this file only the fix-up kernels do.
 #pragma once
 #include "device_common.hpp"
+#include "fixup_queue.hpp"
 #include "valu_body.hpp"
 #include "wave_reduce.hpp"
 #include "wide_sums.hpp"
@@ -336,70 +337,28 @@ __device__ void fix_rows(const Sinks& k, ViewFn view, AddFn add, FetchFn fetch, 
     }
 }
 
-// The flagged bits and MI term of one queued symbol in one lane, 16 to 64 points: one pass over the
-// points for all bits, bound by vector issue.  Against two passes per flagged bit (fixup_one): 2^20
-// symbols of 64-QAM at 18 dB 29.2 -> 8.6 us, 4096 of them at 20 dB 29.9 -> 17.5; 8 x 2^20 symbols to 20 dB
-// 51 -> 44; 64 mixed instances of 2^14 .. 2^22 symbols 153 -> 76.  (Below 16 points the few terms are quicker by fixup_one, which also takes the
-// bits whose sums are out of the wide range.)
+// A queued symbol of up to kFixLaneMaxM points in one lane: fewer than 16 points by fixup_one (too few terms
+// to be worth registers), 16 from registers, more in one pass.  (16-QAM, 2^20 symbols at 18 dB, a call with
+// its queue: 20.2 us with 16 points in one pass, 19.9 so.)
 template <int DP, typename Table>
-__device__ __forceinline__ void fixup_lane(const BlockView& b, const Sinks& k, Table tab, uint32_t n, uint32_t mask,
-                                           double& gcorr, double& mcorr) {
-    float y[DP];
-    load_symbol<DP>(y, b.y + (size_t)n * b.D, b.D, true);
-    const int txl = b.tx ? tx_label(b, k, n) : 0;
-    double accA[16], z4 = 0.0, o4 = 0.0, z5 = 0.0, o5 = 0.0;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) accA[r] = 0.0;
-#pragma unroll 1
-    for (int g = 0; g < (b.M >> 4); ++g) {
-        double T = 0.0;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            float x[DP];
-#pragma unroll
-            for (int d = 0; d < DP; ++d) x[d] = tab[(g * 16 + r) * DP + d];
-            const double w = wide_exp2(fmaf(-b.c, sqdist<DP>(y, x), b.K));
-            accA[r] += w;
-            T += w;
-        }
-        if (g & 1) o4 += T;
-        else z4 += T;
-        if (g & 2) o5 += T;
-        else z5 += T;
-    }
-    uint32_t left = 0u;
-    auto finish = [&](int p, double s0, double s1) {
-        if (!((mask >> p) & 1u)) return;
-        if (!wide_ok(s0, s1)) {
-            left |= 1u << p;
+__device__ __forceinline__ void drain_symbol(const BlockView& b, const Sinks& k, Table tab, uint32_t n, uint32_t mask,
+                                             double& gcorr, double& mcorr) {
+    if (b.M >= 16) {
+        float y[DP];
+        load_symbol<DP>(y, b.y + (size_t)n * b.D, b.D, true);
+        const int txl = b.tx ? tx_label(b, k, n) : 0;
+        const float* const xtx = b.table + (size_t)txl * DP;
+        auto put = [&](int p, float L) {
+            if (b.llr) b.llr[(size_t)n * b.m + (b.m - 1 - p)] = L * 0.69314718055994531f;
+        };
+        if (b.M == 16) {
+            two_pass_symbol<DP, DP, 16>(b, tab, y, mask, txl, xtx, put, gcorr, mcorr);
             return;
         }
-        const float L = wide_log2_ratio(s1, s0);
-        if (b.llr) b.llr[(size_t)n * b.m + (b.m - 1 - p)] = L * 0.69314718055994531f;
-        if (b.tx) gcorr += (double)gmi_bit_term(L, (txl >> p) & 1);
-    };
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        double s0 = 0.0, s1 = 0.0;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            if ((r >> p) & 1) s1 += accA[r];
-            else s0 += accA[r];
-        }
-        finish(p, s0, s1);
+        mask = wide_symbol<DP, DP>(b, tab, y, mask, txl, xtx, put, gcorr, mcorr);
+        if (mask == 0u) return;
     }
-    finish(4, z4, o4);
-    finish(5, z5, o5);
-    if ((mask & kMiFlag) && b.tx) {
-        const double all = z4 + o4;
-        if (wide_ok(all, all)) {
-            const float ttx = fmaf(-b.c, sqdist<DP>(y, b.table + (size_t)txl * DP), b.K);
-            mcorr += (double)wide_mi(b.m, all, ttx);
-        } else {
-            left |= kMiFlag;
-        }
-    }
-    if (left) fixup_one<DP, DP>(b, k, n, left, gcorr, mcorr);
+    fixup_one<DP, DP>(b, k, n, mask, gcorr, mcorr);
 }
 
 // Exclusive prefix of the queue regions' fill into s_qpre[0 .. kMaxQueueRegions] (regions past the
@@ -448,14 +407,12 @@ __device__ __forceinline__ size_t queue_index(const Sinks& k, const uint32_t* s_
 }
 
 // Drain the fix-up queue: symbols of constellations with at most kFixLaneMaxM points are
-// recomputed one per lane (fixup_lane, fixup_one: cheaper than wave reductions for so few points), the
+// recomputed one per lane (drain_symbol: cheaper than wave reductions for so few points), the
 // others one per wavefront (fixup_wave).  view(e) gives the block of a queue entry; tl is the
 // wave's LDS slice of cache_pts floats.  Corrections go to the fixed-point accumulators (slot = lane in the lane
 // pass, wave % kAccSlots in the wave pass).  The filled parts of the queue regions are read as
 // one list (entry i lies in the region whose prefix range holds i); every entry's flagged
 // pairs are added to fix_pairs[tag] here.
-constexpr int kFixLaneMaxM = 64;
-
 template <int DP, typename ViewFn>
 __device__ void drain_fix_queue(const Sinks& k, ViewFn view, float* tl, int cache_pts, int uniform_M = 0,
                                 const float* uniform_table = nullptr) {
@@ -505,15 +462,12 @@ __device__ void drain_fix_queue(const Sinks& k, ViewFn view, float* tl, int cach
             const BlockView b = view(e);
             if (b.M <= kFixLaneMaxM) {
                 double gc = 0.0, mc = 0.0;
-                bool done = false;
                 if constexpr (DP <= 8) {
-                    if (b.M >= 16) {
-                        if (uniform_table) fixup_lane<DP>(b, k, (ScalarTable)(uintptr_t)uniform_table, e.n, e.mask, gc, mc);
-                        else fixup_lane<DP>(b, k, as_global(b.table), e.n, e.mask, gc, mc);
-                        done = true;
-                    }
+                    if (uniform_table) drain_symbol<DP>(b, k, (ScalarTable)(uintptr_t)uniform_table, e.n, e.mask, gc, mc);
+                    else drain_symbol<DP>(b, k, as_global(b.table), e.n, e.mask, gc, mc);
+                } else {
+                    fixup_one<DP, DP>(b, k, e.n, e.mask, gc, mc);
                 }
-                if (!done) fixup_one<DP, DP>(b, k, e.n, e.mask, gc, mc);
                 add((int)e.tag, lane, 0, gc);
                 add((int)e.tag, lane, 1, mc);
             }

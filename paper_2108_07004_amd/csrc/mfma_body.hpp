@@ -18,6 +18,7 @@
 // for the accumulation scheme, the underflow flag and the fix-up.
 #pragma once
 #include "device_common.hpp"
+#include "fixup_queue.hpp"
 
 namespace dm {
 
@@ -480,7 +481,9 @@ __device__ __forceinline__ void mfma_finish(const BlockView& b, const Sinks& k, 
     mask = half_or(mask);
     if (mask && active && h == 0) {
         double gc = 0.0, mc = 0.0;
-        queue_or_fix<D, D>(b, k, fill, (uint32_t)n, mask, near_word(stot, m, bad_sym), gc, mc);
+        // (32 and 64 points: known sizes, or, where they have no kernel of their own, any number of bits)
+        constexpr bool kWide = MB <= 6 || (MB == 16 && D != 2 && D != 4 && D != 8);
+        queue_or_fix<D, D, kWide>(b, k, fill, (uint32_t)n, mask, near_word(stot, m, bad_sym), gc, mc);
         g += (float)gc;
         mi += (float)mc;
     }

@@ -25,6 +25,7 @@
 // are.
 #pragma once
 #include "device_common.hpp"
+#include "fixup_queue.hpp"
 
 namespace dm {
 
@@ -182,48 +183,6 @@ __device__ __forceinline__ void valu_accumulate(Table tab, int c0, int cnt, cons
 // and 174 us in the fix-up with the queue alone, 134 and 10 with this.
 constexpr int kInPlaceLanes = 8;
 
-// The exact recomputation of fixup_one for MC <= 16 points, exponents in registers: LLRs of the flagged
-// bits into Lv, GMI / MI terms added to gc, mc.
-template <int DP, int LS, int MC, int MB, typename Table>
-__device__ __forceinline__ void valu_fix_in_place(const BlockView& b, Table tab, const float (&y)[DP], uint32_t mask,
-                                                  int txl, const float* xtx, float (&Lv)[MB], double& gc, double& mc) {
-    float t[MC];
-#pragma unroll
-    for (int j = 0; j < MC; ++j) {
-        float x[DP];
-#pragma unroll
-        for (int d = 0; d < DP; ++d) x[d] = tab[j * LS + d];
-        t[j] = fmaf(-b.c, sqdist<DP>(y, x), b.K);
-    }
-#pragma unroll
-    for (int p = 0; p < MB; ++p) {
-        if (!((mask >> p) & 1u)) continue;
-        float mx0 = -INFINITY, mx1 = -INFINITY, s0 = 0.0f, s1 = 0.0f;
-#pragma unroll
-        for (int j = 0; j < MC; ++j) {
-            if ((j >> p) & 1) mx1 = fmaxf(mx1, t[j]);
-            else mx0 = fmaxf(mx0, t[j]);
-        }
-#pragma unroll
-        for (int j = 0; j < MC; ++j) {
-            if ((j >> p) & 1) s1 += hw_exp2(t[j] - mx1);
-            else s0 += hw_exp2(t[j] - mx0);
-        }
-        const float L = (mx1 - mx0) + (hw_log2(s1) - hw_log2(s0));
-        Lv[p] = L * 0.69314718055994531f;
-        if (b.tx) gc += (double)gmi_bit_term(L, (txl >> p) & 1);
-    }
-    if ((mask & kMiFlag) && b.tx) {
-        float mx = -INFINITY, s = 0.0f;
-#pragma unroll
-        for (int j = 0; j < MC; ++j) mx = fmaxf(mx, t[j]);
-#pragma unroll
-        for (int j = 0; j < MC; ++j) s += hw_exp2(t[j] - mx);
-        const float ttx = fmaf(-b.c, sqdist<DP>(y, xtx), b.K);
-        mc += (double)((float)MB - ((mx - ttx) + hw_log2(s)));
-    }
-}
-
 // Per-bit subset sums -> LLRs, flags, GMI and MI terms of one symbol; queues flagged bits, or (MC <= 16)
 // recomputes them at once, their (symbol, bit) pairs added to pairs and their GMI / MI terms to gc,
 // mc.  txl: the transmitted label (0 without tx); xtx: its point; LS: row stride of tab and b.table.
@@ -303,10 +262,11 @@ __device__ __forceinline__ void valu_epilogue(const BlockView& b, const Sinks& k
         const bool fix = mask != 0u && active;
         if (__builtin_popcountll(__ballot(fix)) >= kInPlaceLanes && fix) {
             double g1 = 0.0, m1 = 0.0;
-            valu_fix_in_place<DP, LS, MC>(b, tab, y, mask, txl, xtx, Lv, g1, m1);
+            pairs += (uint32_t)__popc(mask & 0xFFFFu);
+            two_pass_symbol<DP, LS, MC>(
+                b, tab, y, mask, txl, xtx, [&](int p, float L) { Lv[p] = L * 0.69314718055994531f; }, g1, m1);
             gc += finite_term(g1);
             mc += finite_term(m1);
-            pairs += (uint32_t)__popc(mask & 0xFFFFu);
             mask = 0u;
         }
     }
@@ -315,7 +275,9 @@ __device__ __forceinline__ void valu_epilogue(const BlockView& b, const Sinks& k
 #pragma unroll
             for (int j = 0; j < MB; ++j) out[j] = Lv[MB - 1 - j];
         }
-    if (mask && active) queue_or_fix<DP, LS>(b, k, fill, (uint32_t)n, mask, near_word(stot, m, false), gc, mc);
+    // (sizes that are not known here but at D = 1, 2, 4, 8 have more than 64 points)
+    constexpr bool kWide = DP <= 8 && (MC ? MC >= 32 && MC <= kFixLaneMaxM : DP == 3 || DP > 4 && DP < 8);
+    if (mask && active) queue_or_fix<DP, LS, kWide>(b, k, fill, (uint32_t)n, mask, near_word(stot, m, false), gc, mc);
 }
 
 }  // namespace dm

@@ -1,0 +1,84 @@
+"""A symbol's LLRs are the same bits whatever else is in the call: few or many flagged symbols in its wave,
+few or many in the queue, the queue full or not, at any place of any part of the block.
+"""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import paper_2108_07004_amd as dm
+import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _block(M, D, N, snr_db):
+    import torch
+    const = W.qam(M) if D == 2 else W.gaussian_constellation(M, D, 82, M, D)
+    s2 = float(W.sigma2_from_snr_db(snr_db))
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(1000 * M + D)
+    tx = torch.randint(0, M, (N,), generator=g, device="cuda:0")
+    z = torch.randn((N, D), generator=g, device="cuda:0")
+    y = (torch.from_numpy(const.points).to("cuda:0")[tx] + s2 ** 0.5 * z).contiguous()
+    return const, dm.Constellation(const.points, const.labels), s2, tx.to(torch.int16), y
+
+
+def _parts_equal_whole(M, D, prec, snr_db, N, parts):
+    import torch
+    const, c, s2, _, y = _block(M, D, N, snr_db)
+    whole = dm.demap_llr(c, s2, y, prec=prec)
+    for lo, hi in parts:
+        assert torch.equal(dm.demap_llr(c, s2, y[lo:hi].contiguous(), prec=prec), whole[lo:hi]), (lo, hi)
+    st = dm.Streamer(c, buffer_symbols=N // 7 + 3, n_buffers=2, prec=prec)
+    llr, _ = st.run(s2, y.cpu().numpy())
+    st.close()
+    assert np.array_equal(llr, whole.cpu().numpy())
+
+
+PARTS = [(0, 1), (5, 6), (1, 64), (7, 72), (60, 1061), (1001, 5000), (33, 40001)]
+
+
+@pytest.mark.parametrize("snr_db", [15.0, 17.5, 20.0, 30.0])
+@pytest.mark.parametrize("M,D,prec", [(4, 2, "fp32"), (8, 2, "fp32"), (16, 2, "fp32"), (16, 8, "fp32"), (16, 3, "fp32"),
+                                      (32, 2, "fp32"), (64, 2, "fp32"), (64, 5, "fp32"), (64, 2, "fp16x3"),
+                                      (32, 8, "fp16x3"), (64, 3, "fp16x3")])
+def test_parts_of_a_block(M, D, prec, snr_db):
+    _parts_equal_whole(M, D, prec, snr_db, 60_001, PARTS)
+
+
+@pytest.mark.parametrize("M,D,prec,snr_db", [(32, 2, "fp32", 30.0), (64, 2, "fp32", 30.0), (16, 3, "fp32", 40.0),
+                                             (64, 3, "fp32", 40.0), (64, 3, "fp16x3", 40.0)])
+def test_queue_full(M, D, prec, snr_db):
+    """2^21 symbols, nearly all flagged: all of them fit the queue of the allocating call, half of them that
+    of the allocation-free one."""
+    import torch
+    N = 1 << 21
+    const, c, s2, tx, y = _block(M, D, N, snr_db)
+    a, b, d = (torch.empty((N, const.m), device="cuda:0") for _ in range(3))
+    g0, m0 = dm.gmi_estimate(c, [s2], [y], tx, [a], prec=prec)
+    g1, m1 = dm.gmi_estimate_noalloc(c, [s2], [y], tx, [b], prec=prec)
+    dm.gmi_estimate_noalloc(c, [s2], [y], tx, [d], prec=prec)
+    assert dm.gmi_estimate(c, [s2], [y], tx, [a], prec=prec)[0][0] == g0[0]
+    assert dm.last_fixup_count(1)[0] > (1 << 21)
+    assert torch.equal(a, b) and torch.equal(b, d)
+    assert abs(g0[0] - g1[0]) <= 1e-6 and abs(m0[0] - m1[0]) <= 1e-6
+
+
+@pytest.mark.parametrize("M,prec", [(64, "fp32"), (32, "fp32")])
+def test_plan_with_the_queue_full(M, prec):
+    """Which workgroup takes which symbols of a plan differs from launch to launch, and so does who finds
+    its region full; 2^23 symbols against a queue of 2^22."""
+    import torch
+    N = 1 << 23
+    const, c, s2, tx, y = _block(M, 2, N, 30.0)
+    llr = torch.empty((N, const.m), device="cuda:0")
+    plan = dm.Plan([(c, s2, y, tx, llr)], prec=prec, autotune=False)
+    n = N // 8
+    want = [dm.demap_llr(c, s2, y[i * n:(i + 1) * n], prec=prec) for i in range(8)]
+    for _ in range(3):
+        llr.zero_()
+        plan.launch()
+        plan.results()
+        for i in range(8):
+            assert torch.equal(llr[i * n:(i + 1) * n], want[i]), i
