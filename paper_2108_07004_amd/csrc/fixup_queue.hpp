@@ -119,29 +119,10 @@ __device__ __forceinline__ uint32_t wide_symbol(const BlockView& b, Table tab, c
     return left;
 }
 
-// One bit's sums of wide_symbol, added up in the same order from few registers: the exponentials are formed
-// anew for each bit, but the sixteen running sums would have the demapping kernels spill.
-template <int DP, int LS>
-__device__ __forceinline__ void wide_bit_sums(const BlockView& b, const float (&y)[DP], int p, double& s0, double& s1) {
-    const float* const tab = as_global(b.table);
-    const int groups = b.M >> 4;
-    auto term = [&](int j) { return wide_exp2(fmaf(-b.c, sqdist<DP>(y, tab + (size_t)j * LS), b.K)); };
-    s0 = s1 = 0.0;
-    // bits 0 .. 3: by index within 16 points, then over these; bits 4 and 5: by group of 16, then over groups
-    const int outer = p < 4 ? 16 : groups, inner = p < 4 ? groups : 16;
-    const int so = p < 4 ? 1 : 16, si = p < 4 ? 16 : 1, bit = p < 4 ? p : p - 4;
-#pragma unroll 1
-    for (int o = 0; o < outer; ++o) {
-        double a = 0.0;
-#pragma unroll 1
-        for (int i = 0; i < inner; ++i) a += term(o * so + i * si);
-        if ((o >> bit) & 1) s1 += a;
-        else s0 += a;
-    }
-}
-
 // The flagged bits and MI term of one symbol in one lane, for the symbols that find their region full.
-// WIDE: the table may have 32 or 64 points (and D <= 8); their results are those of wide_symbol.
+// WIDE: the table may have 32 or 64 points (and D <= 8).  Their results are those of wide_symbol, the same
+// numbers added in the same order, but in two walks over the points, which need half of its
+// registers: with the sixteen running sums the demapping kernels would spill.
 template <int DP, int LS, bool WIDE>
 __device__ void fixup_in_place(const BlockView& b, const Sinks& k, uint32_t n, uint32_t mask, double& gcorr,
                                double& mcorr) {
@@ -149,24 +130,50 @@ __device__ void fixup_in_place(const BlockView& b, const Sinks& k, uint32_t n, u
         if (b.M == 32 || b.M == 64) {
             float y[DP];
             load_symbol<DP>(y, b.y + (size_t)n * b.D, b.D, true);
-            const int txl = b.tx ? tx_label(b, k, n) : 0;
+            const int txl = b.tx ? tx_label(b, k, n) : 0, groups = b.M >> 4;
+            const float* const tab = as_global(b.table);
+            auto term = [&](int j) { return wide_exp2(fmaf(-b.c, sqdist<DP>(y, tab + (size_t)j * LS), b.K)); };
             uint32_t left = 0u;
-#pragma unroll 1
-            for (int p = 0; p <= b.m; ++p) {  // p == m: the MI term
-                const bool mi = p == b.m;
-                if (mi ? !((mask & kMiFlag) && b.tx) : !((mask >> p) & 1u)) continue;
-                double s0, s1;
-                wide_bit_sums<DP, LS>(b, y, mi ? 4 : p, s0, s1);
-                if (mi) s0 = s1 = s0 + s1;
+            auto finish = [&](int p, double s0, double s1) {
+                if (!((mask >> p) & 1u)) return;
                 if (!wide_ok(s0, s1)) {
-                    left |= mi ? kMiFlag : 1u << p;
-                } else if (mi) {
-                    const float ttx = fmaf(-b.c, sqdist<DP>(y, b.table + (size_t)txl * LS), b.K);
-                    mcorr += (double)wide_mi(b.m, s0, ttx);
-                } else {
-                    const float L = wide_log2_ratio(s1, s0);
-                    if (b.llr) b.llr[(size_t)n * b.m + (b.m - 1 - p)] = L * 0.69314718055994531f;
-                    if (b.tx) gcorr += (double)gmi_bit_term(L, (txl >> p) & 1);
+                    left |= 1u << p;
+                    return;
+                }
+                const float L = wide_log2_ratio(s1, s0);
+                if (b.llr) b.llr[(size_t)n * b.m + (b.m - 1 - p)] = L * 0.69314718055994531f;
+                if (b.tx) gcorr += (double)gmi_bit_term(L, (txl >> p) & 1);
+            };
+            // half 0: bits 0 .. 3, by index within 16 points; half 1: bits 4 and 5, by group of 16
+#pragma unroll 1
+            for (int half = 0; half < 2; ++half) {
+                const int outer = half ? groups : 16, inner = half ? 16 : groups, so = half ? 16 : 1, si = half ? 1 : 16;
+                double s0[4], s1[4];
+#pragma unroll
+                for (int p = 0; p < 4; ++p) s0[p] = s1[p] = 0.0;
+#pragma unroll 1
+                for (int o = 0; o < outer; ++o) {
+                    double a = 0.0;
+#pragma unroll 2
+                    for (int i = 0; i < inner; ++i) a += term(o * so + i * si);
+#pragma unroll
+                    for (int p = 0; p < 4; ++p) {
+                        const bool one = (o >> p) & 1;
+                        s1[p] += one ? a : 0.0;
+                        s0[p] += one ? 0.0 : a;
+                    }
+                }
+#pragma unroll
+                for (int p = 0; p < 4; ++p)
+                    if (!half || p < 2) finish(4 * half + p, s0[p], s1[p]);
+                if (half && (mask & kMiFlag) && b.tx) {
+                    const double all = s0[0] + s1[0];
+                    if (wide_ok(all, all)) {
+                        const float ttx = fmaf(-b.c, sqdist<DP>(y, b.table + (size_t)txl * LS), b.K);
+                        mcorr += (double)wide_mi(b.m, all, ttx);
+                    } else {
+                        left |= kMiFlag;
+                    }
                 }
             }
             if (left == 0u) return;
@@ -185,7 +192,7 @@ template <int DP, int LS, bool WIDE>
 __device__ __forceinline__ void queue_or_fix(const BlockView& b, const Sinks& k, uint32_t* fill, uint32_t n,
                                              uint32_t mask, uint32_t near, double& gc, double& mc) {
     const uint32_t slot = atomicAdd(fill, 1u);
-    if (slot < k.queue_seg) {
+    if (__builtin_expect(slot < k.queue_seg, 1)) {
         k.queue[(size_t)(k.queue_first + blockIdx.x) * k.queue_seg + slot] = FixEntry{n, (uint32_t)b.tag, mask, near};
     } else {
         if (k.fix_pairs) atomicAdd(k.fix_pairs + b.tag, (uint32_t)__popc(mask & 0xFFFFu));
