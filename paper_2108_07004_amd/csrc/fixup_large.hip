@@ -3,11 +3,10 @@
 //
 // At high SNR (8D formats beyond 15 dB) nearly every symbol has bits whose far subset underflowed, and
 // the recomputation takes longer than the demapping.  With one wavefront per symbol every symbol reads
-// the whole table (64 KiB at 2048 points of 8D) from L2, and every flagged bit passes over all exponents
-// twice.  Here 64 symbols share each point read (from LDS, broadcast), and one pass serves all bits:
-// (wide_sums.hpp: FP32 exponents, sums with the exponent range of a double).  The sums are taken
-// over indexed accumulators as in valu_body.hpp: two FP64 additions per point.  A sum below 2^-980 (or
-// not finite) sends that bit to the wavefront form (fixup_wave).
+// the whole table (64 KiB at 2048 points of 8D) from L2.  Here 64 symbols share each point read (from LDS,
+// broadcast), and one pass serves all bits (wide_sums.hpp: FP32 exponents, sums with the exponent range
+// of a double).  The sums are taken over indexed accumulators as in valu_body.hpp: two FP64 additions
+// per point.  A sum below 2^-1860 sends that bit to the two-pass form (fixup_wave).
 //
 // A workgroup is four groups of four waves.  A group takes 64 queued symbols; wave q of it walks the
 // points with top label bits q (a quarter of the table), which are then no sums of its own but its
@@ -19,12 +18,14 @@
 // call: 21.2 -> 1.5 ms.
 //
 // A lane takes its quarter of the table point by point, some 80 us at 2048 points of 8D however few
-// symbols there are, so up to 24 symbols per CU go by wavefronts: 4096 symbols 57 us, 6144 70 us (112
-// and 117 before the point loads of fixup_wave were issued four at a time), 8192 symbols 80 us by lanes
-// (166 by wavefronts).
+// symbols there are, so few symbols go by wavefronts: row q of the wave takes quarter q, lane r of
+// it the points of index r modulo 16.  Both forms add the same numbers in the same order (sixteen points
+// by a pairwise tree, which is what the lanes of a row can do), so a symbol's results do not depend on
+// how many are queued with it.
 #include "device_common.hpp"
 #include "fixup_drain.hpp"
 #include "kernels.hpp"
+#include "wave_reduce.hpp"
 #include "wide_sums.hpp"
 
 namespace dm {
@@ -40,6 +41,120 @@ constexpr int kXchg = kGroups * 4 * 2 * kRound * 64;  // doubles
 constexpr int kTot = kGroups * 4 * 64;
 constexpr size_t kLdsBytes = (size_t)kTabFloats * 4 + (size_t)(kXchg + kTot) * 8;
 static_assert(kLdsBytes >= (size_t)(kThreads / 64) * kFixCached * 4, "the wavefront form's exponent caches");
+
+// Sum of v over the 16 lanes of each row, every lane receiving it: pairs, pairs of pairs, ..
+__device__ __forceinline__ double row_tree(double v) {
+    v += dpp_d<0xB1>(v);   // quad_perm [1,0,3,2]
+    v += dpp_d<0x4E>(v);   // quad_perm [2,3,0,1]
+    v += dpp_d<0x141>(v);  // row_half_mirror (the quads are uniform)
+    v += dpp_d<0x140>(v);  // row_mirror
+    return v;
+}
+
+// The same tree over the values f(0) .. f(15) of one lane.
+template <int N, int R = 0, typename Fn>
+__device__ __forceinline__ double lane_tree(Fn&& f) {
+    if constexpr (N == 1) {
+        return f(R);
+    } else {
+        const double a = lane_tree<N / 2, R>(f);
+        const double b = lane_tree<N / 2, R + N / 2>(f);
+        return a + b;
+    }
+}
+
+// Value v of lane src, uniform.
+__device__ __forceinline__ double read_lane(double v, int src) {
+    const uint64_t u = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, src);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), src);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// One queued symbol by a whole wavefront (all lanes active).  Returns the mask of what is out of range here;
+// gcorr, mcorr: the corrections, in every lane.
+template <int DP>
+__device__ uint32_t wide_wave(const BlockView& b, const Sinks& k, uint32_t n, uint32_t mask, double& gcorr,
+                              double& mcorr) {
+    const int lane = threadIdx.x & 63, r = lane & 15, q = lane >> 4;
+    const int M = b.M, m = b.m, ml = m - 2;
+    float y[DP];
+    load_symbol<DP>(y, b.y + (size_t)n * b.D, b.D, true);
+    const int txl = b.tx ? tx_label(b, k, n) : 0;
+    const float* const pts = b.table + ((size_t)q * (M >> 2) + r) * DP;
+    double acc = 0.0, accB[4], h0[kHighBits], h1[kHighBits], tot = 0.0;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) accB[g] = 0.0;
+#pragma unroll
+    for (int p = 0; p < kHighBits; ++p) h0[p] = h1[p] = 0.0;
+#pragma unroll 1
+    for (int blk = 0; blk < (M >> 8); ++blk) {
+        double bt = 0.0;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const double w = wide_exp2(fmaf(-b.c, sqdist<DP>(y, pts + (size_t)(blk * 64 + g * 16) * DP), b.K));
+            acc += w;
+            const double T = row_tree(w);
+            accB[g] += T;
+            bt += T;
+        }
+        tot += bt;
+#pragma unroll
+        for (int p = 0; p < kHighBits; ++p) {
+            if ((blk >> p) & 1) h1[p] += bt;
+            else h0[p] += bt;
+        }
+    }
+    uint32_t left = 0u;
+    auto finish = [&](int p, double s0, double s1) {
+        if (!wide_ok(s0, s1)) {
+            left |= 1u << p;
+            return;
+        }
+        const float L = wide_log2_ratio(s1, s0);
+        if (b.llr && lane == 0) b.llr[(size_t)n * m + (m - 1 - p)] = L * 0.69314718055994531f;
+        if (b.tx) gcorr += (double)gmi_bit_term(L, (txl >> p) & 1);
+    };
+#pragma unroll
+    for (int p = 0; p < 6 + kHighBits; ++p) {
+        if (p >= ml || !((mask >> p) & 1u)) continue;  // uniform
+        double s0 = 0.0, s1 = 0.0;
+        if (p < 4) {
+            const bool one = (r >> p) & 1;
+            s0 = row_tree(one ? 0.0 : acc);
+            s1 = row_tree(one ? acc : 0.0);
+        } else if (p < 6) {
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                if ((g >> (p - 4)) & 1) s1 += accB[g];
+                else s0 += accB[g];
+            }
+        } else {
+            s0 = h0[p - 6];
+            s1 = h1[p - 6];
+        }
+        double t0 = 0.0, t1 = 0.0;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            t0 += read_lane(s0, 16 * w);
+            t1 += read_lane(s1, 16 * w);
+        }
+        finish(p, t0, t1);
+    }
+    const double t0 = read_lane(tot, 0), t1 = read_lane(tot, 16), t2 = read_lane(tot, 32), t3 = read_lane(tot, 48);
+    if ((mask >> (m - 2)) & 1u) finish(m - 2, t0 + t2, t1 + t3);
+    if ((mask >> (m - 1)) & 1u) finish(m - 1, t0 + t1, t2 + t3);
+    if ((mask & kMiFlag) && b.tx) {
+        const double all = (t0 + t1) + (t2 + t3);
+        if (wide_ok(all, all)) {
+            const float ttx = fmaf(-b.c, sqdist<DP>(y, b.table + (size_t)txl * DP), b.K);
+            mcorr += (double)wide_mi(m, all, ttx);
+        } else {
+            left |= kMiFlag;
+        }
+    }
+    return left;
+}
 
 template <int DP>
 __global__ __launch_bounds__(kThreads) void fixup_large_kernel(const LaunchArgs a, uint32_t lanes_from) {
@@ -66,9 +181,15 @@ __global__ __launch_bounds__(kThreads) void fixup_large_kernel(const LaunchArgs 
         // few symbols: a wavefront each
         const uint32_t waves = gridDim.x * (kThreads / 64);
         for (uint32_t i = wv * gridDim.x + blockIdx.x; i < count; i += waves) {
-            const FixEntry e = k.queue[queue_index(k, s_qpre, i)];
+            const FixEntry e = uniform_copy(k.queue[queue_index(k, s_qpre, i)]);
             double gc = 0.0, mc = 0.0;
-            fixup_wave<DP>(view(e), k, e.n, e.mask, dyn + wv * kFixCached, kFixCached, gc, mc);
+            const uint32_t left = wide_wave<DP>(view(e), k, e.n, e.mask, gc, mc);
+            if (lane == 0) {
+                add(e.tag, 0, gc);
+                add(e.tag, 1, mc);
+            }
+            gc = mc = 0.0;
+            if (left) fixup_wave<DP>(view(e), k, e.n, left, dyn + wv * kFixCached, kFixCached, gc, mc);
             if (lane == 0) {
                 count_pairs(e);
                 add(e.tag, 0, gc);
@@ -111,14 +232,12 @@ __global__ __launch_bounds__(kThreads) void fixup_large_kernel(const LaunchArgs 
                 double bt = 0.0;
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
-                    double T = 0.0;
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
+                    double T = lane_tree<16>([&](int r) {
                         const float t = fmaf(-b.c, sqdist<DP>(y, pts + (size_t)(blk * 64 + g * 16 + r) * DP), b.K);
                         const double w = wide_exp2(t);
                         accA[r] += w;
-                        T += w;
-                    }
+                        return w;
+                    });
                     asm volatile("" : "+v"(T)::"memory");  // the next group's points are read here, not before
                     accB[g] += T;
                     bt += T;
@@ -152,12 +271,10 @@ __global__ __launch_bounds__(kThreads) void fixup_large_kernel(const LaunchArgs 
                 for (int j = 0; j < kRound; ++j) {
                     const int p = p0 + j;
                     double s0 = 0.0, s1 = 0.0;
-                    if (p < 4) {
-#pragma unroll
-                        for (int r = 0; r < 16; ++r) {
-                            if ((r >> p) & 1) s1 += accA[r];
-                            else s0 += accA[r];
-                        }
+                    if (p < 4) {  // the eight registers of each side
+                        const int low = (1 << p) - 1;
+                        s0 = lane_tree<8>([&](int i) { return accA[((i & ~low) << 1) | (i & low)]; });
+                        s1 = lane_tree<8>([&](int i) { return accA[((i & ~low) << 1) | (i & low) | (1 << p)]; });
                     } else if (p < 6) {
 #pragma unroll
                         for (int r = 0; r < 4; ++r) {
@@ -233,6 +350,8 @@ hipError_t launch_t(const LaunchArgs& a, int cus, hipStream_t st) {
     if (e != hipSuccess) return e;
     const int64_t most = (a.N * a.n_snr + kThreads / 64 - 1) / (kThreads / 64);  // a wave per symbol
     const int grid = (int)std::min<int64_t>(cus, most);
+    // Up to 24 queued symbols per CU by wavefronts: 2048 points of 8D at 21 dB, a whole call of 4096 symbols
+    // 57 us, of 6000 61 us; by lanes 8192 symbols 63 us, and no less for fewer.
     hipLaunchKernelGGL(fixup_large_kernel<DP>, dim3(grid), dim3(kThreads), kLdsBytes, st, a, (uint32_t)(24 * cus));
     return hipGetLastError();
 }

@@ -1,16 +1,20 @@
 // Sums of likelihoods with the exponent range of a double (gfx950), for the fix-up: exponents t in FP32
 // as everywhere, split into n + f with n whole and |f| <= 1/2, and 2^n * 2^f summed as doubles (2^f from
-// v_exp_f32, n added to the exponent field).  The sums hold every term down to 2^-1020, so no maxima
-// are needed and one pass over the points serves all label bits.
+// v_exp_f32, n added to the exponent field).  Terms are at most 2^123 and so are their sums, so the
+// doubles are 2^kWideShift times the sums: they hold every term down to 2^-1900, no maxima are
+// needed and one pass over the points serves all label bits.
 #pragma once
 #include "device_common.hpp"
 
 namespace dm {
 
-// 2^t as a double, t clamped to at least -1020 (the result is then a normal double).
+constexpr int kWideShift = 880;
+
+// 2^(t + kWideShift) as a double, t clamped to at least -1900 (the result is then a normal double).
 __device__ __forceinline__ double wide_exp2(float t) {
-    constexpr float kMagic = 12582912.0f;  // 1.5 * 2^23: the sum's low mantissa bits are the nearest whole number
-    t = fmaxf(t, -1020.0f);
+    // 1.5 * 2^23: the sum's low mantissa bits are the nearest whole number, here with the shift added
+    constexpr float kMagic = 12582912.0f + (float)kWideShift;
+    t = fmaxf(t, -1900.0f);
     const float z = t + kMagic;
     const double e = (double)hw_exp2(t - (z - kMagic));
     const uint64_t u = __builtin_bit_cast(uint64_t, e);
@@ -25,16 +29,17 @@ __device__ __forceinline__ float wide_log2_ratio(double a, double b) {
     return (float)(ea - eb) + (hw_log2(ma) - hw_log2(mb));
 }
 
-// Both sums finite and large enough that what clamping added does not count: at most 2^13 terms (half of
-// 16384 points) of 2^-1020 each, 2^-27 of a sum of 2^-980.  (With a clamp at -1000 that was 2^-7, and LLRs
-// of some 680 nats were off by up to 4e-3.)
+// Both sums (of terms down to 2^-1900) finite and at least 2^-1860: what clamping added, at most 2^13 terms
+// (half of 16384 points) of 2^-1900 each, is then below 2^-26 of them.  (With sums accepted down
+// to 2^20 times the clamp, LLRs at that end were off by up to 4e-3.)
 __device__ __forceinline__ bool wide_ok(double a, double b) {
-    return fmin(a, b) >= 0x1p-980 && fmax(a, b) < 0x1p+200;
+    return fmin(a, b) >= 0x1p-980 && fmax(a, b) < 0x1p+1020;
 }
+static_assert(kWideShift - 1860 == -980, "wide_ok's bound");
 
 // MI term of a symbol with m label bits: the sum over all points and the transmitted point's exponent.
 __device__ __forceinline__ float wide_mi(int m, double all, float ttx) {
-    const int e = __builtin_amdgcn_frexp_exp(all);
+    const int e = __builtin_amdgcn_frexp_exp(all) - kWideShift;
     return ((float)(m - e) + ttx) - hw_log2((float)__builtin_amdgcn_frexp_mant(all));
 }
 

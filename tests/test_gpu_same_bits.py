@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 
 def _block(M, D, N, snr_db):
     import torch
-    const = W.qam(M) if D == 2 else W.gaussian_constellation(M, D, 82, M, D)
+    const = W.qam(M) if D == 2 and M <= 256 else W.gaussian_constellation(M, D, 82, M, D)
     s2 = float(W.sigma2_from_snr_db(snr_db))
     g = torch.Generator(device="cuda:0")
     g.manual_seed(1000 * M + D)
@@ -45,6 +45,14 @@ PARTS = [(0, 1), (5, 6), (1, 64), (7, 72), (60, 1061), (1001, 5000), (33, 40001)
                                       (32, 8, "fp16x3"), (64, 3, "fp16x3")])
 def test_parts_of_a_block(M, D, prec, snr_db):
     _parts_equal_whole(M, D, prec, snr_db, 60_001, PARTS)
+
+
+@pytest.mark.parametrize("snr_db", [22.0, 30.0, 40.0])
+@pytest.mark.parametrize("M,D,prec", [(512, 1, "fp32"), (512, 8, "fp16x3"), (1024, 4, "fp32"), (2048, 3, "fp32"),
+                                      (2048, 8, "fp32"), (2048, 8, "fp16x3"), (8192, 2, "fp32"), (16384, 1, "fp32")])
+def test_parts_of_a_block_large_tables(M, D, prec, snr_db):
+    """512 points and more: the whole block queues more symbols than go by wavefronts, its parts fewer."""
+    _parts_equal_whole(M, D, prec, snr_db, 11_001, [(0, 1), (7, 72), (1001, 3000), (33, 7001)])
 
 
 @pytest.mark.parametrize("M,D,prec,snr_db", [(32, 2, "fp32", 30.0), (64, 2, "fp32", 30.0), (16, 3, "fp32", 40.0),
