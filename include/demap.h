@@ -95,7 +95,13 @@ int dm_demap_llr(const dm_constellation* c, double sigma2, const float* y, int64
  *   gmi     HOST, n_snr FP64 outputs (bits per symbol; NaN when N == 0).
  *   mi      HOST, n_snr FP64 outputs or NULL.
  * Synchronises `stream` before returning.  The result is bit-reproducible for a
- * given input and precision (fixed-point accumulation across the grid).
+ * given input and precision (fixed-point accumulation across the grid), and a symbol's LLRs are
+ * the same bits whatever else is in the call, dm_demap_llr and the streamer included.
+ *   Limit: flagged symbols wait in a queue of at most 2^22 entries that each launch (up to 32
+ * noise levels) shares out to its workgroups; up to 3.6e6 symbols per launch always fit.  Beyond
+ * that, a symbol that finds its share full is recomputed in place, as exactly.  Which symbols
+ * these are may differ from run to run, and with them GMI and MI by about 1e-8 and, with
+ * M >= 128, the last bits of their LLRs (up to 64 points the arithmetic is the same).
  * Errors: DM_EINVAL, DM_EUNSUPPORTED, DM_EHIP, DM_ENOMEM.
  */
 int dm_gmi_estimate(const dm_constellation* c, int n_snr, const double* sigma2,
@@ -106,8 +112,9 @@ int dm_gmi_estimate(const dm_constellation* c, int n_snr, const double* sigma2,
  * dm_gmi_estimate without any device allocation, for callers that cannot allocate: code
  * under stream capture, tight serving loops, harnesses that forbid hipMalloc.  Same
  * arguments, kernels and results (LLRs bit-identical, GMI / MI from the same fixed-point
- * sums); the launch's scratch (GMI / MI slots, fix-up counts, a fix-up queue of 2^20
- * symbols, about 16 MiB in all) is one static device array that each GPU the library runs on
+ * sums; with the limit above, here for a queue of 2^20 entries, which 5e5 symbols over all
+ * noise levels always fit); the launch's scratch (GMI / MI slots, fix-up counts, the queue,
+ * about 16 MiB in all) is one static device array that each GPU the library runs on
  * holds until the process ends.  No hipMalloc, hipFree or allocating library call is made:
  * the constellation's MFMA operand tables are built by dm_constellation_create.
  *   Limits: n_snr <= 32 (DM_EINVAL beyond: the array holds 32 noise levels); any N < 2^31
