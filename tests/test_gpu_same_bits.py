@@ -42,7 +42,7 @@ PARTS = [(0, 1), (5, 6), (1, 64), (7, 72), (60, 1061), (1001, 5000), (33, 40001)
 @pytest.mark.parametrize("snr_db", [15.0, 17.5, 20.0, 30.0])
 @pytest.mark.parametrize("M,D,prec", [(4, 2, "fp32"), (8, 2, "fp32"), (16, 2, "fp32"), (16, 8, "fp32"), (16, 3, "fp32"),
                                       (32, 2, "fp32"), (64, 2, "fp32"), (64, 5, "fp32"), (64, 2, "fp16x3"),
-                                      (32, 8, "fp16x3"), (64, 3, "fp16x3")])
+                                      (32, 8, "fp16x3"), (64, 3, "fp16x3"), (128, 2, "fp32"), (256, 2, "fp16x3")])
 def test_parts_of_a_block(M, D, prec, snr_db):
     _parts_equal_whole(M, D, prec, snr_db, 60_001, PARTS)
 
