@@ -5,6 +5,8 @@
 // points of 8 coordinates, as one body for all shapes had to, made an 8-QAM symbol five times as long
 // (the shaping search's launches of 2^21 symbols: 72 us, now 33).  Sixty-four mixed instances of
 // 2^14 .. 2^22 symbols: 7.8 ms in one kernel for all bodies, 5.0 + 1.3 + 0.2 ms in three.
+// The twenty-one bodies' loop invariants do not all fit the scalar registers: 25 of the 128 vector registers
+// spill, outside the point loops.
 #include "device_common.hpp"
 #include "kernels.hpp"
 #include "valu_body.hpp"

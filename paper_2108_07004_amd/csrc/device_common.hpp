@@ -164,10 +164,11 @@ __device__ __forceinline__ V uniform_copy(const V& src) {
 }
 
 // A pointer read from memory is generic to the compiler; this says that it is global (plain global
-// loads and stores instead of flat ones, which also wait for the LDS).
+// loads and stores instead of flat ones, which also wait for the LDS).  Through an integer: the compiler
+// drops a cast to the global address space and back as a pair that changes nothing.
 template <typename T>
 __device__ __forceinline__ T* as_global(T* p) {
-    return (T*)(__attribute__((address_space(1))) T*)p;
+    return (T*)(__attribute__((address_space(1))) T*)(uintptr_t)p;
 }
 
 // Wave-uniform copy of an instance's descriptor.

@@ -24,6 +24,8 @@
 // read through the scalar cache instead, into scalar registers that the subtractions take as they
 // are.
 #pragma once
+#include <type_traits>
+
 #include "device_common.hpp"
 #include "fixup_queue.hpp"
 
@@ -57,8 +59,9 @@ struct ValuHigh {
 };
 
 // Where the points are read from: LDS (16-byte aligned, all lanes the same address: broadcast), or the
-// table itself in constant address space (scalar loads).
-typedef const float* LdsTable;
+// table itself in constant address space (scalar loads).  Both say so in their type: a generic pointer
+// that passes an asm statement is read with flat loads.
+typedef const __attribute__((address_space(3))) float* LdsTable;
 typedef const __attribute__((address_space(4))) float* ScalarTable;
 
 // G points of the label-ordered table (row stride LS), read as wide as the stride allows.
@@ -72,7 +75,7 @@ struct ValuPoints {
         for (int g = 0; g < G; ++g)
 #pragma unroll
             for (int d = 0; d < DP; d += W) {
-                const vec v = *reinterpret_cast<const vec*>(p + g * LS + d);
+                const vec v = *(const __attribute__((address_space(3))) vec*)(p + g * LS + d);
                 if constexpr (W == 1) x[g][d] = v[0];
                 else
 #pragma unroll
@@ -125,7 +128,7 @@ __device__ __forceinline__ void valu_accumulate(Table tab, int c0, int cnt, cons
                 // read 16 points at a time (the compiler would otherwise hoist every read out of
                 // the symbol loop, or to its top, and spill).
                 Table t = tab + (blk * 64 + q * 16) * LS;
-                if constexpr (MC * DP > 32 && sizeof(Table) == 8) asm volatile("" : "+s"(t));
+                if constexpr (MC * DP > 32 && std::is_same<Table, ScalarTable>::value) asm volatile("" : "+s"(t));
                 float e[R], T = 0.0f;
                 valu_terms<DP, LS, R>(t, y, c, K, e);
 #pragma unroll
