@@ -5,12 +5,15 @@
 // the most costly instance first (sub per instance, from the plan's shape choice), one list per
 // kernel.  Workgroups claim fixed chunks of `grab` consecutive items from a counter
 // (dynamic balance: the cheap items at the end fill the tail) and restage their LDS table only
-// when the next item belongs to another instance.  GMI / MI partial sums are flushed per chunk
+// when the next item belongs to another instance.  They ask when the last claim is done: a claim ahead,
+// the first workgroups hold two of the last claims and others none (as many claims as workgroups, 2^20
+// symbols of 8D with 2048 points in FP32: 2046 us ahead, 960 so; 2^19 on MFMA 305 and 168), and
+// asking while a claim for each is left gains 0 to 6% on long lists but costs registers that spill.  GMI / MI partial sums are flushed per chunk
 // and instance, so every fixed-point contribution covers a fixed set of symbols whichever
 // workgroup runs it: the totals are bit-reproducible.  One wave takes 32 symbols, a block 512 per
 // tile.  The instances of 32 .. 256 points (the compile-time tile loop of mfma_small.hpp) and those of
 // more points have a kernel each: in one kernel with the FP32 body their registers spilled (46 of 128
-// per lane).  Batched tables use a row stride of 8 (D <= 8 zero-padded): the padded coordinates
+// per lane; now 15 in the larger points' kernel).  Batched tables use a row stride of 8 (D <= 8 zero-padded): the padded coordinates
 // contribute exact zeros, and the MFMA operand vectors of every instance have the same K layout.
 #include "device_common.hpp"
 #include "fixup_drain.hpp"
@@ -47,20 +50,17 @@ __global__ __launch_bounds__(kThreads) void demap_batched_kernel(const BatchArgs
     const int wave = tid >> 6;
     const int wave_slot = (blockIdx.x * kWaves + wave) % kAccSlots;  // integer slots: any spread sums alike
     const Sinks& k = a.sinks;
-    __shared__ int s_claim[2];   // this claim and the next, which is requested a claim ahead
+    __shared__ int s_claim;      // first item of this claim
     __shared__ uint32_t s_fill;  // entries in this block's fix-up queue region
-    if (tid == 0) {
-        s_fill = 0u;
-        s_claim[0] = (int)atomicAdd(a.next, (uint32_t)a.grab);
-    }
-    __syncthreads();
+    if (tid == 0) s_fill = 0u;
     int staged = -1;
-    for (int at = 0;; at ^= 1) {
-        const int i0 = __builtin_amdgcn_readfirstlane(s_claim[at]);
+    for (;;) {
+        // (asked for when the last claim is done, see the file's head)
+        if (tid == 0) s_claim = (int)atomicAdd(a.next, (uint32_t)a.grab);
+        __syncthreads();
+        const int i0 = __builtin_amdgcn_readfirstlane(s_claim);
         if (i0 >= a.n_items) break;
         const int i1 = min(i0 + a.grab, a.n_items);
-        int next = 0;
-        if (tid == 0) next = (int)atomicAdd(a.next, (uint32_t)a.grab);
         for (int i = i0; i < i1;) {
             // a run of items of one instance: its symbol tiles one after the other, GMI / MI terms
             // summed per lane, then over the wave once
@@ -141,8 +141,7 @@ __global__ __launch_bounds__(kThreads) void demap_batched_kernel(const BatchArgs
                 }
             }
         }
-        if (tid == 0) s_claim[at ^ 1] = next;
-        __syncthreads();
+        __syncthreads();  // the claim is read before the next overwrites it
     }
     queue_close(k, &s_fill);
 }

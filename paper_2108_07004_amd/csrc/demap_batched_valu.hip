@@ -5,7 +5,7 @@
 // points of 8 coordinates, as one body for all shapes had to, made an 8-QAM symbol five times as long
 // (the shaping search's launches of 2^21 symbols: 72 us, now 33).  Sixty-four mixed instances of
 // 2^14 .. 2^22 symbols: 7.8 ms in one kernel for all bodies, 5.0 + 1.3 + 0.2 ms in three.
-// The twenty-one bodies' loop invariants do not all fit the scalar registers: 25 of the 128 vector registers
+// The twenty-one bodies' loop invariants do not all fit the scalar registers: 23 of the 128 vector registers
 // spill, outside the point loops.
 #include "device_common.hpp"
 #include "kernels.hpp"
@@ -86,24 +86,21 @@ __device__ __forceinline__ void valu_item_m(const float* lds, const BlockView& b
 
 __global__ __launch_bounds__(kThreads) void demap_batched_valu_kernel(const BatchArgs a) {
     extern __shared__ __align__(16) float lds[];
-    __shared__ int s_claim[2];   // this claim and the next, which is requested a claim ahead
+    __shared__ int s_claim;      // first item of this claim
     __shared__ uint32_t s_fill;  // entries in this block's fix-up queue region
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave_slot = (blockIdx.x * (kThreads / 64) + (tid >> 6)) % kAccSlots;
     const Sinks& k = a.sinks;
-    if (tid == 0) {
-        s_fill = 0u;
-        s_claim[0] = (int)atomicAdd(a.next, (uint32_t)a.grab);
-    }
-    __syncthreads();
+    if (tid == 0) s_fill = 0u;
     int staged = -1;
-    for (int at = 0;; at ^= 1) {
-        const int i0 = __builtin_amdgcn_readfirstlane(s_claim[at]);
+    for (;;) {
+        // (asked for when the last claim is done, see demap_batched.hip)
+        if (tid == 0) s_claim = (int)atomicAdd(a.next, (uint32_t)a.grab);
+        __syncthreads();
+        const int i0 = __builtin_amdgcn_readfirstlane(s_claim);
         if (i0 >= a.n_items) break;
         const int i1 = min(i0 + a.grab, a.n_items);
-        int next = 0;
-        if (tid == 0) next = (int)atomicAdd(a.next, (uint32_t)a.grab);
         for (int i = i0; i < i1;) {
             // a run of items of one instance, GMI / MI terms summed per lane, then over the wave once
             const WorkItem it = uniform_copy(a.items[i]);
@@ -135,8 +132,7 @@ __global__ __launch_bounds__(kThreads) void demap_batched_valu_kernel(const Batc
                 }
             }
         }
-        if (tid == 0) s_claim[at ^ 1] = next;
-        __syncthreads();
+        __syncthreads();  // the claim is read before the next overwrites it
     }
     queue_close(k, &s_fill);
 }
