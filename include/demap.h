@@ -141,8 +141,9 @@ int dm_gmi_estimate_noalloc(const dm_constellation* c, int n_snr, const double* 
  * MFMA), and workgroups claim 1, 2, 4 or 8 work items at a time.  With DM_PLAN_AUTOTUNE the
  * body and item size are chosen per class by timing every pair on a probe block that fills
  * the GPU (results cached per GPU arch in the file named by the environment variable
- * DM_AUTOTUNE_CACHE, if set) and the claim size by timing the whole plan at each; otherwise a
- * fixed rule (MFMA where it applies, one tile per item, claims of 4).  DM_PLAN_FORCE_VALU /
+ * DM_AUTOTUNE_CACHE, if set), then the whole plan is timed at each claim size, in that shape and
+ * in the fixed one, and the fastest is kept; otherwise the fixed shape (MFMA where it applies,
+ * one tile per item) with claims of 4.  DM_PLAN_FORCE_VALU /
  * DM_PLAN_FORCE_MFMA force the body, DM_PLAN_ITEMS(k) items of 2^(k-1) tiles (k = 1..3),
  * DM_PLAN_CLAIM(k) claims of 2^(k-1) items (k = 1..4); the autotuner then picks the rest.
  * Limits: D <= 8 and M <= 4096 per instance (M <= 2048 for split MFMA operands).

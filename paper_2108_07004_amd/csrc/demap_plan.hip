@@ -8,7 +8,9 @@
 // the per-item descriptor reads and wave reductions less often, smaller ones balance the tail
 // better); per plan the claim size (1, 2, 4 or 8 work items per counter increment).  The
 // autotuner times every body x item size of a class on a replicated probe block large enough
-// to fill the GPU (cached per GPU arch), then the whole plan at each claim size.
+// to fill the GPU (cached per GPU arch), then the whole plan at each claim size, in the shape of the
+// fastest classes and in the fixed one (a class that is fastest alone need not be among others: each body
+// has its own kernel, and a list's tail is its own), and keeps the fastest.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -64,8 +66,10 @@ std::string arch_name() {
     return colon == std::string::npos ? a : a.substr(0, colon);
 }
 
-// Cache file: one line per entry, "shape2 arch M D prec kind sub ns_per_pair" (lines of any
-// other format are ignored).
+constexpr const char* kTuneTag = "shape3";
+
+// Cache file: one line per entry, "<kTuneTag> arch M D prec kind sub ns_per_pair" (lines of any
+// other format are ignored).  The tag is raised when the kernels change: times of others are no guide.
 void load_tune_cache() {
     if (g_tune_loaded) return;
     g_tune_loaded = true;
@@ -79,7 +83,7 @@ void load_tune_cache() {
         std::string tag, a;
         TuneKey k;
         double v;
-        if (in >> tag >> a >> k.M >> k.D >> k.prec >> k.kind >> k.sub >> v && tag == "shape2" && a == arch && v > 0.0)
+        if (in >> tag >> a >> k.M >> k.D >> k.prec >> k.kind >> k.sub >> v && tag == kTuneTag && a == arch && v > 0.0)
             g_tune[k] = v;
     }
 }
@@ -90,7 +94,7 @@ void save_tune_cache() {
     std::ofstream f(path, std::ios::trunc);
     const std::string arch = arch_name();
     for (const auto& kv : g_tune)
-        f << "shape2 " << arch << ' ' << kv.first.M << ' ' << kv.first.D << ' ' << kv.first.prec << ' '
+        f << kTuneTag << ' ' << arch << ' ' << kv.first.M << ' ' << kv.first.D << ' ' << kv.first.prec << ' '
           << kv.first.kind << ' ' << kv.first.sub << ' ' << kv.second << '\n';
 }
 
@@ -407,6 +411,8 @@ int dm_plan_create(const dm_instance* inst, int n_inst, int prec, int flags, dm_
         cost[i] = kinds[i] == dm::kKindMfma ? 1.6e-4 : 5.0e-4;
     }
     const bool tune = (flags & DM_PLAN_AUTOTUNE) != 0;
+    const std::vector<int> fixed_kinds = kinds, fixed_subs = subs;
+    std::vector<double> fixed_cost = cost;
     if (tune) {
         std::lock_guard<std::mutex> lock(g_tune_mu);
         load_tune_cache();
@@ -433,6 +439,7 @@ int dm_plan_create(const dm_instance* inst, int n_inst, int prec, int flags, dm_
                         g_tune[key] = ns;
                         tuned = true;
                     }
+                    if (kind == fixed_kinds[i] && sub == fixed_subs[i]) fixed_cost[i] = ns;
                     if (best == 0.0 || ns < best) {
                         best = ns;
                         best_kind = kind;
@@ -446,23 +453,44 @@ int dm_plan_create(const dm_instance* inst, int n_inst, int prec, int flags, dm_
         }
         if (tuned) save_tune_cache();
     }
-    // Claim size: forced, the default, or the fastest whole plan (timed without LLR writes).
+    // Claim size: forced, the default, or the fastest whole plan, of the tuned and of the fixed shape.
     int grab = force_claim ? 1 << (force_claim - 1) : kGrabDefault;
-    if (tune && !force_claim) {
-        std::vector<dm_instance> quiet(inst, inst + n_inst);
-        for (auto& q : quiet) q.llr = nullptr;
+    if (tune && !(force_claim && kinds == fixed_kinds && subs == fixed_subs)) {
+        // timed with every instance's LLRs written to one scratch block (without, if there is no room for it)
+        std::vector<dm_instance> probe(inst, inst + n_inst);
+        size_t llr_bytes = 0;
+        for (const auto& q : probe)
+            if (q.llr) llr_bytes = std::max(llr_bytes, sizeof(float) * (size_t)q.N * q.c->m);
+        float* llr = nullptr;
+        if (llr_bytes && hipMalloc((void**)&llr, llr_bytes) != hipSuccess) (void)hipGetLastError();
+        for (auto& q : probe) q.llr = q.llr ? llr : nullptr;
         float best_ms = 0.0f;
-        for (int g : kGrabs) {
-            dm_plan* tp = nullptr;
-            if ((r = make_plan(quiet.data(), n_inst, prec, kinds, subs, cost, g, &tp))) return r;
-            float ms = 0.0f;
-            r = time_plan(tp, &ms);
-            free_plan(tp);
-            if (r) return r;
-            if (best_ms == 0.0f || ms < best_ms) {
-                best_ms = ms;
-                grab = g;
+        auto try_shape = [&](const std::vector<int>& kk, const std::vector<int>& ss, const std::vector<double>& cc) {
+            for (int g : kGrabs) {
+                if (force_claim && g != 1 << (force_claim - 1)) continue;
+                dm_plan* tp = nullptr;
+                int e = make_plan(probe.data(), n_inst, prec, kk, ss, cc, g, &tp);
+                if (e) return e;
+                float ms = 0.0f;
+                e = time_plan(tp, &ms);
+                free_plan(tp);
+                if (e) return e;
+                if (best_ms == 0.0f || ms < best_ms) {
+                    best_ms = ms;
+                    grab = g;
+                }
             }
+            return (int)DM_OK;
+        };
+        r = try_shape(kinds, subs, cost);
+        const float tuned_ms = best_ms;
+        if (!r && !(kinds == fixed_kinds && subs == fixed_subs)) r = try_shape(fixed_kinds, fixed_subs, fixed_cost);
+        (void)hipFree(llr);
+        if (r) return r;
+        if (best_ms < tuned_ms) {
+            kinds = fixed_kinds;
+            subs = fixed_subs;
+            cost = fixed_cost;
         }
     }
     dm_plan* p = nullptr;
