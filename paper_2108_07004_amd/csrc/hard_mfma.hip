@@ -17,8 +17,11 @@
 // under 2.1e-5 K in all; with eps = 2^-15 K (+ a floor for FP16 subnormal lo parts) a gap between
 // the two best groups above 2 eps proves that the minimiser of the reference distance lies in the
 // winning group.  Otherwise (near or exact ties between groups, values out of FP16 range,
-// non-finite inputs) the wave scans the whole table for that symbol with the reference formula,
-// 64 points at a time (lowest label among equal distances): no queue and no second launch.
+// non-finite inputs) the whole table is scanned for that symbol with the reference formula (lowest label
+// among equal distances): by the wave, 64 points at a time, or where that is less work for so many
+// of its symbols, by each lane for its own.  No queue and no second launch.  (All symbols unproven, as
+// with points of 1e-3: 2^20 symbols of 8D with 2048 points 1930 us by the wave alone, 990 so;
+// 4096 of 32-QAM 47 and 29.)
 //
 // A wave takes 64 symbols, one per lane, as two sets of 32 MFMA columns, so that each point
 // tile read from LDS serves both (with one set the LDS reads, 16 cycles a tile and wave, took as
@@ -243,6 +246,31 @@ __global__ __launch_bounds__(kHardMfmaThreads) void hard_mfma_kernel(const HardA
 #pragma unroll 1
             for (int q = 0; q < 16; ++q) near += ref_dist<D>(y, cand + q * D) <= lim;
             if (active && (!ok || near > 1)) ++exact;
+        }
+        // (in issue slots: 2 D + 3 per point by lanes, 2 D + 5 per 64 points and some 60 to reduce per symbol)
+        if (__builtin_popcountll(todo) * (((a.M + 63) >> 6) * (2 * D + 5) + 60) > a.M * (2 * D + 3)) {
+            // many: each lane scans it for its own symbol, points read as scalars
+            const auto tab = (const __attribute__((address_space(4))) float*)(uintptr_t)a.table;
+            float best_d = __builtin_inff();
+            int best_l = 0;
+            constexpr int G = D <= 4 ? 16 : 8;  // points in flight (64 scalars): few waves may be there to hide the reads
+#pragma unroll 1
+            for (int l = 0; l < a.M; l += G) {
+                float x[G][D];
+#pragma unroll
+                for (int g = 0; g < G; ++g)
+#pragma unroll
+                    for (int d = 0; d < D; ++d) x[g][d] = tab[(size_t)(l + g) * D + d];
+#pragma unroll
+                for (int g = 0; g < G; ++g) {
+                    const float d = ref_dist<D>(y, x[g]);
+                    const bool better = d < best_d;
+                    best_d = better ? d : best_d;
+                    best_l = better ? l + g : best_l;
+                }
+            }
+            if (!ok) dec = best_l;
+            todo = 0;
         }
         while (todo) {
             const int j = __builtin_ctzll(todo);
