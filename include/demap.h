@@ -134,7 +134,7 @@ int dm_gmi_estimate_noalloc(const dm_constellation* c, int n_snr, const double* 
 
 /*
  * Batched demapping of many instances (constellation, noise level, block) of uneven M, D and
- * N in one graph of persistent launches (the GMI of many candidate constellations, as the paper's
+ * N in one persistent launch (the GMI of many candidate constellations, as the paper's
  * shaping search evaluates, Sec. 5).  All instances share one operand precision `prec`.
  * Launch shape: each (M, D, prec) class runs the FP32 direct-difference body or the MFMA body
  * with work items of 1, 2 or 4 of that body's symbol tiles (1024 symbols for FP32, 512 for
@@ -167,7 +167,7 @@ typedef struct dm_plan dm_plan;
  * Build a plan for n_inst instances (copied; their device buffers must stay valid for the
  * plan's lifetime): autotune if asked, list the work items (symbol tiles of each instance, the
  * most costly instance first; a list each for the FP32 body and for the MFMA body's small and
- * large tables), allocate all scratch and capture zero-fill + batched kernels + fix-up into a
+ * large tables), allocate all scratch and capture zero-fill + batched kernel + fix-up into a
  * hipGraph.  At run time each workgroup claims the next chunk of work items from
  * a device counter until the list is exhausted (dynamic balance).  Synchronous (runs timing
  * launches when autotuning).
@@ -187,7 +187,7 @@ int dm_plan_results(dm_plan* plan, double* gmi, double* mi, int64_t* fixup_pairs
 int dm_plan_info(const dm_plan* plan, int* kinds, double* ns_per_pair, int32_t* item_symbols);
 
 /* Launch shape of a plan (any output may be NULL): work items in its lists, items a workgroup
- * claims at a time, and workgroups of its widest persistent launch. */
+ * claims at a time, and workgroups of its longest list. */
 int dm_plan_stats(const dm_plan* plan, int64_t* n_items, int32_t* claim_items, int32_t* grid);
 
 void dm_plan_destroy(dm_plan* plan);

@@ -1,20 +1,27 @@
-// Batched exact demapping on MFMA: persistent launches over many (constellation, noise level, block)
-// instances of uneven M, D and N (gfx950); the FP32 instances' launch is in demap_batched_valu.hip.
+// Batched exact demapping: one persistent launch over many (constellation, noise level, block) instances
+// of uneven M, D and N (gfx950).
 //
 // Work items are (instance, sub consecutive symbol tiles) pairs listed instance by instance,
-// the most costly instance first (sub per instance, from the plan's shape choice), one list per
-// kernel.  Workgroups claim fixed chunks of `grab` consecutive items from a counter
+// the most costly instance first (sub per instance, from the plan's shape choice).  There are three
+// lists, each with its own body: MFMA instances of more than 256 points, of 32 .. 256 points (the
+// compile-time tile loop of mfma_small.hpp), and FP32 instances (batched_valu.hpp).  A workgroup belongs to
+// one list, and fills a CU; the launch has the large tables' workgroups first, so those of the next
+// list start as CUs run out of work.  As three kernels one after the other, each list's tail left the chip
+// idle (12 instances of 2^12 .. 2^17 symbols: 271 us, now 191; 64 of 2^14 .. 2^22: 6.43 ms, now 6.32),
+// and as one loop over one list the bodies' registers spilled in each other's loops (228 us; 8.11 ms).
+//
+// Workgroups claim fixed chunks of `grab` consecutive items of their list from a counter
 // (dynamic balance: the cheap items at the end fill the tail) and restage their LDS table only
 // when the next item belongs to another instance.  They ask when the last claim is done: a claim ahead,
 // the first workgroups hold two of the last claims and others none (as many claims as workgroups, 2^20
 // symbols of 8D with 2048 points in FP32: 2046 us ahead, 960 so; 2^19 on MFMA 305 and 168), and
-// asking while a claim for each is left gains 0 to 6% on long lists but costs registers that spill.  GMI / MI partial sums are flushed per chunk
-// and instance, so every fixed-point contribution covers a fixed set of symbols whichever
-// workgroup runs it: the totals are bit-reproducible.  One wave takes 32 symbols, a block 512 per
-// tile.  The instances of 32 .. 256 points (the compile-time tile loop of mfma_small.hpp) and those of
-// more points have a kernel each: in one kernel with the FP32 body their registers spilled (46 of 128
-// per lane; now 15 in the larger points' kernel).  Batched tables use a row stride of 8 (D <= 8 zero-padded): the padded coordinates
-// contribute exact zeros, and the MFMA operand vectors of every instance have the same K layout.
+// asking while a claim for each is left gains 0 to 6% on long lists but costs registers that spill.  GMI / MI
+// partial sums are flushed per chunk and instance, so every fixed-point contribution covers a fixed
+// set of symbols whichever workgroup runs it: the totals are bit-reproducible.  On MFMA one wave takes
+// 32 symbols, a block 512 per tile.  Batched tables use a row stride of 8 (D <= 8 zero-padded): the
+// padded coordinates contribute exact zeros, and the MFMA operand vectors of every instance have the same
+// K layout.  Some 40 of the 128 vector registers spill, outside the tile and point loops.
+#include "batched_valu.hpp"
 #include "device_common.hpp"
 #include "fixup_drain.hpp"
 #include "kernels.hpp"
@@ -25,7 +32,7 @@ namespace dm {
 
 namespace {
 
-constexpr int kThreads = 1024;
+constexpr int kThreads = kBatchThreads;
 constexpr int kWaves = kThreads / 64;
 
 // One 32-symbol batch of an instance with 32 * NT points (D padded to 8): compile-time tile loop
@@ -40,9 +47,9 @@ __device__ __forceinline__ void small_item(const uint4* lds, const BlockView& b,
     mfma_finish<T, 8, SPLIT, MB>(b, k, fill, pv, bfr, S0, S1, tot, n, active, bad, txl, lane, g, mi);
 }
 
+// A workgroup of the list of small (SMALL) or large MFMA tables.
 template <typename T, bool SPLIT, bool SMALL>
-__global__ __launch_bounds__(kThreads) void demap_batched_kernel(const BatchArgs a) {
-    extern __shared__ uint4 lds_raw[];
+__device__ __forceinline__ void batched_mfma(const BatchArgs& a, uint4* lds_raw) {
     constexpr int S = Slots<8, SPLIT>::S;
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -146,6 +153,16 @@ __global__ __launch_bounds__(kThreads) void demap_batched_kernel(const BatchArgs
     queue_close(k, &s_fill);
 }
 
+template <typename T, bool SPLIT>
+__global__ __launch_bounds__(kThreads) void demap_batched_kernel(const BatchLists p) {
+    extern __shared__ __align__(16) uint4 lds_raw[];
+    const int at = (int)blockIdx.x;
+    const int large = p.grid[kBatchLarge], small = p.grid[kBatchSmall];
+    if (at < large) batched_mfma<T, SPLIT, false>(p.list[kBatchLarge], lds_raw);
+    else if (at < large + small) batched_mfma<T, SPLIT, true>(p.list[kBatchSmall], lds_raw);
+    else batched_valu(p.list[kBatchValu], reinterpret_cast<float*>(lds_raw));
+}
+
 // Exact recomputation of the queued symbols of every instance (one lane or one wavefront per symbol).
 __global__ __launch_bounds__(kFixThreads) void batched_fixup_kernel(const BatchArgs a) {
     __shared__ float s_t[4][kFixCached];  // per-wave exponent cache (32 KiB per block)
@@ -159,30 +176,21 @@ __global__ void zero_words(uint32_t* p, size_t n) {
         p[i] = 0u;
 }
 
-// Dynamic LDS: the largest table of the kernel's instances, plus the one fragment tile that the
-// pipeline of the larger tables reads past a 16-tile block.
-template <bool SPLIT, bool SMALL>
-constexpr int batched_lds() {
-    return SMALL ? 8 * Slots<8, SPLIT>::S * 1024 : kBatchedLdsAlloc;
-}
-
 template <typename T, bool SPLIT>
 hipError_t prepare_t() {
-    hipError_t e = hipFuncSetAttribute((const void*)demap_batched_kernel<T, SPLIT, false>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, batched_lds<SPLIT, false>());
-    if (e != hipSuccess) return e;
-    return hipFuncSetAttribute((const void*)demap_batched_kernel<T, SPLIT, true>,
-                               hipFuncAttributeMaxDynamicSharedMemorySize, batched_lds<SPLIT, true>());
+    return hipFuncSetAttribute((const void*)demap_batched_kernel<T, SPLIT>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                               kBatchedLdsAlloc);
 }
 
 template <typename T, bool SPLIT>
-hipError_t launch_batched_t(const BatchArgs& a, bool small, int grid, hipStream_t st) {
-    if (small)
-        hipLaunchKernelGGL((demap_batched_kernel<T, SPLIT, true>), dim3(grid), dim3(kThreads), (batched_lds<SPLIT, true>()),
-                           st, a);
-    else
-        hipLaunchKernelGGL((demap_batched_kernel<T, SPLIT, false>), dim3(grid), dim3(kThreads),
-                           (batched_lds<SPLIT, false>()), st, a);
+hipError_t launch_batched_t(const BatchLists& p, hipStream_t st) {
+    // the largest table of the lists at hand; a large table also has the one fragment tile that its pipeline
+    // reads past a 16-tile block
+    size_t lds = p.grid[kBatchValu] ? p.list[kBatchValu].lds_bytes : 0;
+    if (p.grid[kBatchSmall]) lds = std::max<size_t>(lds, 8 * Slots<8, SPLIT>::S * 1024);
+    if (p.grid[kBatchLarge]) lds = std::max<size_t>(lds, kBatchedLdsAlloc);
+    const int grid = p.grid[kBatchValu] + p.grid[kBatchSmall] + p.grid[kBatchLarge];
+    hipLaunchKernelGGL((demap_batched_kernel<T, SPLIT>), dim3(grid), dim3(kThreads), lds, st, p);
     return hipGetLastError();
 }
 
@@ -190,14 +198,14 @@ hipError_t launch_batched_t(const BatchArgs& a, bool small, int grid, hipStream_
 
 int batched_tile_symbols(int kind) { return kind == kKindMfma ? kWaves * 32 : 1024; }
 
-hipError_t launch_demap_batched(const BatchArgs& a, int which, int prec, int grid, hipStream_t st) {
-    if (which == kBatchValu) return launch_demap_batched_valu(a, grid, st);
-    const bool small = which == kBatchSmall;
+hipError_t launch_demap_batched(const BatchLists& p, int prec, hipStream_t st) {
+    if (p.grid[kBatchSmall] + p.grid[kBatchLarge] == 0)
+        return p.grid[kBatchValu] ? launch_demap_batched_valu(p.list[kBatchValu], p.grid[kBatchValu], st) : hipSuccess;
     switch (prec) {
-        case 4: return launch_batched_t<_Float16, true>(a, small, grid, st);
-        case 1: return launch_batched_t<__bf16, false>(a, small, grid, st);
-        case 2: return launch_batched_t<_Float16, false>(a, small, grid, st);
-        case 3: return launch_batched_t<__bf16, true>(a, small, grid, st);
+        case 4: return launch_batched_t<_Float16, true>(p, st);
+        case 1: return launch_batched_t<__bf16, false>(p, st);
+        case 2: return launch_batched_t<_Float16, false>(p, st);
+        case 3: return launch_batched_t<__bf16, true>(p, st);
         default: return hipErrorInvalidValue;
     }
 }

@@ -10,7 +10,7 @@
 // autotuner times every body x item size of a class on a replicated probe block large enough
 // to fill the GPU (cached per GPU arch), then the whole plan at each claim size, in the shape of the
 // fastest classes and in the fixed one (a class that is fastest alone need not be among others: each body
-// has its own kernel, and a list's tail is its own), and keeps the fastest.
+// has its own list and workgroups), and keeps the fastest.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -120,8 +120,7 @@ struct dm_plan {
     dm::FixEntry* d_queue = nullptr;
     uint32_t queue_cap = 0;
     void* h_stage = nullptr;
-    dm::BatchArgs args[dm::kBatchKernels] = {};  // per kernel: its work list, claim counter, queue regions
-    int grids[dm::kBatchKernels] = {};           // its workgroups (0: no work)
+    dm::BatchLists lists{};  // work lists, their claim counters and workgroups
     hipStream_t cap_stream = nullptr;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -165,10 +164,10 @@ int build_descs(dm_plan* p, std::vector<dm::BatchDesc>& desc) {
     return DM_OK;
 }
 
-// Work lists, one per kernel, one after the other in `items` (kernel q's from first[q] to first[q + 1]):
+// Work lists, one after the other in `items` (list q's from first[q] to first[q + 1]):
 // instances in decreasing order of estimated cost (ns per pair x M x N), each as consecutive
 // symbol tiles.  Workgroups claim a list in chunks at run time.
-void build_work(const dm_plan* p, std::vector<dm::WorkItem>& items, int (&first)[dm::kBatchKernels + 1]) {
+void build_work(const dm_plan* p, std::vector<dm::WorkItem>& items, int (&first)[dm::kBatchLists + 1]) {
     std::vector<int> order(p->n_inst);
     std::vector<double> cost(p->n_inst);
     for (int i = 0; i < p->n_inst; ++i) {
@@ -176,27 +175,27 @@ void build_work(const dm_plan* p, std::vector<dm::WorkItem>& items, int (&first)
         cost[i] = p->ns_per_pair[i] * p->inst[i].c->M * (double)p->inst[i].N;
     }
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return cost[a] > cost[b]; });
-    for (int q = 0; q < dm::kBatchKernels; ++q) {
+    for (int q = 0; q < dm::kBatchLists; ++q) {
         first[q] = (int)items.size();
         for (int i : order) {
-            if (dm::batch_kernel(p->kind[i], p->inst[i].c->M) != q) continue;
+            if (dm::batch_list(p->kind[i], p->inst[i].c->M) != q) continue;
             const int64_t tile = (int64_t)dm::batched_tile_symbols(p->kind[i]) * p->sub[i];
             for (int64_t n0 = 0; n0 < p->inst[i].N; n0 += tile) items.push_back(dm::WorkItem{i, 1, n0});
         }
         for (int t = (int)items.size() - 2; t >= first[q]; --t)
             if (items[t].inst == items[t + 1].inst && (t + 1 - first[q]) % p->grab) items[t].run = items[t + 1].run + 1;
     }
-    first[dm::kBatchKernels] = (int)items.size();
+    first[dm::kBatchLists] = (int)items.size();
 }
 
 int alloc_plan_buffers(dm_plan* p, const std::vector<dm::BatchDesc>& desc, const std::vector<dm::WorkItem>& items,
-                       const int (&first)[dm::kBatchKernels + 1], int cus) {
+                       const int (&first)[dm::kBatchLists + 1], int cus) {
     DM_HIP_TRY(hipMalloc(&p->d_desc, desc.size() * sizeof(dm::BatchDesc)));
     DM_HIP_TRY(hipMalloc(&p->d_items, std::max<size_t>(1, items.size()) * sizeof(dm::WorkItem)));
     DM_HIP_TRY(hipMemcpy(p->d_desc, desc.data(), desc.size() * sizeof(dm::BatchDesc), hipMemcpyHostToDevice));
     if (!items.empty())
         DM_HIP_TRY(hipMemcpy(p->d_items, items.data(), items.size() * sizeof(dm::WorkItem), hipMemcpyHostToDevice));
-    p->n_words = (size_t)p->n_inst * dm::kAccSlots * 2 * 2 + p->n_inst + 1 + dm::kBatchKernels;  // cleared by every launch
+    p->n_words = (size_t)p->n_inst * dm::kAccSlots * 2 * 2 + p->n_inst + 1 + dm::kBatchLists;  // cleared by every launch
     DM_HIP_TRY(hipMalloc(&p->d_words, (p->n_words + dm::kMaxQueueRegions) * sizeof(uint32_t)));
     int64_t total_n = 0;
     for (const auto& in : p->inst) total_n += in.N;
@@ -205,21 +204,20 @@ int alloc_plan_buffers(dm_plan* p, const std::vector<dm::BatchDesc>& desc, const
     DM_HIP_TRY(hipHostMalloc(&p->h_stage, p->n_words * sizeof(uint32_t), hipHostMallocDefault));
     auto* acc = reinterpret_cast<unsigned long long*>(p->d_words);
     uint32_t* tail = p->d_words + (size_t)p->n_inst * dm::kAccSlots * 2 * 2;
-    // one block of 1024 threads per CU, no more than a kernel's list has claims
+    // one block of 1024 threads per CU and list, no more than the list has claims
     size_t valu_lds = 0;
     for (int i = 0; i < p->n_inst; ++i)
         if (p->kind[i] == dm::kKindValu && p->inst[i].N > 0)
             valu_lds = std::max(valu_lds, (size_t)std::max(16, p->inst[i].c->M) * 8 * sizeof(float));
     int regions = 0;
-    for (int q = 0; q < dm::kBatchKernels; ++q) {
+    for (int q = 0; q < dm::kBatchLists; ++q) {
         const int n = first[q + 1] - first[q];
-        p->grids[q] = std::min((n + p->grab - 1) / p->grab, std::min(cus, dm::kMaxQueueRegions / dm::kBatchKernels));
-        p->grid = std::max(p->grid, p->grids[q]);
-        regions += p->grids[q];
+        p->lists.grid[q] = std::min((n + p->grab - 1) / p->grab, std::min(cus, dm::kMaxQueueRegions / dm::kBatchLists));
+        p->grid = std::max(p->grid, p->lists.grid[q]);
+        regions += p->lists.grid[q];
     }
-    int at = 0;
-    for (int q = 0; q < dm::kBatchKernels; ++q) {
-        dm::BatchArgs& a = p->args[q];
+    for (int q = 0; q < dm::kBatchLists; ++q) {
+        dm::BatchArgs& a = p->lists.list[q];
         a.desc = p->d_desc;
         a.items = p->d_items + first[q];
         a.n_items = (int32_t)(first[q + 1] - first[q]);
@@ -232,18 +230,15 @@ int alloc_plan_buffers(dm_plan* p, const std::vector<dm::BatchDesc>& desc, const
         a.sinks.queue_count = p->d_words + p->n_words;
         a.sinks.queue = p->d_queue;
         a.sinks.queue_regions = regions;
-        a.sinks.queue_first = at;
         a.sinks.queue_seg = p->queue_cap / (uint32_t)std::max(1, regions);
-        at += p->grids[q];
     }
     return DM_OK;
 }
 
 int enqueue(dm_plan* p, hipStream_t st) {
     DM_HIP_TRY(dm::launch_zero_words(p->d_words, p->n_words, st));
-    for (int q = dm::kBatchKernels - 1; q >= 0; --q)
-        if (p->grids[q] > 0) DM_HIP_TRY(dm::launch_demap_batched(p->args[q], q, p->prec, p->grids[q], st));
-    DM_HIP_TRY(dm::launch_batched_fixup(p->args[0], p->fix_grid, st));
+    DM_HIP_TRY(dm::launch_demap_batched(p->lists, p->prec, st));
+    DM_HIP_TRY(dm::launch_batched_fixup(p->lists.list[0], p->fix_grid, st));
     return DM_OK;
 }
 
@@ -293,7 +288,7 @@ int make_plan(const dm_instance* inst, int n_inst, int prec, const std::vector<i
         return hip_fail(e, "hipFuncSetAttribute(batched kernel)");
     }
     p->fix_grid = cus * 4;
-    int first[dm::kBatchKernels + 1];
+    int first[dm::kBatchLists + 1];
     build_work(p, items, first);
     r = alloc_plan_buffers(p, desc, items, first, cus);
     if (r) {
@@ -560,7 +555,7 @@ int dm_plan_stats(const dm_plan* p, int64_t* n_items, int32_t* claim_items, int3
     if (!p) return fail(DM_EINVAL, "null plan");
     if (n_items) {
         *n_items = 0;
-        for (const dm::BatchArgs& a : p->args) *n_items += a.n_items;
+        for (const dm::BatchArgs& a : p->lists.list) *n_items += a.n_items;
     }
     if (claim_items) *claim_items = p->grab;
     if (grid) *grid = p->grid;

@@ -71,8 +71,7 @@ struct Sinks {
     FixEntry* queue;             // queue_regions regions of queue_seg entries, one per workgroup
     uint32_t* queue_count;       // [queue_regions] entries of each region, stored by its workgroup
     uint32_t queue_seg;
-    int32_t queue_regions;       // workgroups of the demapping launches that share the queue
-    int32_t queue_first;         // region of this launch's workgroup 0
+    int32_t queue_regions;       // workgroups of the demapping launch
 };
 
 struct SnrArg {
@@ -115,10 +114,10 @@ struct LaunchArgs {
 // ---- batched launch over many instances ----
 constexpr int kKindValu = 0;  // FP32 direct-difference body
 constexpr int kKindMfma = 1;  // MFMA cross-term body
-// Kernels of a batched launch, each with its own work list: FP32 items, MFMA items of 32 .. 256 points
+// Work lists of a batched launch: FP32 items, MFMA items of 32 .. 256 points
 // and MFMA items of more points.
-enum : int { kBatchValu = 0, kBatchSmall = 1, kBatchLarge = 2, kBatchKernels = 3 };
-inline int batch_kernel(int kind, int M) { return kind == kKindValu ? kBatchValu : M <= 256 ? kBatchSmall : kBatchLarge; }
+enum : int { kBatchValu = 0, kBatchSmall = 1, kBatchLarge = 2, kBatchLists = 3 };
+inline int batch_list(int kind, int M) { return kind == kKindValu ? kBatchValu : M <= 256 ? kBatchSmall : kBatchLarge; }
 constexpr int kBatchedLdsBytes = 131072;  // largest staged table (FP32 rows or MFMA fragments)
 // Dynamic LDS of the batched kernel: the table plus the one 2 KiB fragment tile (split
 // operands) that the MFMA pipeline reads past a 16-tile block.
@@ -146,6 +145,12 @@ struct BatchArgs {
     uint32_t* next;            // claim counter (zeroed before every launch)
     int32_t lds_bytes;         // FP32 kernel: its largest table
     Sinks sinks;
+};
+
+// The lists of a launch: workgroups of the large MFMA tables' list first, then of the small, then of FP32.
+struct BatchLists {
+    BatchArgs list[kBatchLists];
+    int32_t grid[kBatchLists];  // workgroups of each list (0: empty)
 };
 
 // Wave-uniform copy of a struct in memory: its words in scalar registers.  Loads that the compiler

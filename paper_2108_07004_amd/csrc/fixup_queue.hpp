@@ -193,7 +193,7 @@ __device__ __forceinline__ void queue_or_fix(const BlockView& b, const Sinks& k,
                                              uint32_t mask, uint32_t near, double& gc, double& mc) {
     const uint32_t slot = atomicAdd(fill, 1u);
     if (__builtin_expect(slot < k.queue_seg, 1)) {
-        k.queue[(size_t)(k.queue_first + blockIdx.x) * k.queue_seg + slot] = FixEntry{n, (uint32_t)b.tag, mask, near};
+        k.queue[(size_t)blockIdx.x * k.queue_seg + slot] = FixEntry{n, (uint32_t)b.tag, mask, near};
     } else {
         if (k.fix_pairs) atomicAdd(k.fix_pairs + b.tag, (uint32_t)__popc(mask & 0xFFFFu));
         double g1 = 0.0, m1 = 0.0;
@@ -206,7 +206,7 @@ __device__ __forceinline__ void queue_or_fix(const BlockView& b, const Sinks& k,
 // Store the workgroup's region count; every thread calls it once, after its last queue_or_fix.
 __device__ __forceinline__ void queue_close(const Sinks& k, const uint32_t* fill) {
     __syncthreads();
-    if (threadIdx.x == 0) k.queue_count[k.queue_first + blockIdx.x] = min(*fill, k.queue_seg);
+    if (threadIdx.x == 0) k.queue_count[blockIdx.x] = min(*fill, k.queue_seg);
 }
 
 }  // namespace dm

@@ -66,9 +66,8 @@ int batched_tile_symbols(int kind);
 // capturing it).
 hipError_t prepare_batched(int prec);
 
-// One persistent batched kernel (kBatchValu / kBatchSmall / kBatchLarge); prec selects the MFMA
-// operand variant.
-hipError_t launch_demap_batched(const BatchArgs& a, int which, int prec, int grid, hipStream_t st);
+// The persistent batched kernel over a plan's lists; prec selects the MFMA operand variant.
+hipError_t launch_demap_batched(const BatchLists& p, int prec, hipStream_t st);
 hipError_t launch_demap_batched_valu(const BatchArgs& a, int grid, hipStream_t st);
 hipError_t prepare_batched_valu();
 
