@@ -466,6 +466,12 @@ int dm_plan_create(const dm_instance* inst, int n_inst, int prec, int flags, dm_
                 dm_plan* tp = nullptr;
                 int e = make_plan(probe.data(), n_inst, prec, kk, ss, cc, g, &tp);
                 if (e) return e;
+                int64_t n_items = 0;
+                for (const dm::BatchArgs& a : tp->lists.list) n_items += a.n_items;
+                if (!force_claim && g > kGrabDefault && n_items < (int64_t)4 * g * tp->grid) {
+                    free_plan(tp);  // so few claims per workgroup balance only by luck of the timing runs
+                    continue;
+                }
                 float ms = 0.0f;
                 e = time_plan(tp, &ms);
                 free_plan(tp);
