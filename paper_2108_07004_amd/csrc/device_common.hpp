@@ -298,19 +298,28 @@ __device__ __forceinline__ void load_symbol(float (&y)[DP], const float* src, in
     for (int d = 0; d < DP; ++d) y[d] = (active && d < D) ? src[d] : 0.0f;
 }
 
+// ||y - x||^2 of a point read through any kind of pointer.
+template <int DP, typename Ptr>
+__device__ __forceinline__ float point_dist(const float (&y)[DP], Ptr p) {
+    float x[DP];
+#pragma unroll
+    for (int d = 0; d < DP; ++d) x[d] = p[d];
+    return sqdist<DP>(y, x);
+}
+
 // Exact log-sum-exp (log2 units, t_j = K - c d_j^2) of the subsets of label bit p,
 // with each subset shifted by its own maximum (table rows LS apart).  Returns L = log2 S^1 - log2 S^0.
-template <int DP, int LS>
-__device__ float exact_bit_llr2(const float (&y)[DP], const float* table, int M, int p, float c, float K) {
+template <int DP, int LS, typename Table>
+__device__ float exact_bit_llr2(const float (&y)[DP], Table table, int M, int p, float c, float K) {
     float mx0 = -INFINITY, mx1 = -INFINITY;
     for (int j = 0; j < M; ++j) {
-        const float t = fmaf(-c, sqdist<DP>(y, table + (size_t)j * LS), K);
+        const float t = fmaf(-c, point_dist<DP>(y, table + (size_t)j * LS), K);
         if ((j >> p) & 1) mx1 = fmaxf(mx1, t);
         else mx0 = fmaxf(mx0, t);
     }
     float s0 = 0.0f, s1 = 0.0f;
     for (int j = 0; j < M; ++j) {
-        const float t = fmaf(-c, sqdist<DP>(y, table + (size_t)j * LS), K);
+        const float t = fmaf(-c, point_dist<DP>(y, table + (size_t)j * LS), K);
         if ((j >> p) & 1) s1 += hw_exp2(t - mx1);
         else s0 += hw_exp2(t - mx0);
     }
@@ -318,13 +327,14 @@ __device__ float exact_bit_llr2(const float (&y)[DP], const float* table, int M,
 }
 
 // MI term m - log2 sum_j 2^(t_j - t_tx), exact max shift.
-template <int DP, int LS>
-__device__ float exact_mi_term(const float (&y)[DP], const float* table, int M, int m, int txl, float c, float K) {
+template <int DP, int LS, typename Table>
+__device__ float exact_mi_term(const float (&y)[DP], Table table, int M, int m, const float* xtx, float c,
+                               float K) {
     float mx = -INFINITY;
-    for (int j = 0; j < M; ++j) mx = fmaxf(mx, fmaf(-c, sqdist<DP>(y, table + (size_t)j * LS), K));
+    for (int j = 0; j < M; ++j) mx = fmaxf(mx, fmaf(-c, point_dist<DP>(y, table + (size_t)j * LS), K));
     float s = 0.0f;
-    for (int j = 0; j < M; ++j) s += hw_exp2(fmaf(-c, sqdist<DP>(y, table + (size_t)j * LS), K) - mx);
-    const float ttx = fmaf(-c, sqdist<DP>(y, table + (size_t)txl * LS), K);
+    for (int j = 0; j < M; ++j) s += hw_exp2(fmaf(-c, point_dist<DP>(y, table + (size_t)j * LS), K) - mx);
+    const float ttx = fmaf(-c, sqdist<DP>(y, xtx), K);
     return (float)m - ((mx - ttx) + hw_log2(s));
 }
 
@@ -332,20 +342,22 @@ __device__ float exact_mi_term(const float (&y)[DP], const float* table, int M, 
 // a NaN, an infinity or overflowing distances contributes nothing, and the others' terms stay.
 __device__ __forceinline__ double finite_term(double v) { return __builtin_isfinite(v) ? v : 0.0; }
 
-// Recompute the flagged bits of one symbol in one lane; returns the GMI / MI corrections.
-template <int DP, int LS>
-__device__ void fixup_one(const BlockView& b, const Sinks& k, uint32_t n, uint32_t mask, double& gcorr,
+// Recompute the flagged bits of one symbol in one lane; returns the GMI / MI corrections.  table: b.table, as
+// the caller can best read it.
+template <int DP, int LS, typename Table>
+__device__ void fixup_one(const BlockView& b, const Sinks& k, Table table, uint32_t n, uint32_t mask, double& gcorr,
                           double& mcorr) {
     float y[DP];
     load_symbol<DP>(y, b.y + (size_t)n * b.D, b.D, true);
     const int txl = b.tx ? tx_label(b, k, n) : 0;
     for (int p = 0; p < b.m; ++p) {
         if (!((mask >> p) & 1u)) continue;
-        const float L = exact_bit_llr2<DP, LS>(y, b.table, b.M, p, b.c, b.K);
+        const float L = exact_bit_llr2<DP, LS>(y, table, b.M, p, b.c, b.K);
         if (b.llr) b.llr[(size_t)n * b.m + (b.m - 1 - p)] = L * 0.69314718055994531f;
         if (b.tx) gcorr += (double)gmi_bit_term(L, (txl >> p) & 1);
     }
-    if ((mask & kMiFlag) && b.tx) mcorr += (double)exact_mi_term<DP, LS>(y, b.table, b.M, b.m, txl, b.c, b.K);
+    if ((mask & kMiFlag) && b.tx)
+        mcorr += (double)exact_mi_term<DP, LS>(y, table, b.M, b.m, b.table + (size_t)txl * LS, b.c, b.K);
 }
 
 }  // namespace dm

@@ -180,7 +180,7 @@ __device__ void fixup_in_place(const BlockView& b, const Sinks& k, uint32_t n, u
             mask = left;
         }
     }
-    fixup_one<DP, LS>(b, k, n, mask, gcorr, mcorr);
+    fixup_one<DP, LS>(b, k, b.table, n, mask, gcorr, mcorr);
 }
 
 // Queue a symbol for the fix-up (near: FixEntry.near of the symbol) in the workgroup's region, whose
