@@ -278,8 +278,7 @@ int run_chunk_on(dm_constellation* c, const ChunkScratch& scr, int n_snr, const 
                                      fp32 ? (c->M <= 64 ? 4 : 2) : dm::mfma_small_supported(c->M, c->D) ? (c->M == 256 ? 3 : 4) : 1);
     a.sinks.queue_regions = grid;
     a.sinks.queue_seg = scr.queue_cap / (uint32_t)grid;
-    const int per_block = dm::fixup_block_symbols(c->M);
-    const int64_t fix_most = ((int64_t)N * n_snr + per_block - 1) / per_block;
+    const int64_t fix_most = dm::fixup_most_blocks(c->M, N * n_snr);
     const int fix_grid = (int)std::min<int64_t>((int64_t)c->cus * dm::fixup_blocks_per_cu(c->M), fix_most);
     ProfRec pr{nullptr, nullptr, nullptr};
     if (g_prof_on && allow_prof) {

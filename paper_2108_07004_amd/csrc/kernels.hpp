@@ -22,11 +22,17 @@ hipError_t launch_hard_mfma(const HardArgs& a, const void* frag, float r_max, in
 // FP32 direct-difference demapper (one lane per symbol, persistent grid).
 hipError_t launch_demap_valu(const LaunchArgs& a, int grid, int threads, hipStream_t st);
 
-// Queued symbols that make work for one block of the fix-up kernel: a lane each up to 64 points, the smallest
-// chunk of the row form (128 and 256 points), else a wavefront each.  A launch has no more blocks
-// than its symbols could fill, so that an empty pass costs little.  (With 256 for every form, 64 symbols
-// per wavefront: 4096 symbols of 8D, 4096 points at 21 dB 4040 us a call, now 476; of 256-QAM 22.5, now 18.3.)
-inline int fixup_block_symbols(int M) { return M <= 64 ? 256 : M <= 256 ? 32 : 4; }
+// Most blocks that a launch's symbols give the fix-up kernel work for, so that an empty pass costs little: a
+// lane per symbol up to 64 points; for 128 and 256 points (rows) chunks of 32 on up to 512 blocks, then
+// of 256; else a wavefront per symbol.  (With 256 symbols per block for every form, 64 per wavefront: 4096
+// symbols of 8D, 4096 points at 21 dB 4040 us a call, now 476; of 256-QAM 22.5, now 18.3.  Rows over more
+// than 512 blocks: an empty pass over 200000 symbols takes 1.6 us more.)
+inline int64_t fixup_most_blocks(int M, int64_t symbols) {
+    auto blocks = [symbols](int per) { return (symbols + per - 1) / per; };
+    if (M <= 64) return blocks(256);
+    if (M <= 256) return std::max(blocks(256), std::min<int64_t>(blocks(32), 512));
+    return blocks(4);
+}
 
 // Exact recomputation of the queued (symbol, bit) pairs whose far-subset sum underflowed.
 hipError_t launch_fixup(const LaunchArgs& a, int grid, hipStream_t st);
