@@ -338,9 +338,9 @@ __device__ float exact_mi_term(const float (&y)[DP], Table table, int M, int m, 
     return (float)m - ((mx - ttx) + hw_log2(s));
 }
 
-// GMI / MI terms of one recomputed symbol, as they enter sums shared with other symbols: a symbol with
-// a NaN, an infinity or overflowing distances contributes nothing, and the others' terms stay.
-__device__ __forceinline__ double finite_term(double v) { return __builtin_isfinite(v) ? v : 0.0; }
+// A recomputed symbol's GMI and MI terms as they enter sums shared with other symbols: those of a NaN, an
+// infinity or overflowing distances count nothing, and the others' stay.
+__device__ __forceinline__ float finite_term(float v) { return __builtin_fabsf(v) < __builtin_inff() ? v : 0.0f; }
 
 // Recompute the flagged bits of one symbol in one lane; returns the GMI / MI corrections.  table: b.table, as
 // the caller can best read it.
@@ -354,10 +354,10 @@ __device__ void fixup_one(const BlockView& b, const Sinks& k, Table table, uint3
         if (!((mask >> p) & 1u)) continue;
         const float L = exact_bit_llr2<DP, LS>(y, table, b.M, p, b.c, b.K);
         if (b.llr) b.llr[(size_t)n * b.m + (b.m - 1 - p)] = L * 0.69314718055994531f;
-        if (b.tx) gcorr += (double)gmi_bit_term(L, (txl >> p) & 1);
+        if (b.tx) gcorr += (double)finite_term(gmi_bit_term(L, (txl >> p) & 1));
     }
     if ((mask & kMiFlag) && b.tx)
-        mcorr += (double)exact_mi_term<DP, LS>(y, table, b.M, b.m, b.table + (size_t)txl * LS, b.c, b.K);
+        mcorr += (double)finite_term(exact_mi_term<DP, LS>(y, table, b.M, b.m, b.table + (size_t)txl * LS, b.c, b.K));
 }
 
 }  // namespace dm

@@ -93,7 +93,7 @@ __device__ void fixup_wave(const BlockView& b, const Sinks& k, uint32_t n, uint3
                                : wave_exact_llr2<DP>(y, b.table, b.M, p, b.c, b.K, lse0);
         if (lane == 0) {
             if (b.llr) b.llr[(size_t)n * b.m + (b.m - 1 - p)] = L * 0.69314718055994531f;
-            if (b.tx) gcorr += (double)gmi_bit_term(L, (txl >> p) & 1);
+            if (b.tx) gcorr += (double)finite_term(gmi_bit_term(L, (txl >> p) & 1));
         }
     }
     if ((mask & kMiFlag) && b.tx) {
@@ -101,7 +101,7 @@ __device__ void fixup_wave(const BlockView& b, const Sinks& k, uint32_t n, uint3
         if (cached) (void)cached_exact_llr2(tl, b.M, -1, lse_all);
         else (void)wave_exact_llr2<DP>(y, b.table, b.M, -1, b.c, b.K, lse_all);
         const float ttx = fmaf(-b.c, sqdist<DP>(y, b.table + (size_t)txl * DP), b.K);
-        if (lane == 0) mcorr += (double)((float)b.m - (lse_all - ttx));
+        if (lane == 0) mcorr += (double)finite_term((float)b.m - (lse_all - ttx));
     }
 }
 
@@ -276,7 +276,7 @@ __device__ void fix_rows(const Sinks& k, ViewFn view, AddFn add, FetchFn fetch, 
                         const float lf = sh + hw_log2(sf);
                         const float L = fb ? lf - near_lse : near_lse - lf;
                         if (b.llr) b.llr[(size_t)e.n * m + (m - 1 - p)] = L * 0.69314718055994531f;
-                        if (b.tx) gc += (double)gmi_bit_term(L, (txl >> p) & 1);
+                        if (b.tx) gc += (double)finite_term(gmi_bit_term(L, (txl >> p) & 1));
                     }
                 }
                 if (__ballot(want && !far_ok) == 0ull) continue;
@@ -320,11 +320,11 @@ __device__ void fix_rows(const Sinks& k, ViewFn view, AddFn add, FetchFn fetch, 
                     if (p < m) {
                         const float L = (mx1 - mx0) + (hw_log2(s1) - hw_log2(s0));
                         if (b.llr) b.llr[(size_t)e.n * m + (m - 1 - p)] = L * 0.69314718055994531f;
-                        if (b.tx) gc += (double)gmi_bit_term(L, (txl >> p) & 1);
+                        if (b.tx) gc += (double)finite_term(gmi_bit_term(L, (txl >> p) & 1));
                     } else {
                         const float lse_all = (mx0 + hw_log2(s0)) + sh;
                         const float ttx = fmaf(-b.c, sqdist<DP>(y, tab + txl * DP), b.K);
-                        mc += (double)((float)m - (lse_all - ttx));
+                        mc += (double)finite_term((float)m - (lse_all - ttx));
                     }
                 }
             }
@@ -437,7 +437,6 @@ __device__ void drain_fix_queue(const Sinks& k, ViewFn view, float* tl, int cach
     };
     auto add = [&](int tag, int slot, int which, double v) {
         if (!k.acc) return;
-        v = finite_term(v);
         if (tag < kFixLdsTags) {
             const long long q = __double2ll_rn(v * kFixScale);
             if (q != 0) atomicAdd(&s_acc[tag * 2 + which], (unsigned long long)q);

@@ -174,7 +174,7 @@ __global__ __launch_bounds__(kThreads) void fixup_large_kernel(const LaunchArgs 
         if (k.fix_pairs) atomicAdd(&s_pairs[e.tag], (uint32_t)__popc(e.mask & 0xFFFFu));
     };
     auto add = [&](uint32_t tag, int which, double v) {
-        const long long q = __double2ll_rn(finite_term(v) * kFixScale);
+        const long long q = __double2ll_rn(v * kFixScale);
         if (k.acc && q != 0) atomicAdd(&s_acc[tag * 2 + which], (unsigned long long)q);
     };
     if (count < lanes_from) {

@@ -47,7 +47,7 @@ __device__ __forceinline__ void two_pass_symbol(const BlockView& b, Table tab, c
         }
         const float L = (mx1 - mx0) + (hw_log2(s1) - hw_log2(s0));
         put(p, L);
-        if (b.tx) g += (double)gmi_bit_term(L, (txl >> p) & 1);
+        if (b.tx) g += (double)finite_term(gmi_bit_term(L, (txl >> p) & 1));
     }
     if ((mask & kMiFlag) && b.tx) {
         float mx = -INFINITY, s = 0.0f;
@@ -56,7 +56,7 @@ __device__ __forceinline__ void two_pass_symbol(const BlockView& b, Table tab, c
 #pragma unroll
         for (int j = 0; j < MC; ++j) s += hw_exp2(t[j] - mx);
         const float ttx = fmaf(-b.c, sqdist<DP>(y, xtx), b.K);
-        mi += (double)((float)MB - ((mx - ttx) + hw_log2(s)));
+        mi += (double)finite_term((float)MB - ((mx - ttx) + hw_log2(s)));
     }
 }
 
@@ -192,14 +192,13 @@ template <int DP, int LS, bool WIDE>
 __device__ __forceinline__ void queue_or_fix(const BlockView& b, const Sinks& k, uint32_t* fill, uint32_t n,
                                              uint32_t mask, uint32_t near, double& gc, double& mc) {
     const uint32_t slot = atomicAdd(fill, 1u);
-    if (__builtin_expect(slot < k.queue_seg, 1)) {
+    // (the long form is marked unlikely, which keeps it from the registers of the kernels of D = 3, 5, 6, 7; the
+    // short one not: with it 8 points of 2D take a 65th register)
+    if (WIDE ? __builtin_expect(slot < k.queue_seg, 1) : slot < k.queue_seg) {
         k.queue[(size_t)blockIdx.x * k.queue_seg + slot] = FixEntry{n, (uint32_t)b.tag, mask, near};
     } else {
         if (k.fix_pairs) atomicAdd(k.fix_pairs + b.tag, (uint32_t)__popc(mask & 0xFFFFu));
-        double g1 = 0.0, m1 = 0.0;
-        fixup_in_place<DP, LS, WIDE>(b, k, n, mask, g1, m1);
-        gc += finite_term(g1);
-        mc += finite_term(m1);
+        fixup_in_place<DP, LS, WIDE>(b, k, n, mask, gc, mc);
     }
 }
 

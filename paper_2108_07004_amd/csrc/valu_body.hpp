@@ -264,12 +264,9 @@ __device__ __forceinline__ void valu_epilogue(const BlockView& b, const Sinks& k
     if constexpr (MC != 0 && MC <= 16) {
         const bool fix = mask != 0u && active;
         if (__builtin_popcountll(__ballot(fix)) >= kInPlaceLanes && fix) {
-            double g1 = 0.0, m1 = 0.0;
-            pairs += (uint32_t)__popc(mask & 0xFFFFu);
             two_pass_symbol<DP, LS, MC>(
-                b, tab, y, mask, txl, xtx, [&](int p, float L) { Lv[p] = L * 0.69314718055994531f; }, g1, m1);
-            gc += finite_term(g1);
-            mc += finite_term(m1);
+                b, tab, y, mask, txl, xtx, [&](int p, float L) { Lv[p] = L * 0.69314718055994531f; }, gc, mc);
+            pairs += (uint32_t)__popc(mask & 0xFFFFu);
             mask = 0u;
         }
     }

@@ -40,7 +40,7 @@ static_assert(kWideShift - 1860 == -980, "wide_ok's bound");
 // MI term of a symbol with m label bits: the sum over all points and the transmitted point's exponent.
 __device__ __forceinline__ float wide_mi(int m, double all, float ttx) {
     const int e = __builtin_amdgcn_frexp_exp(all) - kWideShift;
-    return ((float)(m - e) + ttx) - hw_log2((float)__builtin_amdgcn_frexp_mant(all));
+    return finite_term(((float)(m - e) + ttx) - hw_log2((float)__builtin_amdgcn_frexp_mant(all)));
 }
 
 }  // namespace dm
