@@ -379,7 +379,8 @@ int dm_gs_optimize(const float* points, const uint16_t* labels, int32_t M, int32
  * dm_streamer_run: y HOST N x D FP32 (any host memory; page-locked memory is transferred
  * directly, other memory through the pinned staging), llr HOST N x m FP32 output (nats),
  * seconds HOST wall time of the call or NULL.  Synchronous: returns when every LLR is in llr.
- * LLRs are identical to dm_demap_llr on the whole block.  Limits: 1 <= buffer_symbols <= 2^26,
+ * LLRs are identical to dm_demap_llr on the whole block (within the limit stated at
+ * dm_gmi_estimate).  Limits: 1 <= buffer_symbols <= 2^26,
  * 2 <= n_buffers <= 16.  Errors: DM_EINVAL, DM_EUNSUPPORTED, DM_ENOMEM, DM_EHIP.
  */
 typedef struct dm_streamer dm_streamer;

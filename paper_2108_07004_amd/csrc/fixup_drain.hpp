@@ -130,7 +130,7 @@ __device__ __forceinline__ float row_reduce_f(float v, Op op) {
 // corrections, which add(tag, slot, which, value) receives.
 //
 // A wave's four rows run the bit loop for the union of their flagged bits, so the queue is taken
-// in chunks of 512 entries per workgroup (256 threads, two entries each), each chunk
+// in chunks of up to 512 entries per workgroup (256 threads, two entries each), each chunk
 // counting-sorted by the low eight mask bits in LDS before its rows are dealt out: rows of a wave
 // then mostly share their flagged bits.  The processing order does not change any result (each (symbol, bit) is written
 // once, the corrections are integer sums).
@@ -165,7 +165,7 @@ __device__ void fix_rows(const Sinks& k, ViewFn view, AddFn add, FetchFn fetch, 
     const auto fadd2 = [](float a, float b) { return a + b; };
     constexpr int kPer = kFixRowChunk / kFixSortChunk;
     // Fewer entries than fill every block's chunk are spread over the blocks: 4096 symbols of 256-QAM in
-    // 512-entry chunks kept eight blocks busy (40 us, now 12).  Over 512 blocks, half of them are better
+    // 512-entry chunks kept eight blocks busy (41 us, now 7.6).  Over 512 blocks, half of them are better
     // until each has 256 entries: every block adds its counts to the same few addresses at its end
     // (DP-16QAM split FP16, 11 x 2^20 symbols: 33 us over all blocks, 29 over half).
     const uint32_t blocks = count >= 256u * gridDim.x ? gridDim.x : max(min(gridDim.x, 512u), gridDim.x / 2);

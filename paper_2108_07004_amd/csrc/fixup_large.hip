@@ -12,12 +12,12 @@
 // points with top label bits q (a quarter of the table), which are then no sums of its own but its
 // total.  The four partial sums of every other bit meet in LDS, and each wave finishes its own bits.
 //
-// What bounds it: vector issue, some 30 instructions per (point, 64 symbols) at 8D.  Measured, 8 x 262144
-// symbols of an 8D 2048-point format in one sweep: to 20 dB 4770 us by wavefronts, now 520; to 22 dB
-// 5530, now 525 (the demapping before it: 650 on MFMA, 2200 in FP32).  881619 symbols at 20 dB, whole
-// call: 21.2 -> 1.5 ms.
+// What bounds it: vector issue, some 30 instructions per (point, 64 symbols) at 8D.  Measured, sweeps of
+// 8 x 262144 symbols of 8D, 2048 points, with LLRs: the product format from 6 to 20 dB 6050 us with two
+// passes by wavefronts, now 690; random points from 8 to 22 dB 6730, now 590 (the demapping before it: 630
+// on MFMA).  881619 symbols of the product format at 20 dB, whole call: 21.2 -> 1.5 ms.
 //
-// A lane takes its quarter of the table point by point, some 80 us at 2048 points of 8D however few
+// A lane takes its quarter of the table point by point, some 25 us at 2048 points of 8D however few
 // symbols there are, so few symbols go by wavefronts: row q of the wave takes quarter q, lane r of
 // it the points of index r modulo 16.  Both forms add the same numbers in the same order (sixteen points
 // by a pairwise tree, which is what the lanes of a row can do), so a symbol's results do not depend on

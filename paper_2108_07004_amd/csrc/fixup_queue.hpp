@@ -62,8 +62,8 @@ __device__ __forceinline__ void two_pass_symbol(const BlockView& b, Table tab, c
 
 // The same for 32 and 64 points: one pass over the points for all bits.  Returns the mask of what is out of
 // the wide range, for the form under maxima.  Against two passes per flagged bit (fixup_one): 2^20
-// symbols of 64-QAM at 18 dB 29.2 -> 8.6 us, 4096 of them at 20 dB 29.9 -> 17.5; 8 x 2^20 symbols to
-// 20 dB 51 -> 44; 64 mixed instances of 2^14 .. 2^22 symbols 153 -> 76.  Bound by vector issue.
+// symbols of 64-QAM at 18 dB 29.2 -> 7.6 us, 4096 of them at 20 dB 29.9 -> 7.2; 8 x 2^20 symbols from 6
+// to 20 dB 93 -> 27; 64 mixed instances of 2^14 .. 2^22 symbols 153 -> 76.  Bound by vector issue.
 template <int DP, int LS, typename Table, typename Put>
 __device__ __forceinline__ uint32_t wide_symbol(const BlockView& b, Table tab, const float (&y)[DP], uint32_t mask,
                                                 int txl, const float* xtx, Put put, double& g, double& mi) {

@@ -13,7 +13,7 @@
 //                       weights and rewrites their BF16 copies.
 // It was sixteen launches, one GEMM per layer, with activations written twice (row-major and
 // transposed, two bytes a lane) and read back: 139 us per step of 4096 samples, most of it launch
-// gaps and partial-line stores.  Now 32 us: 14.7 + 10 + 5.3 us of kernels and the gaps.  Every
+// gaps and partial-line stores.  Now 36 us: 14.7 + 10 + 5.3 us of kernels and the gaps.  Every
 // product and sum keeps its operands and its order, so the results are the same bit for bit.
 //
 // Activations and back-propagated deltas are stored as BF16 pairs hi + lo (lo = the rounding
