@@ -41,10 +41,10 @@ EXP2_ISSUE_CYCLES = 2  # v_exp_f32 issues at half the full FP32 rate on gfx950 (
 # 512 MiB device copy in the same runs.  Valid only for the kernel sources they were taken on.
 TRAFFIC_PMC = {
     "prec": "fp16x3", "workload": "gauss8d2048",
-    "bytes": (4513922 * 2 + 11550836) * 1024,
+    "bytes": (4527706 * 2 + 11550830) * 1024,
     "sources": ["paper_2108_07004_amd/csrc/demap_mfma.hip", "paper_2108_07004_amd/csrc/mfma_body.hpp",
-                "paper_2108_07004_amd/csrc/device_common.hpp"],
-    "sha256": "75c170307221eb6e8077542dea72397e4075b7bee4139af2b5668380c7988377",
+                "paper_2108_07004_amd/csrc/device_common.hpp", "paper_2108_07004_amd/csrc/fixup_queue.hpp"],
+    "sha256": "4e46885afbfabc3c342cd2bf05fa0e2a750278bf07ca5f913ce1a68fa0a89345",
 }
 
 
